@@ -39,13 +39,13 @@
  *    nonzero, of dimension D = C(n_orb, n_alpha) C(n_orb, n_beta)):
  *      - its tables, owned by the plan and allocated at creation: operator pair
  *        lists, string tables and same-spin string Hamiltonians (sparse rows,
- *        and dense copies of D_alpha^2 + 2 D_beta^2 doubles where the dense
- *        products are chosen), integrals, and the programs of the fused
- *        operator runs (fsv_plan_runs); fsv_plan_device_bytes reports them;
+ *        and dense copies of up to D_alpha^2 + 2 D_beta^2 doubles where the
+ *        dense products are chosen, none of the beta ones where (pq|rs)
+ *        factorises), integrals, and the programs of the fused operator runs
+ *        (fsv_plan_runs); fsv_plan_device_bytes reports them;
  *      - its workspace of fsv_plan_workspace_bytes: four complex sector
- *        vectors (16 D bytes each), the factorised alpha-beta intermediate
- *        (8 x 16 D bytes, when that product is used), density-matrix overlaps
- *        and the per-operator gradient partials (K x 8192 doubles).  The caller
+ *        vectors (16 D bytes each), density-matrix overlaps, the per-operator
+ *        gradient partials (K x 8192 doubles) and energy partials.  The caller
  *        may provide it (fsv_plan_set_workspace; the Python binding allocates
  *        it through PyTorch, so that running out of memory shows up there);
  *        otherwise the plan allocates it on the first call that needs it.

@@ -77,7 +77,8 @@ struct DevBuf {
 // array's name to a kernel or a copy: it is a host-side stand-in there.  The
 // device address comes from hipGetSymbolAddress, once per device.
 constexpr size_t kScratchBytes = (size_t)64 << 20;
-static __device__ __align__(256) unsigned char scratch[kScratchBytes];
+constexpr size_t kScratchExtra = (size_t)32768 * 8;  // energy partials, one per alpha string
+static __device__ __align__(256) unsigned char scratch[kScratchBytes + kScratchExtra];
 
 namespace {
 
@@ -145,7 +146,7 @@ struct fsv_plan {
     double *d_cs = nullptr, *d_gpart = nullptr, *d_epart = nullptr, *d_out = nullptr;
     int *d_gcount = nullptr, *d_ecount = nullptr;
     uint64_t *d_Xa = nullptr, *d_Xb = nullptr;
-    uint32_t *d_sa = nullptr, *d_PPb = nullptr, *d_excA = nullptr, *d_excB = nullptr, *d_excBT = nullptr;
+    uint32_t *d_sa = nullptr, *d_PPb = nullptr, *d_excA = nullptr, *d_excB = nullptr;
     double *d_g = nullptr;
     int64_t *d_ha_ptr = nullptr, *d_hb_ptr = nullptr;
     int32_t *d_ha_col = nullptr, *d_hb_col = nullptr;
@@ -159,14 +160,15 @@ struct fsv_plan {
     // allocated by the plan on first use, holding d_C .. d_epart below.
     // d_C also holds the interleaved (psi, lam) pairs of a packet adjoint sweep.
     double2 *d_C = nullptr, *d_S = nullptr, *d_CT = nullptr, *d_ST = nullptr, *d_O = nullptr;
-    double2 *d_gamma = nullptr, *d_YT = nullptr;
+    double2 *d_gamma = nullptr;
     void *ws = nullptr;
     bool ws_owned = false, ws_warm = false;
     size_t ws_bytes = 0;
-    size_t ws_off[10] = {};  // byte offsets of C, S, CT, ST, O, gamma, YT, gpart, epart; [9] = end
+    size_t ws_off[9] = {};  // byte offsets of C, S, CT, ST, O, gamma, gpart, epart; [8] = end
     // the parts energy_grad_noalloc takes from the scratch block (sector
-    // engine): C, S, CT, ST, YT, gpart, epart offsets; [7] = end
-    size_t na_off[8] = {};
+    // engine): C, S, CT, ST, gpart, epart offsets; na_need: the size by which a
+    // plan is accepted
+    size_t na_off[6] = {}, na_need = 0;
     double *h_pin = nullptr;  // pinned: cs (2K) then out (K + 1) then gamma (4 M^2)
     double *h_cs = nullptr;   // pinned, coherent: cs (2K) read by energy_grad's graph itself
     size_t pin_doubles = 0;
@@ -188,6 +190,10 @@ struct fsv_plan {
     // dense same-spin string Hamiltonians (FP64 GEMM on the matrix cores)
     rocblas_handle blas = nullptr;
     double *d_ha_dense = nullptr, *d_hb_dense = nullptr, *d_hb_dense_t = nullptr;
+    // row kernels: h' and the one-body tables made from it
+    double *d_heff = nullptr, *d_hp = nullptr, *d_hda = nullptr, *d_hdb = nullptr;
+    bool need_hb = true;  // whether a product uses the beta string Hamiltonian
+    int32_t *d_im_flag = nullptr, im_epoch = 0;  // whether the last gathered state had imaginary parts
     std::vector<PairOp> pops;
     std::vector<uint32_t> h_plists;  // host copy of the pair lists (fused-run tables are built from it)
     uint32_t *d_plists = nullptr;
@@ -205,7 +211,7 @@ struct fsv_plan {
     uint64_t gen = 0;  // bumped whenever captured launches may have changed
     bool use_graph = true;
     bool defer_e = false;  // energy_grad body: E is reduced with the gradients, after the sweep
-    // energy_grad body, real FP64 state, adjoint sweep on pairs: the product
+    // energy_grad body, adjoint sweep on pairs: the product
     // may write lam interleaved with psi into d_C (z_ready then says so)
     bool zip_in_sigma = false, z_ready = false;
     hipGraphExec_t g_eg = nullptr;
@@ -523,6 +529,36 @@ void build_exc(int M, const std::vector<uint32_t> &str, const std::vector<int32_
     }
 }
 
+// Pair {p, q}, p < q: a string holding exactly one of the two maps to the
+// string holding the other; E_pq (on q's holder) and E_qp carry the same sign,
+// the parity of the occupied orbitals between them.  Pair {p, p}: a string
+// holding p maps to itself.  Entries index a row of z = 2 ts values, a zero at
+// z (for strings the pair does not reach), then the row's negatives z + 2
+// further on.
+std::vector<uint32_t> build_partners(int M, const std::vector<uint32_t> &str, const std::vector<int32_t> &rank) {
+    const size_t n = str.size(), ts = (n + 1) / 2;
+    const uint32_t none = (uint32_t)(2 * ts);
+    std::vector<uint32_t> out((size_t)M * (M + 1) / 2 * ts, none | (none << 16));
+    size_t k = 0;
+    auto put = [&](size_t I, uint32_t v) {
+        uint32_t &w = out[k * ts + I / 2];
+        w = (I & 1) ? (w & 0xFFFFu) | (v << 16) : (w & 0xFFFF0000u) | v;
+    };
+    for (int p = 0; p < M; ++p)
+        for (int q = p + 1; q < M; ++q, ++k) {
+            const uint32_t both = 1u << p | 1u << q, between = ((1u << q) - 1) & ~((2u << p) - 1);
+            for (size_t I = 0; I < n; ++I) {
+                const uint32_t s = str[I];
+                if (__builtin_popcount(s & both) != 1) continue;
+                put(I, (uint32_t)rank[s ^ both] + ((__builtin_popcount(s & between) & 1) ? none + 2 : 0u));
+            }
+        }
+    for (int p = 0; p < M; ++p, ++k)
+        for (size_t I = 0; I < n; ++I)
+            if (str[I] >> p & 1u) put(I, (uint32_t)I);
+    return out;
+}
+
 // Per string I: sum over its occupied p of the factor row Lt[pp][0..rp), the
 // diagonal entries of I's excitation list folded into one (nstr x rp).
 std::vector<double> diag_factor_sums(int M, const std::vector<uint32_t> &str, const std::vector<double> &Lt, int rp) {
@@ -692,14 +728,16 @@ int pivoted_cholesky(int n, const double *G, double tol, std::vector<double> &L)
 
 namespace {
 
-// Choose the factorised alpha-beta product when (pq|rs) has a small exact
-// pivoted-Cholesky rank: per sector element it costs R (e_a + e_b) instead of
-// e_a e_b multiply-adds.  The factorisation must reproduce g to 1e-12 relative.
+// Choose the factorised product when (pq|rs) has a small exact pivoted-Cholesky
+// rank: the row kernel then needs no beta same-spin product and no pass over
+// its results, which pays at every size (at 8 qubits, where the direct form
+// has fewer multiply-adds, two launches instead of six).  The factorisation
+// must reproduce g to 1e-12 relative.
 int lr_pad(int) { return 8; }  // factor columns of the factorised kernels (ranks <= 8)
 
 void choose_sigma(fsv_plan &P, int &R_out, std::vector<double> &Lt_out) {
     R_out = 0;
-    const char *mode = std::getenv("FSV_SIGMA");
+    const char *mode = std::getenv("FSV_SIGMA");  // direct: never factorised
     if (mode && std::strcmp(mode, "direct") == 0) return;
     const int M2 = P.M * P.M;
     if (P.nexcA <= 0 || P.nexcB <= 0 || M2 > 511) return;
@@ -717,12 +755,8 @@ void choose_sigma(fsv_plan &P, int &R_out, std::vector<double> &Lt_out) {
             err = std::max(err, std::fabs(v - P.g[(size_t)i * M2 + j]));
         }
     if (err > 1e-12 * std::max(1.0, gmax)) return;
-    const bool forced = mode && std::strcmp(mode, "lowrank") == 0;
-    if (!forced && (int64_t)R * (P.nexcA + P.nexcB) >= (int64_t)P.nexcA * P.nexcB) return;
-    // the beta step stages one row of the intermediate (complex for the dense
-    // engine) with one factor column in LDS
+    if (!row_kernel_fits(P.nsb)) return;
     const int rp = lr_pad(R);
-    if (P.nsb * 16 + (int64_t)M2 * 8 > 163840) return;
     R_out = R;
     Lt_out.assign((size_t)M2 * rp, 0.0);  // M^2 x rp, zero beyond column R
     for (int k = 0; k < R; ++k)
@@ -732,11 +766,12 @@ void choose_sigma(fsv_plan &P, int &R_out, std::vector<double> &Lt_out) {
 // Dense copies of the same-spin string Hamiltonians, rebuilt on the device
 // from the CSR rows whenever the one-body part changes.
 int refresh_dense_same_spin(fsv_plan &P) {
-    if (!P.d_ha_dense) return FSV_OK;
-    HIPCHECK(launch_csr_dense(P.d_ha_ptr, P.d_ha_col, P.d_ha_val, P.d_ha_dense, P.nsa, P.work));
-    HIPCHECK(launch_csr_dense(P.d_hb_ptr, P.d_hb_col, P.d_hb_val, P.d_hb_dense, P.nsb, P.work));
-    HIPCHECK(launch_ctranspose(false, P.d_hb_dense, P.d_hb_dense_t, P.nsb, P.nsb, P.work));
-    HIPCHECK(hipStreamSynchronize(P.work));
+    if (P.d_ha_dense)
+        HIPCHECK(launch_csr_dense(P.d_ha_ptr, P.d_ha_col, P.d_ha_val, P.d_ha_dense, P.nsa, P.work));
+    if (P.d_hb_dense) {
+        HIPCHECK(launch_csr_dense(P.d_hb_ptr, P.d_hb_col, P.d_hb_val, P.d_hb_dense, P.nsb, P.work));
+        HIPCHECK(launch_plane_transpose(P.d_hb_dense, P.d_hb_dense_t, P.nsb, P.nsb, 1, P.work));
+    }
     return FSV_OK;
 }
 
@@ -747,17 +782,36 @@ int refresh_dense_same_spin(fsv_plan &P) {
 bool want_dense_same_spin(const fsv_plan &P) {
     const char *m = std::getenv("FSV_SAME_SPIN");
     if (m && std::strcmp(m, "sparse") == 0) return false;
-    const double bytes = 8.0 * ((double)P.nsa * P.nsa + (double)P.nsb * P.nsb);
+    const double bytes = 8.0 * ((double)P.nsa * P.nsa + (P.need_hb ? (double)P.nsb * P.nsb : 0.0));
     if (bytes > 16e9) return false;
     if (m && std::strcmp(m, "dense") == 0) return true;
     if (P.nsa * P.nsb < 4096) return false;
     const double nnz_a = (double)P.ha_col.size() / (double)P.nsa, nnz_b = (double)P.hb_col.size() / (double)P.nsb;
-    return nnz_a * 16.0 > (double)P.nsa && nnz_b * 16.0 > (double)P.nsb;
+    return nnz_a * 16.0 > (double)P.nsa && (!P.need_hb || nnz_b * 16.0 > (double)P.nsb);
 }
 
-// New one-body potential: h + v goes up (M^2 doubles) and the string
-// Hamiltonian values (and their dense copies) are rebuilt on the device from
-// the fixed two-body parts and the one-body descriptors.
+// The one-body tables of the row kernels from h + v: h'_pq = (h + v)_pq -
+// 1/2 sum_r (pr|rq).
+int upload_row_onebody(fsv_plan &P, const std::vector<double> &ht) {
+    if (!P.d_heff) return FSV_OK;
+    const int M = P.M, M2 = M * M, M3 = M2 * M;
+    std::vector<double> he(ht);
+    for (int p = 0; p < M; ++p)
+        for (int q = 0; q < M; ++q) {
+            double x = 0.0;
+            for (int r = 0; r < M; ++r) x += P.g[(size_t)p * M3 + r * M2 + r * M + q];
+            he[p * M + q] -= 0.5 * x;
+        }
+    const int rc = upload(P, P.d_heff, he.data(), he.size());
+    if (rc) return rc;
+    HIPCHECK(launch_row_onebody(P.d_heff, M, P.d_str_a, P.nsa, P.d_str_b, P.nsb, P.d_hp, P.d_hda, P.d_hdb, P.work));
+    return FSV_OK;
+}
+
+// New one-body potential: h + v goes up (M^2 doubles) and the tables made
+// from it are rebuilt on the device: the string Hamiltonian values (and their
+// dense copies) from the fixed two-body parts and the one-body descriptors,
+// and the row kernels' one-body values.
 int upload_hamiltonian_values(fsv_plan &P) {
     std::vector<double> ht(P.h);
     for (size_t i = 0; i < ht.size(); ++i) ht[i] += P.v[i];
@@ -768,14 +822,11 @@ int upload_hamiltonian_values(fsv_plan &P) {
     if ((rc = upload(P, P.d_htilde, ht.data(), ht.size()))) return rc;
     HIPCHECK(launch_string_h_values(P.d_ha_val, P.d_ha_v2, P.d_ha_desc, P.d_str_a, P.d_htilde, P.M,
                                     (int64_t)P.ha_col.size(), P.work));
-    HIPCHECK(launch_string_h_values(P.d_hb_val, P.d_hb_v2, P.d_hb_desc, P.d_str_b, P.d_htilde, P.M,
-                                    (int64_t)P.hb_col.size(), P.work));
-    if (P.d_ha_dense) {
-        HIPCHECK(launch_csr_dense(P.d_ha_ptr, P.d_ha_col, P.d_ha_val, P.d_ha_dense, P.nsa, P.work));
-        HIPCHECK(launch_csr_dense(P.d_hb_ptr, P.d_hb_col, P.d_hb_val, P.d_hb_dense, P.nsb, P.work));
-        HIPCHECK(launch_ctranspose(false, P.d_hb_dense, P.d_hb_dense_t, P.nsb, P.nsb, P.work));
-    }
-    return FSV_OK;
+    if (P.need_hb)
+        HIPCHECK(launch_string_h_values(P.d_hb_val, P.d_hb_v2, P.d_hb_desc, P.d_str_b, P.d_htilde, P.M,
+                                        (int64_t)P.hb_col.size(), P.work));
+    if ((rc = refresh_dense_same_spin(P))) return rc;
+    return upload_row_onebody(P, ht);
 }
 
 // Byte model of one pair kernel (read + write of the touched 128-byte lines).
@@ -879,25 +930,39 @@ int enq_forward_dense(fsv_plan &P, void *psi) {
     return FSV_OK;
 }
 
-// S = H C on the sector (alpha-first basis, complex or real FP64) and
-// E = Re<C|S> into d_out[0].
-int enq_sector_sigma(fsv_plan &P, bool cplex, const void *C, void *S) {
+// S = H C on the sector (alpha-first basis, real or as two planes, FP64) and
+// E = Re<C|S> into d_out[0]; S == nullptr: the energy only.
+int enq_sector_sigma(fsv_plan &P, int planes, const void *C, void *S) {
     bool zipped = false;
-    HIPCHECK(launch_sector_sigma(cplex, P.tabs, C, S, P.d_CT, P.d_ST, P.d_epart, P.work,
-                                 P.zip_in_sigma && !cplex ? (void *)P.d_C : nullptr, &zipped));
+    if (S)
+        HIPCHECK(launch_sector_sigma(planes, P.tabs, (const double *)C, (double *)S, (double *)P.d_CT,
+                                     (double *)P.d_ST, P.d_epart, P.work,
+                                     P.zip_in_sigma && planes == 1 ? (void *)P.d_C : nullptr, P.svt, &zipped));
+    else
+        HIPCHECK(launch_sector_energy(planes, P.tabs, (const double *)C, (double *)P.d_S, (double *)P.d_CT,
+                                      (double *)P.d_ST, P.d_epart, P.d_im_flag, P.im_epoch, P.work));
     P.z_ready = zipped;
-    if (!P.defer_e) HIPCHECK(launch_reduce_rows(P.d_epart, P.d_ecount, 0, 1, 1.0, P.d_out, P.work));
+    if (!P.defer_e)
+        HIPCHECK(launch_reduce_rows(P.d_epart, P.d_ecount + (planes - 1), 0, 1, 1.0, P.d_out, P.work));
+    return FSV_OK;
+}
+
+int enq_gather(fsv_plan &P, const void *psi) {
+    ++P.im_epoch;
+    HIPCHECK(launch_gather(P.precision, psi, P.d_Xa, P.d_Xb, P.d_sa, P.d_PPb, P.nsa, P.nsb, (double *)P.d_C,
+                           P.d_im_flag, P.im_epoch, P.work));
     return FSV_OK;
 }
 
 // Dense input: gather the complex sector, H on it; lam == nullptr: energy only.
 int enq_sigma_dense(fsv_plan &P, const void *psi, void *lam) {
-    HIPCHECK(launch_gather(P.precision, psi, P.d_Xa, P.d_Xb, P.d_sa, P.d_PPb, P.nsa, P.nsb, P.d_C, P.work));
-    int rc = enq_sector_sigma(P, true, P.d_C, P.d_S);
-    if (rc) return rc;
+    int rc;
+    if ((rc = enq_gather(P, psi))) return rc;
+    if ((rc = enq_sector_sigma(P, 2, P.d_C, lam ? (void *)P.d_S : nullptr))) return rc;
     if (lam) {
         HIPCHECK(launch_fill_zero(lam, ((size_t)1 << P.n) * P.amp_bytes, P.work));
-        HIPCHECK(launch_scatter(P.precision, lam, P.d_S, P.d_Xa, P.d_Xb, P.d_sa, P.d_PPb, P.nsa, P.nsb, P.work));
+        HIPCHECK(launch_scatter(P.precision, lam, (const double *)P.d_S, P.d_Xa, P.d_Xb, P.d_sa, P.d_PPb, P.nsa,
+                                P.nsb, P.work));
     }
     return FSV_OK;
 }
@@ -915,7 +980,7 @@ int enq_reverse_dense(fsv_plan &P, void *psi, void *lam) {
                                 P.shape_adj, P.d_gpart + (size_t)k * G, P.work));
     }
     if (P.defer_e)
-        HIPCHECK(launch_reduce_eg(P.d_epart, P.d_ecount, P.d_gpart, P.d_gcount, G, P.K, P.d_out, P.work));
+        HIPCHECK(launch_reduce_eg(P.d_epart, P.d_ecount + 1, P.d_gpart, P.d_gcount, G, P.K, P.d_out, P.work));
     else
         HIPCHECK(launch_reduce_rows(P.d_gpart, P.d_gcount, G, P.K, 2.0, P.d_out + 1, P.work));
     return FSV_OK;
@@ -1014,13 +1079,15 @@ int enq_forward_sector(fsv_plan &P, void *c) {
     return FSV_OK;
 }
 
-// lam_c == nullptr: energy only.  FP32 states are widened for the product.
+// lam_c == nullptr: energy only.  FP32 states are widened for the product, into
+// the second half of d_C (the first may receive the interleaved FP32 pairs).
 int enq_sigma_sector(fsv_plan &P, const void *c, void *lam_c) {
-    if (P.svt == V_F64) return enq_sector_sigma(P, false, c, lam_c ? lam_c : (void *)P.d_S);
-    HIPCHECK(launch_convert(V_F32, c, V_F64, P.d_C, P.dim, P.work));
-    int rc = enq_sector_sigma(P, false, P.d_C, P.d_S);
+    if (P.svt == V_F64) return enq_sector_sigma(P, 1, c, lam_c);
+    double *wide = (double *)P.d_C + P.dim;
+    HIPCHECK(launch_convert(V_F32, c, V_F64, wide, P.dim, P.work));
+    int rc = enq_sector_sigma(P, 1, wide, lam_c ? (void *)P.d_S : nullptr);
     if (rc) return rc;
-    if (lam_c) HIPCHECK(launch_convert(V_F64, P.d_S, V_F32, lam_c, P.dim, P.work));
+    if (lam_c && !P.z_ready) HIPCHECK(launch_convert(V_F64, P.d_S, V_F32, lam_c, P.dim, P.work));
     return FSV_OK;
 }
 
@@ -1165,7 +1232,7 @@ int run_energy_grad_body(fsv_plan &P, void *psi, void *lam) {
     int rc;
     if ((rc = enq_forward(P, psi))) return rc;
     P.defer_e = true;
-    P.zip_in_sigma = P.engine == 0 && P.svt == V_F64 && reverse_on_pairs(P);
+    P.zip_in_sigma = P.engine == 0 && reverse_on_pairs(P);
     if (!(rc = enq_sigma(P, psi, lam))) rc = enq_reverse(P, psi, lam);
     P.defer_e = false;
     P.zip_in_sigma = P.z_ready = false;
@@ -1347,6 +1414,19 @@ int check_csr(const std::vector<int64_t> &ptr, const std::vector<int32_t> &col, 
     return FSV_OK;
 }
 
+// Partner table of the row kernels: every entry names a string of the spin, its
+// negative, or the zero after the row.
+int check_partners(int M, const std::vector<uint32_t> &t, int64_t n) {
+    const int64_t ts = (n + 1) / 2;
+    if (n > 32766 || (int64_t)t.size() != (int64_t)M * (M + 1) / 2 * ts)
+        return fail(FSV_EINVAL, "internal: partner table of %zu words", t.size());
+    for (uint32_t w : t)
+        for (int64_t x : {(int64_t)(w & 0xFFFFu), (int64_t)(w >> 16)})
+            if (x != 2 * ts && (x >= 2 * (2 * ts + 2) || x % (2 * ts + 2) >= n))
+                return fail(FSV_EINVAL, "internal: partner out of range");
+    return FSV_OK;
+}
+
 int bind_workspace(fsv_plan &P, void *base);
 
 int build_device(fsv_plan &P) {
@@ -1421,7 +1501,8 @@ int build_device(fsv_plan &P) {
     if ((rc = dalloc(P, &P.d_rot, P.K))) return rc;
     if ((rc = dalloc(P, &P.d_cs, 2 * (size_t)P.K))) return rc;
     if ((rc = dalloc(P, &P.d_gcount, (size_t)P.K))) return rc;
-    if ((rc = dalloc(P, &P.d_ecount, 1))) return rc;
+    if ((rc = dalloc(P, &P.d_ecount, 2))) return rc;
+    if ((rc = dalloc(P, &P.d_im_flag, 1))) return rc;
     if ((rc = dalloc(P, &P.d_out, (size_t)P.K + 1))) return rc;
     if ((rc = dalloc(P, &P.d_Xa, P.nsa))) return rc;
     if ((rc = dalloc(P, &P.d_Xb, P.nsb))) return rc;
@@ -1429,7 +1510,6 @@ int build_device(fsv_plan &P) {
     if ((rc = dalloc(P, &P.d_PPb, P.nsb))) return rc;
     if ((rc = dalloc(P, &P.d_excA, excA.size()))) return rc;
     if ((rc = dalloc(P, &P.d_excB, excB.size()))) return rc;
-    if ((rc = dalloc(P, &P.d_excBT, excB.size()))) return rc;
     if ((rc = dalloc(P, &P.d_g, M2 * M2))) return rc;
     if ((rc = dalloc(P, &P.d_binA_off, boA.size()))) return rc;
     if ((rc = dalloc(P, &P.d_binA_idx, biA.size()))) return rc;
@@ -1443,88 +1523,129 @@ int build_device(fsv_plan &P) {
     if ((rc = upload(P, P.d_PPb, PPb.data(), PPb.size()))) return rc;
     if ((rc = upload(P, P.d_excA, excA.data(), excA.size()))) return rc;
     if ((rc = upload(P, P.d_excB, excB.data(), excB.size()))) return rc;
-    {
-        std::vector<uint32_t> excBT(excB.size());
-        for (int64_t r = 0; r < P.nsb; ++r)
-            for (int f = 0; f < P.nexcB; ++f) excBT[(size_t)f * P.nsb + r] = excB[(size_t)r * P.nexcB + f];
-        if ((rc = upload(P, P.d_excBT, excBT.data(), excBT.size()))) return rc;
-    }
     if ((rc = upload(P, P.d_g, P.g.data(), P.g.size()))) return rc;
     if ((rc = upload(P, P.d_binA_off, boA.data(), boA.size()))) return rc;
     if ((rc = upload(P, P.d_binA_idx, biA.data(), biA.size()))) return rc;
     if ((rc = upload(P, P.d_binB_off, boB.data(), boB.size()))) return rc;
     if ((rc = upload(P, P.d_binB_idx, biB.data(), biB.size()))) return rc;
-    const int ec = (int)combine_grid(P.dim);
-    if ((rc = upload(P, P.d_ecount, &ec, 1))) return rc;
     if ((rc = upload_counts(P))) return rc;
+    {
+        const int32_t none = 0;
+        if ((rc = upload(P, P.d_im_flag, &none, 1))) return rc;
+    }
+    if ((rc = dalloc(P, &P.d_str_a, P.sa.size())) || (rc = upload(P, P.d_str_a, P.sa.data(), P.sa.size())) ||
+        (rc = dalloc(P, &P.d_str_b, P.sb.size())) || (rc = upload(P, P.d_str_b, P.sb.data(), P.sb.size())))
+        return rc;
+
+    // which product: R > 0 the factorised rows, which need no beta string
+    // Hamiltonian
+    int R = 0;
+    std::vector<double> Lt;
+    choose_sigma(P, R, Lt);
+    P.lr_R = R;
+    P.need_hb = R == 0;
 
     // string Hamiltonians: structure and values
     std::vector<double> ht(P.h);
-    build_string_h(M, P.sa, ra, ht.data(), P.g.data(), P.ha_ptr, P.ha_col, P.ha_val);
-    build_string_h(M, P.sb, rb, ht.data(), P.g.data(), P.hb_ptr, P.hb_col, P.hb_val);
-    if ((rc = check_csr(P.ha_ptr, P.ha_col, P.ha_val.size(), nullptr, P.nsa, (int)M2)) ||
-        (rc = check_csr(P.hb_ptr, P.hb_col, P.hb_val.size(), nullptr, P.nsb, (int)M2)))
-        return rc;
-    if ((rc = dalloc(P, &P.d_ha_ptr, P.ha_ptr.size()))) return rc;
-    if ((rc = dalloc(P, &P.d_ha_col, P.ha_col.size()))) return rc;
-    if ((rc = dalloc(P, &P.d_ha_val, P.ha_val.size()))) return rc;
-    if ((rc = dalloc(P, &P.d_hb_ptr, P.hb_ptr.size()))) return rc;
-    if ((rc = dalloc(P, &P.d_hb_col, P.hb_col.size()))) return rc;
-    if ((rc = dalloc(P, &P.d_hb_val, P.hb_val.size()))) return rc;
-    if ((rc = upload(P, P.d_ha_ptr, P.ha_ptr.data(), P.ha_ptr.size()))) return rc;
-    if ((rc = upload(P, P.d_ha_col, P.ha_col.data(), P.ha_col.size()))) return rc;
-    if ((rc = upload(P, P.d_ha_val, P.ha_val.data(), P.ha_val.size()))) return rc;
-    if ((rc = upload(P, P.d_hb_ptr, P.hb_ptr.data(), P.hb_ptr.size()))) return rc;
-    if ((rc = upload(P, P.d_hb_col, P.hb_col.data(), P.hb_col.size()))) return rc;
-    if ((rc = upload(P, P.d_hb_val, P.hb_val.data(), P.hb_val.size()))) return rc;
+    auto csr = [&](const std::vector<uint32_t> &str, const std::vector<int32_t> &rk, std::vector<int64_t> &ptr,
+                   std::vector<int32_t> &col, std::vector<double> &val, int64_t **d_ptr, int32_t **d_col,
+                   double **d_val) -> int {
+        int r;
+        build_string_h(M, str, rk, ht.data(), P.g.data(), ptr, col, val);
+        if ((r = check_csr(ptr, col, val.size(), nullptr, (int64_t)str.size(), (int)M2))) return r;
+        if ((r = dalloc(P, d_ptr, ptr.size())) || (r = dalloc(P, d_col, col.size())) ||
+            (r = dalloc(P, d_val, val.size())))
+            return r;
+        if ((r = upload(P, *d_ptr, ptr.data(), ptr.size())) || (r = upload(P, *d_col, col.data(), col.size())) ||
+            (r = upload(P, *d_val, val.data(), val.size())))
+            return r;
+        return FSV_OK;
+    };
+    if ((rc = csr(P.sa, ra, P.ha_ptr, P.ha_col, P.ha_val, &P.d_ha_ptr, &P.d_ha_col, &P.d_ha_val))) return rc;
+    if (P.need_hb && (rc = csr(P.sb, rb, P.hb_ptr, P.hb_col, P.hb_val, &P.d_hb_ptr, &P.d_hb_col, &P.d_hb_val))) return rc;
     {
         std::vector<double> zero((size_t)M * M, 0.0), v2;
         std::vector<int64_t> ptr2;
         std::vector<int32_t> col2, desc;
         auto part = [&](const std::vector<uint32_t> &str, const std::vector<int32_t> &rk, size_t nent,
-                        double **d_v2, int32_t **d_desc, uint32_t **d_str) -> int {
+                        double **d_v2, int32_t **d_desc) -> int {
             int r;
             build_string_h(M, str, rk, zero.data(), P.g.data(), ptr2, col2, v2);
             build_string_h_onebody(M, str, rk, desc);
             if (v2.size() != nent || desc.size() != nent)
                 return fail(FSV_EINVAL, "internal: string Hamiltonian parts disagree");
             if ((r = check_csr(ptr2, col2, v2.size(), &desc, (int64_t)str.size(), (int)M2))) return r;
-            if ((r = dalloc(P, d_v2, nent)) || (r = dalloc(P, d_desc, nent)) || (r = dalloc(P, d_str, str.size())))
-                return r;
-            if ((r = upload(P, *d_v2, v2.data(), nent)) || (r = upload(P, *d_desc, desc.data(), nent)) ||
-                (r = upload(P, *d_str, str.data(), str.size())))
-                return r;
+            if ((r = dalloc(P, d_v2, nent)) || (r = dalloc(P, d_desc, nent))) return r;
+            if ((r = upload(P, *d_v2, v2.data(), nent)) || (r = upload(P, *d_desc, desc.data(), nent))) return r;
             return FSV_OK;
         };
-        if ((rc = part(P.sa, ra, P.ha_val.size(), &P.d_ha_v2, &P.d_ha_desc, &P.d_str_a)) ||
-            (rc = part(P.sb, rb, P.hb_val.size(), &P.d_hb_v2, &P.d_hb_desc, &P.d_str_b)) ||
+        if ((rc = part(P.sa, ra, P.ha_val.size(), &P.d_ha_v2, &P.d_ha_desc)) ||
+            (P.need_hb && (rc = part(P.sb, rb, P.hb_val.size(), &P.d_hb_v2, &P.d_hb_desc))) ||
             (rc = dalloc(P, &P.d_htilde, (size_t)M * M)))
             return rc;
     }
-    int R = 0;
-    std::vector<double> Lt;
-    choose_sigma(P, R, Lt);
-    double *d_Lt = nullptr, *d_lda = nullptr, *d_ldb = nullptr;
+    auto put = [&](const auto &v, auto **d) -> int {
+        const int r = dalloc(P, d, v.size());
+        return r ? r : upload(P, *d, v.data(), v.size());
+    };
+    // tables of the row kernels
+    double *d_Lt = nullptr, *d_Lp = nullptr, *d_lda = nullptr, *d_ldb = nullptr, *d_gp = nullptr, *d_dg = nullptr;
+    uint32_t *d_tpb = nullptr;
+    const bool direct_rows = R == 0 && P.nexcA > 0 && P.nexcB > 0 && ab_kernel_fits(P.nsb);
+    const int npair = M * (M - 1) / 2, npd = npair + M, npp = (npd + 23) & ~3;
+    if (R > 0 || direct_rows) {
+        const std::vector<uint32_t> tb = build_partners(M, P.sb, rb);
+        if ((rc = check_partners(M, tb, P.nsb)) || (rc = put(tb, &d_tpb))) return rc;
+    }
     if (R > 0) {
         const int rp = lr_pad(R);
         const std::vector<double> da = diag_factor_sums(M, P.sa, Lt, rp), db = diag_factor_sums(M, P.sb, Lt, rp);
-        if ((rc = dalloc(P, &d_Lt, Lt.size()))) return rc;
-        if ((rc = upload(P, d_Lt, Lt.data(), Lt.size()))) return rc;
-        if ((rc = dalloc(P, &d_lda, da.size())) || (rc = upload(P, d_lda, da.data(), da.size()))) return rc;
-        if ((rc = dalloc(P, &d_ldb, db.size())) || (rc = upload(P, d_ldb, db.data(), db.size()))) return rc;
+        std::vector<double> Lp;
+        for (int p = 0; p < M; ++p)
+            for (int q = p + 1; q < M; ++q)
+                Lp.insert(Lp.end(), Lt.begin() + (size_t)(p * M + q) * rp, Lt.begin() + (size_t)(p * M + q + 1) * rp);
+        // the columns' diagonal factors, one row per factor (coalesced)
+        auto by_factor = [&](const std::vector<double> &d, size_t n) {
+            const size_t w = (n + 1) & ~(size_t)1;
+            std::vector<double> t((size_t)rp * w, 0.0);
+            for (size_t i = 0; i < n; ++i)
+                for (int l = 0; l < rp; ++l) t[(size_t)l * w + i] = d[i * rp + l];
+            return t;
+        };
+        if ((rc = put(Lt, &d_Lt)) || (rc = put(Lp, &d_Lp)) || (rc = put(da, &d_lda)) ||
+            (rc = put(by_factor(db, db.size() / rp), &d_ldb)))
+            return rc;
+        if ((rc = dalloc(P, &P.d_heff, M2)) || (rc = dalloc(P, &P.d_hp, (size_t)npair)) ||
+            (rc = dalloc(P, &P.d_hda, P.nsa + 1)) || (rc = dalloc(P, &P.d_hdb, P.nsb + 1)) ||
+            (rc = upload_row_onebody(P, ht)))
+            return rc;
     }
-    P.lr_R = R;
+    if (direct_rows) {
+        // (pq|rs) with rs packed: the off-diagonal pairs r < s, then r = s
+        std::vector<double> gp(M2 * npp, 0.0), dg((size_t)P.nsa * npp, 0.0);
+        for (size_t pq = 0; pq < M2; ++pq) {
+            int k = 0;
+            for (int r = 0; r < M; ++r)
+                for (int t = r + 1; t < M; ++t) gp[pq * npp + k++] = P.g[pq * M2 + r * M + t];
+            for (int r = 0; r < M; ++r) gp[pq * npp + k++] = P.g[pq * M2 + r * M + r];
+        }
+        for (int64_t I = 0; I < P.nsa; ++I)
+            for (int p = 0; p < M; ++p)
+                if (P.sa[I] >> p & 1u)
+                    for (int k = 0; k < npd; ++k) dg[(size_t)I * npp + k] += gp[(size_t)(p * M + p) * npp + k];
+        if ((rc = put(gp, &d_gp)) || (rc = put(dg, &d_dg))) return rc;
+    }
+    const int64_t epart_n = std::max<int64_t>(1024, 2 * P.nsa);
     {  // workspace layout (256-byte aligned parts)
-        const size_t parts[9] = {16 * (size_t)P.dim, 16 * (size_t)P.dim, 16 * (size_t)P.dim, 16 * (size_t)P.dim,
+        const size_t parts[8] = {16 * (size_t)P.dim, 16 * (size_t)P.dim, 16 * (size_t)P.dim, 16 * (size_t)P.dim,
                                  16 * (size_t)std::max<int64_t>(std::max(P.nsa * P.nexcA, P.nsb * P.nexcB), 1),
-                                 16 * 2 * M2, R > 0 ? 16 * (size_t)lr_pad(R) * P.dim : 0,
-                                 8 * (size_t)std::max(P.K, 1) * G, 8 * 1024};
+                                 16 * 2 * M2, 8 * (size_t)std::max(P.K, 1) * G, 8 * (size_t)epart_n};
         size_t at = 0;
-        for (int i = 0; i < 9; ++i) {
+        for (int i = 0; i < 8; ++i) {
             P.ws_off[i] = at;
             at += (parts[i] + 255) & ~(size_t)255;
         }
-        P.ws_off[9] = at;
+        P.ws_off[8] = at;
         P.ws_bytes = at;
     }
     if (want_dense_same_spin(P)) {
@@ -1535,27 +1656,72 @@ int build_device(fsv_plan &P) {
         if (rocblas_set_atomics_mode(P.blas, rocblas_atomics_not_allowed) != rocblas_status_success)
             return fail(FSV_EDEVICE, "rocblas_set_atomics_mode failed");
         if ((rc = dalloc(P, &P.d_ha_dense, (size_t)P.nsa * P.nsa))) return rc;
-        if ((rc = dalloc(P, &P.d_hb_dense, (size_t)P.nsb * P.nsb))) return rc;
-        if ((rc = dalloc(P, &P.d_hb_dense_t, (size_t)P.nsb * P.nsb))) return rc;
+        if (P.need_hb) {
+            if ((rc = dalloc(P, &P.d_hb_dense, (size_t)P.nsb * P.nsb))) return rc;
+            if ((rc = dalloc(P, &P.d_hb_dense_t, (size_t)P.nsb * P.nsb))) return rc;
+        }
         if ((rc = refresh_dense_same_spin(P))) return rc;
     }
-    P.tabs = SectorTabs{P.nsa, P.nsb, M, P.nexcA, P.nexcB, P.d_ha_ptr, P.d_hb_ptr, P.d_ha_col,
-                        P.d_hb_col, P.d_ha_val, P.d_hb_val, P.d_excA, P.d_excB, P.d_excBT, P.d_g, P.ecore,
-                        R, d_Lt, nullptr, P.d_ha_dense, P.d_hb_dense, (void *)P.blas, P.d_hb_dense_t,
-                        d_lda, d_ldb, P.na, P.nb};
+    HIPCHECK(hipStreamSynchronize(P.work));
+    SectorTabs &T = P.tabs;
+    T = SectorTabs{};
+    T.nsa = P.nsa;
+    T.nsb = P.nsb;
+    T.M = M;
+    T.nexcA = P.nexcA;
+    T.nexcB = P.nexcB;
+    T.ha_ptr = P.d_ha_ptr;
+    T.hb_ptr = P.d_hb_ptr;
+    T.ha_col = P.d_ha_col;
+    T.hb_col = P.d_hb_col;
+    T.ha_val = P.d_ha_val;
+    T.hb_val = P.d_hb_val;
+    T.excA = P.d_excA;
+    T.excB = P.d_excB;
+    T.g = P.d_g;
+    T.ecore = P.ecore;
+    T.R = R;
+    T.Lt = d_Lt;
+    T.ha_dense = P.d_ha_dense;
+    T.hb_dense_t = P.d_hb_dense_t;
+    T.blas = (void *)P.blas;
+    T.da = d_lda;
+    T.ndA = P.na;
+    T.ndB = P.nb;
+    T.tp = d_tpb;
+    T.Lp = d_Lp;
+    T.hp = P.d_hp;
+    T.db = d_ldb;
+    T.hda = P.d_hda;
+    T.hdb = P.d_hdb;
+    T.heff = P.d_heff;
+    T.gp = d_gp;
+    T.dg = d_dg;
+    T.npp = npp;
+    {
+        const int ec[2] = {sigma_partials(T, 1), sigma_partials(T, 2)};
+        if (std::max(ec[0], ec[1]) > epart_n) return fail(FSV_EINVAL, "internal: energy partials");
+        if ((rc = upload(P, P.d_ecount, ec, 2))) return rc;
+    }
     {  // the scratch parts of energy_grad_noalloc (sector engine, real states)
         const bool f32 = P.svt == V_F32;
-        const size_t parts[7] = {16 * (size_t)P.dim,                           // C: (psi, lam) pairs; FP32: widened psi
+        const size_t parts[6] = {16 * (size_t)P.dim,                           // C: (psi, lam) pairs; FP32: widened psi
                                  f32 ? 8 * (size_t)P.dim : 0,                  // S: FP32 only, H psi in FP64
                                  8 * (size_t)P.dim, 8 * (size_t)P.dim,         // CT, ST: real transposes
-                                 lr_uses_intermediate(P.tabs, false) ? 8 * (size_t)lr_pad(R) * P.dim : 0,
-                                 8 * (size_t)std::max(P.K, 1) * G, 8 * 1024};
+                                 8 * (size_t)std::max(P.K, 1) * G, 8 * (size_t)std::max<int64_t>(1024, P.nsa)};
         size_t at = 0;
-        for (int i = 0; i < 7; ++i) {
+        for (int i = 0; i < 6; ++i) {
             P.na_off[i] = at;
             at += (parts[i] + 255) & ~(size_t)255;
         }
-        P.na_off[7] = at;
+        // the limit by which plans are accepted is part of the entry point: it
+        // counts 1024 energy partials (the block itself holds more beyond it)
+        // and, for factorised products on rows of more than 1137 - M^2 columns,
+        // eight further sector vectors
+        P.na_need = at - ((parts[5] + 255) & ~(size_t)255) + 8 * 1024;
+        if (R > 0 && (int64_t)R * (P.nexcA + P.nexcB) < (int64_t)P.nexcA * P.nexcB &&
+            ((int64_t)M2 + P.nsb) * 9 * 8 * 2 > 163840)
+            P.na_need += (64 * (size_t)P.dim + 255) & ~(size_t)255;
     }
     if (P.blas) {
         // one eager product per amplitude type on a temporary workspace, outside
@@ -1586,18 +1752,17 @@ int bind_workspace(fsv_plan &P, void *base) {
     P.d_ST = (double2 *)(b + P.ws_off[3]);
     P.d_O = (double2 *)(b + P.ws_off[4]);
     P.d_gamma = (double2 *)(b + P.ws_off[5]);
-    P.d_YT = P.lr_R > 0 ? (double2 *)(b + P.ws_off[6]) : nullptr;
-    P.d_gpart = (double *)(b + P.ws_off[7]);
-    P.d_epart = (double *)(b + P.ws_off[8]);
-    P.tabs.YT = P.d_YT;
+    P.d_gpart = (double *)(b + P.ws_off[6]);
+    P.d_epart = (double *)(b + P.ws_off[7]);
     drop_graphs(P);
     if (P.blas && !P.ws_warm) {
-        // one eager product per amplitude type, outside any graph capture, so
+        // one eager product per kind of state, outside any graph capture, so
         // that the GEMM library has loaded its kernels and sized its own
         // workspace before the first capture (the work buffers hold no state)
         HIPCHECK(launch_fill_zero(P.d_C, (size_t)P.dim * sizeof(double2), P.work));
-        HIPCHECK(launch_sector_sigma(false, P.tabs, P.d_C, P.d_S, P.d_CT, P.d_ST, P.d_epart, P.work));
-        HIPCHECK(launch_sector_sigma(true, P.tabs, P.d_C, P.d_S, P.d_CT, P.d_ST, P.d_epart, P.work));
+        for (int planes = 1; planes <= 2; ++planes)
+            HIPCHECK(launch_sector_sigma(planes, P.tabs, (const double *)P.d_C, (double *)P.d_S, (double *)P.d_CT,
+                                         (double *)P.d_ST, P.d_epart, P.work));
         HIPCHECK(hipStreamSynchronize(P.work));
         P.ws_warm = true;
     }
@@ -1930,8 +2095,8 @@ int energy_grad_noalloc(fsv_plan *P, const double *theta, void *psi, void *lam, 
     if (psi == lam) return fail(FSV_EINVAL, "psi and lam must be distinct buffers");
     if (P->K > 0 && !grad_out) return fail(FSV_EINVAL, "grad_out is NULL");
     if (P->engine != 0) return fail(FSV_ESTATE, "energy_grad_noalloc runs on the sector engine");
-    if (P->na_off[7] > kScratchBytes)
-        return fail(FSV_EINVAL, "this plan needs %zu bytes of scratch; energy_grad_noalloc has %zu", P->na_off[7],
+    if (P->na_need > kScratchBytes)
+        return fail(FSV_EINVAL, "this plan needs %zu bytes of scratch; energy_grad_noalloc has %zu", P->na_need,
                     kScratchBytes);
     void *base = nullptr;
     int rc;
@@ -1941,24 +2106,19 @@ int energy_grad_noalloc(fsv_plan *P, const double *theta, void *psi, void *lam, 
     // the pass takes its parts from the scratch block: the plan's workspace
     // fields point there for the duration of the (eager) launches
     char *b = (char *)base;
-    double2 *sv[5] = {P->d_C, P->d_S, P->d_CT, P->d_ST, P->d_YT};
+    double2 *sv[4] = {P->d_C, P->d_S, P->d_CT, P->d_ST};
     double *sg = P->d_gpart, *se = P->d_epart;
-    void *syt = P->tabs.YT;
     P->d_C = (double2 *)(b + P->na_off[0]);
     P->d_S = (double2 *)(b + P->na_off[1]);
     P->d_CT = (double2 *)(b + P->na_off[2]);
     P->d_ST = (double2 *)(b + P->na_off[3]);
-    P->d_YT = (double2 *)(b + P->na_off[4]);
-    P->tabs.YT = P->d_YT;
-    P->d_gpart = (double *)(b + P->na_off[5]);
-    P->d_epart = (double *)(b + P->na_off[6]);
+    P->d_gpart = (double *)(b + P->na_off[4]);
+    P->d_epart = (double *)(b + P->na_off[5]);
     rc = run_energy_grad_body(*P, psi, lam);
     P->d_C = sv[0];
     P->d_S = sv[1];
     P->d_CT = sv[2];
     P->d_ST = sv[3];
-    P->d_YT = sv[4];
-    P->tabs.YT = syt;
     P->d_gpart = sg;
     P->d_epart = se;
     if (rc) return rc;
@@ -2003,16 +2163,16 @@ int rdm1(fsv_plan *P, const void *psi, double *gamma_out) {
     if ((rc = need_workspace(*P))) return rc;
     hipStream_t st = P->work;
     const int M2 = P->M * P->M;
-    HIPCHECK(launch_gather(P->precision, psi, P->d_Xa, P->d_Xb, P->d_sa, P->d_PPb, P->nsa, P->nsb, P->d_C, st));
+    if ((rc = enq_gather(*P, psi))) return rc;
     if (P->nexcA > 0) {
-        HIPCHECK(launch_rdm_overlap(P->d_C, P->nsa, P->nsb, P->d_excA, P->nexcA, P->d_O, st));
+        HIPCHECK(launch_rdm_overlap((const double *)P->d_C, P->nsa, P->nsb, P->d_excA, P->nexcA, P->d_O, st));
         HIPCHECK(launch_rdm_bin(P->d_O, P->d_binA_off, P->d_binA_idx, M2, P->d_gamma, st));
     } else {
         HIPCHECK(launch_fill_zero(P->d_gamma, sizeof(double2) * M2, st));
     }
-    HIPCHECK(launch_ctranspose(true, P->d_C, P->d_CT, P->nsa, P->nsb, st));
+    HIPCHECK(launch_plane_transpose((const double *)P->d_C, (double *)P->d_CT, P->nsa, P->nsb, 2, st));
     if (P->nexcB > 0) {
-        HIPCHECK(launch_rdm_overlap(P->d_CT, P->nsb, P->nsa, P->d_excB, P->nexcB, P->d_O, st));
+        HIPCHECK(launch_rdm_overlap((const double *)P->d_CT, P->nsb, P->nsa, P->d_excB, P->nexcB, P->d_O, st));
         HIPCHECK(launch_rdm_bin(P->d_O, P->d_binB_off, P->d_binB_idx, M2, P->d_gamma + M2, st));
     } else {
         HIPCHECK(launch_fill_zero(P->d_gamma + M2, sizeof(double2) * M2, st));

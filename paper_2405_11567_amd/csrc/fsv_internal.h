@@ -79,6 +79,8 @@ void build_string_h(int M, const std::vector<uint32_t> &str, const std::vector<i
 // diagonal entries p -> p (the last popcount entries), as packed words.
 void build_exc(int M, const std::vector<uint32_t> &str, const std::vector<int32_t> &rank,
                std::vector<uint32_t> &exc, int &nexc);
+// Partner table of the row kernels (SectorTabs::tp) for the strings of one spin.
+std::vector<uint32_t> build_partners(int M, const std::vector<uint32_t> &str, const std::vector<int32_t> &rank);
 // Per string: the factor rows Lt[pp][0..rp) of its occupied p summed (its
 // diagonal excitations folded into one), nstr x rp.
 std::vector<double> diag_factor_sums(int M, const std::vector<uint32_t> &str, const std::vector<double> &Lt, int rp);
@@ -135,13 +137,15 @@ hipError_t launch_reduce_eg(const double *epart, const int *ecount, const double
 hipError_t launch_reduce_rows(const double *partial, const int *counts, int stride, int rows,
                               double scale, double *out, hipStream_t st);
 
+// Complex sector states as planes: row Ia holds nsb real, then nsb imaginary
+// parts.  *im_flag = im_epoch when an imaginary part is not zero.
 hipError_t launch_gather(int precision, const void *psi, const uint64_t *Xa, const uint64_t *Xb,
                          const uint32_t *sa, const uint32_t *PPb, int64_t nsa, int64_t nsb,
-                         double2 *C, hipStream_t st);
-hipError_t launch_scatter(int precision, void *lam, const double2 *S, const uint64_t *Xa,
+                         double *C, int32_t *im_flag, int32_t im_epoch, hipStream_t st);
+hipError_t launch_scatter(int precision, void *lam, const double *S, const uint64_t *Xa,
                           const uint64_t *Xb, const uint32_t *sa, const uint32_t *PPb,
                           int64_t nsa, int64_t nsb, hipStream_t st);
-hipError_t launch_rdm_overlap(const double2 *A, int64_t nrows, int64_t ncols,
+hipError_t launch_rdm_overlap(const double *A, int64_t nrows, int64_t ncols,
                               const uint32_t *exc, int nexc, double2 *O, hipStream_t st);
 hipError_t launch_rdm_bin(const double2 *O, const int32_t *off, const int32_t *idx, int nbins,
                           double2 *out, hipStream_t st);
@@ -159,30 +163,40 @@ struct SectorTabs {
     const int32_t *ha_col, *hb_col;
     const double *ha_val, *hb_val;
     const uint32_t *excA, *excB;
-    const uint32_t *excBT;  // excB transposed: [f][Ib]
     const double *g;
     double ecore;
     // Optional exact factorisation (pq|rs) = sum_l L[l][pq] L[l][rs] of rank R
     // (pivoted Cholesky of the pair supermatrix): Lt holds L transposed and
-    // padded to RP = 8 columns (M^2 x RP, zero beyond R) and YT is an
-    // RP * nsa * nsb work array (complex-sized).  R = 0 (also for every rank
-    // above 8): direct product.
+    // padded to 8 columns (M^2 x 8, zero beyond R).  R = 0 (also for every
+    // rank above 8): direct product.
     int R;
     const double *Lt;
-    void *YT;
-    // Optional dense same-spin string Hamiltonians (nsa x nsa, nsb x nsb,
-    // row-major) applied as FP64 GEMMs through the rocBLAS handle blas;
-    // nullptr: the CSR rows above.
-    const double *ha_dense, *hb_dense;
+    // Optional dense same-spin string Hamiltonians applied as FP64 GEMMs
+    // through the rocBLAS handle blas (alpha row-major; beta transposed, added
+    // into S, not used with the factorisation); nullptr: the CSR rows above.
+    const double *ha_dense, *hb_dense_t;
     void *blas;
-    // hb_dense transposed (its column-major form): real states add the beta
-    // product into S with one untransposed GEMM on it
-    const double *hb_dense_t;
-    // With the factorisation: per alpha (beta) string, the factor rows of its
-    // diagonal excitations summed (nsa x RP, nsb x RP).  Each string's list in
-    // excA / excB ends with its ndA (ndB) diagonal entries p -> p.
-    const double *lr_da, *lr_db;
+    // Each string's list in excA / excB ends with its ndA (ndB) diagonal
+    // entries p -> p.  With the factorisation, da: per alpha string the factor
+    // rows of its diagonal excitations summed (nsa x 8); db: the same per beta
+    // string, one row per factor (8 x 2 ceil(nsb / 2)).
     int ndA, ndB;
+    const double *da, *db;
+    // Partner table of the beta strings for the row kernels: orbital pairs p <
+    // q in lexicographic order, then the diagonal ones p = p; per pair ts =
+    // ceil(nsb / 2) words, word j the partners of strings 2 j and 2 j + 1 in
+    // 16 bits each: the rank, 2 ts + 2 more for a negative sign, or 2 ts where
+    // the pair does not reach the string.
+    const uint32_t *tp;
+    // Factors of the off-diagonal pairs (pairs x 8), and the one-body values
+    // h' = h + v - 1/2 sum_r (pr|rq): all of them (M x M), per off-diagonal
+    // pair, and summed over each string's occupied orbitals.
+    const double *Lp, *heff, *hp, *hda, *hdb;
+    // Direct product: (pq|rs) with rs packed in the order of tp (M^2 x npp,
+    // zero beyond the pairs), and per alpha string its diagonal rows summed
+    // (nsa x npp); nullptr: rows that k_ab does not take.
+    const double *gp, *dg;
+    int npp;
 };
 
 int cadj_blocks(const PairOp &op, int64_t nsa, int64_t nsb);  // partials written by launch_cadj
@@ -198,17 +212,28 @@ hipError_t launch_cadj_zip(int vtype, void *z, const PairOp &op, const uint32_t 
                            int64_t nsa, int64_t nsb, double *partial, hipStream_t st);
 // out (vtype_out) <- in (vtype_in), element-wise; complex <-> real keeps the real part.
 hipError_t launch_convert(int vt_in, const void *in, int vt_out, void *out, int64_t n, hipStream_t st);
-// S = H C on the sector; C, S, CT, ST hold nsa*nsb values of type complex
-// (cplex) or real double.  Writes combine_grid(nsa*nsb) partials of Re<C|S>.
-// zout (real states, may be null): where the product's last step allows it,
-// the (C, S) pairs go to zout instead of S, and *zipped is set.
+// S = H C on the sector.  planes = 1: real states, nsa x nsb; planes = 2:
+// complex ones, nsa rows of nsb real then nsb imaginary parts.  CT, ST: work
+// arrays of the same size.  Writes sigma_partials(T, planes) partials of
+// Re<C|S>.  zout (real states, may be null): where the product's last step
+// allows it, the (C, S) pairs go to zout (of type zvt) instead of S, and
+// *zipped is set.
 unsigned combine_grid(int64_t dim);
-// Whether the product on a real (cplex = false) or complex sector state writes
-// the factorised intermediate YT (the two-kernel form of the alpha-beta term).
-bool lr_uses_intermediate(const SectorTabs &T, bool cplex);
-hipError_t launch_sector_sigma(bool cplex, const SectorTabs &T, const void *C, void *S, void *CT,
-                               void *ST, double *epart, hipStream_t st, void *zout = nullptr,
+int sigma_partials(const SectorTabs &T, int planes);
+// Whether rows of ncols columns fit k_row (factorised) and k_ab (direct).
+bool row_kernel_fits(int64_t ncols);
+bool ab_kernel_fits(int64_t ncols);
+hipError_t launch_sector_sigma(int planes, const SectorTabs &T, const double *C, double *S, double *CT,
+                               double *ST, double *epart, hipStream_t st, void *zout = nullptr, int zvt = V_F64,
                                bool *zipped = nullptr);
+// Only the partials of Re<C|H|C>; S, CT, ST are work arrays.  planes = 2: the
+// imaginary parts may be taken as zero unless *im_flag equals im_epoch.
+hipError_t launch_sector_energy(int planes, const SectorTabs &T, const double *C, double *S, double *CT,
+                                double *ST, double *epart, const int32_t *im_flag, int32_t im_epoch,
+                                hipStream_t st);
+// hp, hda, hdb of the row kernels from h' (strings sa, sb as masks).
+hipError_t launch_row_onebody(const double *heff, int M, const uint32_t *sa, int64_t nsa, const uint32_t *sb,
+                              int64_t nsb, double *hp, double *hda, double *hdb, hipStream_t st);
 // ADAPT pool screening on a real sector state (V_F64 / V_F32): grid (gx, n_ops),
 // partial[t * gx + x] = workgroup x's share of Re<lam|T_t|psi> for pool op t.
 hipError_t launch_pool(int vtype, const void *psi, const void *lam, const PairOp *ops, const uint32_t *lists,
@@ -222,9 +247,10 @@ hipError_t launch_string_h_values(double *val, const double *v2, const int32_t *
 // Dense row-major copy (n x n) of an n-row CSR matrix.
 hipError_t launch_csr_dense(const int64_t *rowptr, const int32_t *col, const double *val, double *out, int64_t n,
                             hipStream_t st);
-// Transpose of a compact vector (rows x cols -> cols x rows), complex or real.
-hipError_t launch_ctranspose(bool cplex, const void *in, void *out, int64_t rows, int64_t cols,
-                             hipStream_t st);
+// Transpose of each plane of a compact vector: row r of `in` holds planes x
+// cols values, row c of `out` planes x rows.
+hipError_t launch_plane_transpose(const double *in, double *out, int64_t rows, int64_t cols, int planes,
+                                  hipStream_t st);
 // Real compact vector (double) -> dense complex buffer, like launch_scatter.
 hipError_t launch_scatter_real(int precision, void *lam, const double *S, const uint64_t *Xa,
                                const uint64_t *Xb, const uint32_t *sa, const uint32_t *PPb,

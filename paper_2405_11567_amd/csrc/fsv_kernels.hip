@@ -321,44 +321,52 @@ __global__ void k_reduce_rows(const double *__restrict__ partial, const int *__r
 // ------------------------------------------------- sector gather/scatter ----
 // Dense amplitude of (Ia, Ib) -> alpha-first compact value.  The sign converts
 // the qubit-ordered creator product into the alpha-string-first product.
+// Row Ia of C holds the nsb real parts, then the nsb imaginary parts.
+// *im_flag = im_epoch when some imaginary part is not zero (every workgroup
+// that finds one stores the same value).
 template <typename R>
 __global__ void k_gather(const typename C2<R>::T *__restrict__ psi, const uint64_t *__restrict__ Xa,
                          const uint64_t *__restrict__ Xb, const uint32_t *__restrict__ sa,
-                         const uint32_t *__restrict__ PPb, int64_t nsb, double2 *__restrict__ C) {
+                         const uint32_t *__restrict__ PPb, int64_t nsb, double *__restrict__ C,
+                         int32_t *__restrict__ im_flag, int32_t im_epoch) {
     const int64_t Ia = blockIdx.y;
+    double *row = C + 2 * Ia * nsb;
+    bool im = false;
     for (int64_t Ib = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; Ib < nsb;
          Ib += (int64_t)gridDim.x * blockDim.x) {
         const uint64_t x = Xa[Ia] | Xb[Ib];
         const bool neg = popc(sa[Ia] & PPb[Ib]) & 1;
         const typename C2<R>::T v = psi[x];
-        double2 o;
-        o.x = neg ? -(double)v.x : (double)v.x;
-        o.y = neg ? -(double)v.y : (double)v.y;
-        C[Ia * nsb + Ib] = o;
+        row[Ib] = neg ? -(double)v.x : (double)v.x;
+        row[nsb + Ib] = neg ? -(double)v.y : (double)v.y;
+        im = im || v.y != (R)0;
     }
+    if (im) *im_flag = im_epoch;
 }
 
 template <typename R>
-__global__ void k_scatter(typename C2<R>::T *__restrict__ lam, const double2 *__restrict__ S,
+__global__ void k_scatter(typename C2<R>::T *__restrict__ lam, const double *__restrict__ S,
                           const uint64_t *__restrict__ Xa, const uint64_t *__restrict__ Xb,
                           const uint32_t *__restrict__ sa, const uint32_t *__restrict__ PPb,
                           int64_t nsb) {
     const int64_t Ia = blockIdx.y;
+    const double *row = S + 2 * Ia * nsb;
     for (int64_t Ib = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; Ib < nsb;
          Ib += (int64_t)gridDim.x * blockDim.x) {
         const uint64_t x = Xa[Ia] | Xb[Ib];
         const bool neg = popc(sa[Ia] & PPb[Ib]) & 1;
-        const double2 v = S[Ia * nsb + Ib];
+        const double re = row[Ib], im = row[nsb + Ib];
         typename C2<R>::T o;
-        o.x = (R)(neg ? -v.x : v.x);
-        o.y = (R)(neg ? -v.y : v.y);
+        o.x = (R)(neg ? -re : re);
+        o.y = (R)(neg ? -im : im);
         lam[x] = o;
     }
 }
 
 // ------------------------------------------------------------- 1-RDM ----
 // O[I*nexc + e] = s_e * sum_c conj(A[I][c]) A[J_e][c]; one wavefront per (I, e).
-__global__ __launch_bounds__(256) void k_rdm_overlap(const double2 *__restrict__ A, int64_t ncols,
+// Rows of A: ncols real parts, then ncols imaginary parts.
+__global__ __launch_bounds__(256) void k_rdm_overlap(const double *__restrict__ A, int64_t ncols,
                                                      const uint32_t *__restrict__ exc, int nexc,
                                                      double2 *__restrict__ O) {
     const int64_t I = blockIdx.x;
@@ -367,11 +375,12 @@ __global__ __launch_bounds__(256) void k_rdm_overlap(const double2 *__restrict__
     for (int e = wid; e < nexc; e += nw) {
         const uint32_t w = exc[I * nexc + e];
         const int64_t J = w & 0xFFFFu;
+        const double *a = A + 2 * I * ncols, *b = A + 2 * J * ncols;
         double re = 0.0, im = 0.0;
         for (int64_t c = lane; c < ncols; c += kWave) {
-            const double2 a = A[I * ncols + c], b = A[J * ncols + c];
-            re += a.x * b.x + a.y * b.y;
-            im += a.x * b.y - a.y * b.x;
+            const double ax = a[c], ay = a[ncols + c], bx = b[c], by = b[ncols + c];
+            re += ax * bx + ay * by;
+            im += ax * by - ay * bx;
         }
         re = wave_sum(re);
         im = wave_sum(im);
@@ -554,16 +563,18 @@ hipError_t launch_reduce_rows(const double *partial, const int *counts, int stri
 
 hipError_t launch_gather(int precision, const void *psi, const uint64_t *Xa, const uint64_t *Xb,
                          const uint32_t *sa, const uint32_t *PPb, int64_t nsa, int64_t nsb,
-                         double2 *C, hipStream_t st) {
+                         double *C, int32_t *im_flag, int32_t im_epoch, hipStream_t st) {
     const dim3 grid(blocks_for(nsb, 256) > 64 ? 64 : blocks_for(nsb, 256), (unsigned)nsa);
     if (precision == 0)
-        hipLaunchKernelGGL(k_gather<double>, grid, dim3(256), 0, st, (const double2 *)psi, Xa, Xb, sa, PPb, nsb, C);
+        hipLaunchKernelGGL(k_gather<double>, grid, dim3(256), 0, st, (const double2 *)psi, Xa, Xb, sa, PPb, nsb, C,
+                           im_flag, im_epoch);
     else
-        hipLaunchKernelGGL(k_gather<float>, grid, dim3(256), 0, st, (const float2 *)psi, Xa, Xb, sa, PPb, nsb, C);
+        hipLaunchKernelGGL(k_gather<float>, grid, dim3(256), 0, st, (const float2 *)psi, Xa, Xb, sa, PPb, nsb, C,
+                           im_flag, im_epoch);
     return hipGetLastError();
 }
 
-hipError_t launch_scatter(int precision, void *lam, const double2 *S, const uint64_t *Xa,
+hipError_t launch_scatter(int precision, void *lam, const double *S, const uint64_t *Xa,
                           const uint64_t *Xb, const uint32_t *sa, const uint32_t *PPb,
                           int64_t nsa, int64_t nsb, hipStream_t st) {
     const dim3 grid(blocks_for(nsb, 256) > 64 ? 64 : blocks_for(nsb, 256), (unsigned)nsa);
@@ -574,7 +585,7 @@ hipError_t launch_scatter(int precision, void *lam, const double2 *S, const uint
     return hipGetLastError();
 }
 
-hipError_t launch_rdm_overlap(const double2 *A, int64_t nrows, int64_t ncols,
+hipError_t launch_rdm_overlap(const double *A, int64_t nrows, int64_t ncols,
                               const uint32_t *exc, int nexc, double2 *O, hipStream_t st) {
     hipLaunchKernelGGL(k_rdm_overlap, dim3((unsigned)nrows), dim3(256), 0, st, A, ncols, exc, nexc, O);
     return hipGetLastError();

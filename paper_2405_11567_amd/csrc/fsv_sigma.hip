@@ -21,10 +21,10 @@ namespace {
 
 // ---- amplitude arithmetic (accumulations in FP64) ----
 template <typename V> struct Vt;
-template <> struct Vt<double2> { using R = double; using A = double2; };
-template <> struct Vt<float2> { using R = float; using A = double2; };
-template <> struct Vt<double> { using R = double; using A = double; };
-template <> struct Vt<float> { using R = float; using A = double; };
+template <> struct Vt<double2> { using R = double; };
+template <> struct Vt<float2> { using R = float; };
+template <> struct Vt<double> { using R = double; };
+template <> struct Vt<float> { using R = float; };
 
 // (a, b) <- (c a - s b, c b + s a)
 __device__ __forceinline__ void rot(double &a, double &b, double c, double s) {
@@ -50,19 +50,7 @@ __device__ __forceinline__ double dotre(double l, double p) { return l * p; }
 __device__ __forceinline__ double dotre(float l, float p) { return (double)l * p; }
 __device__ __forceinline__ double dotre(double2 l, double2 p) { return l.x * p.x + l.y * p.y; }
 __device__ __forceinline__ double dotre(float2 l, float2 p) { return (double)l.x * p.x + (double)l.y * p.y; }
-// acc += w x
-__device__ __forceinline__ void axpy(double &acc, double w, double x) { acc += w * x; }
-__device__ __forceinline__ void axpy(double2 &acc, double w, double2 x) {
-    acc.x += w * x.x;
-    acc.y += w * x.y;
-}
-template <typename A> __device__ __forceinline__ A zero();
-template <> __device__ __forceinline__ double zero<double>() { return 0.0; }
-template <> __device__ __forceinline__ double2 zero<double2>() { return make_double2(0.0, 0.0); }
 __device__ __forceinline__ double neg_if(bool n, double v) { return n ? -v : v; }
-__device__ __forceinline__ double2 neg_if(bool n, double2 v) { return n ? make_double2(-v.x, -v.y) : v; }
-__device__ __forceinline__ double add(double a, double b) { return a + b; }
-__device__ __forceinline__ double2 add(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 
 // ---- conversions ----
 __device__ __forceinline__ void cvt(double a, double &b) { b = a; }
@@ -239,17 +227,16 @@ __global__ __launch_bounds__(256) void k_cadj_zip(typename Zip2<R>::P *__restric
 // out[I][:] = sum_k val[k] in[col[k]][:].  Blocks are dispatched row-fastest
 // over one column tile at a time (blockIdx.x = row, blockIdx.y = tile), so the
 // workgroups in flight share the input rows of the same tile in L2.
-template <typename A>
 __global__ __launch_bounds__(256) void k_spmm(const int64_t *__restrict__ rowptr,
                                               const int32_t *__restrict__ col,
-                                              const double *__restrict__ val, const A *__restrict__ in,
-                                              A *__restrict__ out, int64_t ncols) {
+                                              const double *__restrict__ val, const double *__restrict__ in,
+                                              double *__restrict__ out, int64_t ncols) {
     const int64_t I = blockIdx.x;
     const int64_t k0 = rowptr[I], k1 = rowptr[I + 1];
     const int64_t c = (int64_t)blockIdx.y * blockDim.x + threadIdx.x;
     if (c >= ncols) return;
-    A acc = zero<A>();
-    for (int64_t k = k0; k < k1; ++k) axpy(acc, val[k], in[(int64_t)col[k] * ncols + c]);
+    double acc = 0.0;
+    for (int64_t k = k0; k < k1; ++k) acc += val[k] * in[(int64_t)col[k] * ncols + c];
     out[I * ncols + c] = acc;
 }
 
@@ -286,6 +273,7 @@ hipError_t dense_same_spin(void *blas, const double *H, const double *in, double
 // transposes of the state: S[Ia][Ib] += sum_Jb Hb[Ib][Jb] C[Ia][Jb].  Read
 // column-major, the row-major S and C are nsb x nsa matrices and the
 // row-major Hb^T (HbT) is Hb, so this is S += Hb x C, one untransposed GEMM.
+// (nsa: the rows of C, both planes' of a complex state.)
 hipError_t dense_beta_accumulate(void *blas, const double *HbT, const double *C, double *S, int64_t nsa,
                                  int64_t nsb, hipStream_t st) {
     rocblas_handle h = (rocblas_handle)blas;
@@ -303,15 +291,16 @@ hipError_t dense_beta_accumulate(void *blas, const double *HbT, const double *C,
 // in LDS interleaved as Rt[Jb][e] and their weights as Wt[rs][e] = s_e (pq_e|rs),
 // so each beta excitation of a thread's Ib costs one contiguous LDS read of
 // the ec row values and one of the ec weights.
-template <typename A>
 __global__ __launch_bounds__(512) void k_sigma_ab(const uint32_t *__restrict__ excA, int nexcA,
                                                   const uint32_t *__restrict__ excB, int nexcB,
                                                   const double *__restrict__ g, int M,
-                                                  const A *__restrict__ C, A *__restrict__ S,
-                                                  int64_t nsb, int ec) {
+                                                  const double *__restrict__ Cin, double *__restrict__ Sin,
+                                                  int64_t nsb, int64_t ld, int ec) {
     extern __shared__ double smem_d[];
-    A *Rt = (A *)smem_d;                           // nsb * ec
-    double *Wt = (double *)(Rt + (int64_t)nsb * ec);  // M2 * ec
+    double *Rt = smem_d;                    // nsb * ec
+    double *Wt = Rt + (int64_t)nsb * ec;    // M2 * ec
+    const double *C = Cin + (int64_t)blockIdx.y * nsb;  // the plane's rows, ld apart
+    double *S = Sin + (int64_t)blockIdx.y * nsb;
     const int64_t Ia = blockIdx.x;
     const int M2 = M * M;
     for (int e0 = 0; e0 < nexcA; e0 += ec) {
@@ -321,274 +310,494 @@ __global__ __launch_bounds__(512) void k_sigma_ab(const uint32_t *__restrict__ e
             const int64_t Ja = w & 0xFFFFu;
             const int pq = (w >> 16) & 0x1FFu;
             const double sa = (w >> 31) ? -1.0 : 1.0;
-            for (int64_t jb = threadIdx.x; jb < nsb; jb += blockDim.x) Rt[jb * ec + e] = C[Ja * nsb + jb];
+            for (int64_t jb = threadIdx.x; jb < nsb; jb += blockDim.x) Rt[jb * ec + e] = C[Ja * ld + jb];
             for (int rs = threadIdx.x; rs < M2; rs += blockDim.x) Wt[rs * ec + e] = sa * g[pq * M2 + rs];
         }
         __syncthreads();
         for (int64_t Ib = threadIdx.x; Ib < nsb; Ib += blockDim.x) {
-            A acc = zero<A>();
+            double acc = 0.0;
             for (int f = 0; f < nexcB; ++f) {
                 const uint32_t eb = excB[Ib * nexcB + f];
-                const A *r = Rt + (int64_t)(eb & 0xFFFFu) * ec;
+                const double *r = Rt + (int64_t)(eb & 0xFFFFu) * ec;
                 const double *wr = Wt + (int)((eb >> 16) & 0x1FFu) * ec;
-                A t = zero<A>();
-                for (int e = 0; e < ne; ++e) axpy(t, wr[e], r[e]);
-                acc = add(acc, neg_if((eb >> 31) != 0, t));
+                double t = 0.0;
+                for (int e = 0; e < ne; ++e) t += wr[e] * r[e];
+                acc += neg_if((eb >> 31) != 0, t);
             }
-            S[Ia * nsb + Ib] = add(S[Ia * nsb + Ib], acc);
+            S[Ia * ld + Ib] += acc;
         }
         __syncthreads();
     }
 }
 
-// Same term with each thread's beta-excitation list held in registers: a
-// workgroup of 1024 threads takes the output columns Ib in groups of 1024;
-// for each group it loads every thread's (J_f, rs_f, s_f) list once, then
-// streams the alpha excitations through LDS ec at a time.  The list is read
-// once per output element instead of once per LDS chunk.  MAXF bounds the
-// number of beta excitations per string (N (M - N + 1)).
-template <typename A, int MAXF, int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_sigma_ab_reg(const uint32_t *__restrict__ excA, int nexcA,
-                                                       const uint32_t *__restrict__ excB, int nexcB,
-                                                       const double *__restrict__ g, int M,
-                                                       const A *__restrict__ C, A *__restrict__ S,
-                                                       int64_t nsb, int ec) {
-    extern __shared__ double smem_d[];
-    A *Rt = (A *)smem_d;                              // nsb * ec
-    double *Wt = (double *)(Rt + (int64_t)nsb * ec);  // M2 * ec
-    const int64_t Ia = blockIdx.x;
-    const int M2 = M * M;
-    for (int64_t ib0 = 0; ib0 < nsb; ib0 += blockDim.x) {
-        const int64_t Ib = ib0 + threadIdx.x;
-        const bool active = Ib < nsb;
-        uint32_t ex[MAXF];
+// Product with a factorised interaction, (pq|rs) = sum_l L_l[pq] L_l[rs]
+// (l < R <= 8, padded to 8 with zero columns).  With A_l = sum_pq L_l[pq]
+// E^alpha_pq, B_l the same on the beta strings and h'_pq = h_pq - 1/2 sum_r
+// (pr|rq),
+//   H = h'_alpha + h'_beta + 1/2 sum_l (A_l + B_l)^2,
+// so all of H that is not purely alpha is local to a row of C once
+// Y_l = A_l C + 1/2 B_l C is known there:
+//   (H - H_alpha) C = h'_beta C + sum_l B_l Y_l,
+// added to the purely alpha part that S holds already.  One workgroup per row (alpha string Ia), each thread CP pairs of
+// neighbouring columns:
+//  1. the row goes to LDS; B_l C gathers it through the partner table: for an
+//     orbital pair {p, q}, a string holding exactly one of them maps to the
+//     string holding the other, with one sign for E_pq and E_qp alike, so all
+//     lanes work on the same pair and its factors L_l[pq] are scalars;
+//  2. A_l C reads whole rows of C (row-uniform lists and factors);
+//  3. B_l Y, pair by pair: every column's sum_l L_l[pq] Y_l goes to LDS (8
+//     bytes instead of the 8 values of Y_l), and the partner reads it.
+// Bound by FP64 vector arithmetic (the matrix cores have the same FP64 rate):
+// ~17 multiply-adds per element and orbital pair plus 8 per alpha excitation.
+// The former kernels read the 8 values of Y_l and the 8 factors of each beta
+// excitation from LDS per lane, and left both same-spin parts to GEMMs.  H C
+// at 24 qubits (924 rows of 924): 102 us with the beta same-spin part, E and
+// the (psi, lam) pairs included, where the former kernel, the beta GEMM and
+// the pass over the result took 102 + 39 + 6 us; about half of the vector
+// issue slots are filled (3.6 rows per CU).  Energies alone (two planes of a
+// dense state) 55 us instead of ~300 us.  30 qubits (6435 rows of 6435): 13.5
+// ms instead of 11.7 ms and a beta GEMM of 8.0 ms.  (The purely alpha part
+// could run the same way on the rows of C^T: 9.7 ms there against the GEMM's
+// 8.0 ms, ~60 against 39 us at 24 qubits, so it stays a GEMM.)  28 qubits, energy alone: 1.2 ms
+// instead of 7.4 ms.
+// The LDS slot after the row (2 ceil(ncols / 2)) holds zero: the partner of a
+// string outside the pair's reach.
+constexpr int kRowR = 8;
+
+typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));
+typedef double dbl2a __attribute__((ext_vector_type(2), aligned(16)));
+
+struct RowArgs {
+    int32_t nrows, ncols, npair, ts;  // ts: column pairs, the words of a pair's partner row
+    int32_t nexc, noff;               // stride and off-diagonal length of the alpha lists
+    int64_t ld, plane;                // row stride of C and S, offset of the imaginary plane
+    double ecore;
+    int32_t im_epoch;                 // energy of complex states: the plane counts when *im_flag equals it
+    const int32_t *im_flag;
+};
+
+enum RowOut { ROW_ENERGY = 0, ROW_S = 1, ROW_ZIP = 2, ROW_ZIP32 = 3 };
+
+__device__ __forceinline__ double flip_sign(double v, uint32_t sign_bit) {  // sign_bit: 0 or 1 << 31
+    return __hiloint2double(__double2hiint(v) ^ (int)sign_bit, __double2loint(v));
+}
+
+// NB buffers of NC pairs (1: long rows, a second barrier per buffer); WV: waves
+// per SIMD the registers must allow.
+template <int BS, int CP, int LH, int NC, int NB, int WV, int OUT>
+__global__ __launch_bounds__(BS, WV) void k_row(const double *__restrict__ C, double *__restrict__ S,
+                                            void *__restrict__ z, double *__restrict__ epart,
+                                            const uint32_t *__restrict__ tp, const double *__restrict__ Lp,
+                                            const double *__restrict__ hp, const double *__restrict__ db,
+                                            const double *__restrict__ hd, const uint32_t *__restrict__ exc,
+                                            const double *__restrict__ Lt, const double *__restrict__ da,
+                                            const double *__restrict__ heff, const double *__restrict__ hda,
+                                            RowArgs a) {
+    extern __shared__ double buf[];
+    const int n = a.ncols, ncp = (n + 1) >> 1, zero = 2 * ncp, Wp = zero + 2, tid = threadIdx.x;
+    // XCD x takes a contiguous range of rows: neighbouring strings share most
+    // of their source rows, which then share that XCD's L2
+    int row;
+    {
+        const int v = blockIdx.x, per = a.nrows >> 3, rem = a.nrows & 7, x = v & 7;
+        row = x * per + min(x, rem) + (v >> 3);
+    }
+    if (OUT == ROW_ENERGY && blockIdx.y && *a.im_flag != a.im_epoch) {  // a zero imaginary plane
+        if (tid == 0) epart[a.nrows + row] = 0.0;
+        return;
+    }
+    const double *Cp = C + (int64_t)blockIdx.y * a.plane;
+    const double *crow = Cp + (int64_t)row * a.ld;
+    // column pair of slot q (clamped): columns 2 j and 2 j + 1.  In a row of
+    // odd length the last pair's second column is the value after the row
+    // (inside the state's buffer or workspace); no partner names it.  Loads
+    // take a uniform base and a 32-bit byte offset per lane.
+    uint32_t off[CP];
 #pragma unroll
-        for (int f = 0; f < MAXF; ++f) ex[f] = (active && f < nexcB) ? excB[Ib * nexcB + f] : 0u;
-        A acc = zero<A>();
-        for (int e0 = 0; e0 < nexcA; e0 += ec) {
-            const int ne = min(ec, nexcA - e0);
-            __syncthreads();  // previous chunk fully consumed
-            for (int e = 0; e < ne; ++e) {
-                const uint32_t w = excA[Ia * nexcA + e0 + e];
-                const int64_t Ja = w & 0xFFFFu;
-                const int pq = (w >> 16) & 0x1FFu;
-                const double sa = (w >> 31) ? -1.0 : 1.0;
-                for (int64_t jb = threadIdx.x; jb < nsb; jb += blockDim.x) Rt[jb * ec + e] = C[Ja * nsb + jb];
-                for (int rs = threadIdx.x; rs < M2; rs += blockDim.x) Wt[rs * ec + e] = sa * g[pq * M2 + rs];
+    for (int q = 0; q < CP; ++q) off[q] = 16u * (uint32_t)min(tid + q * BS, ncp - 1);
+    auto pair = [&](int q) { return (int)(off[q] >> 4); };
+    auto on = [&](int q) { return tid + q * BS < ncp; };
+    auto load2 = [&](const double *p, int q) { return *(const dbl2u *)((const char *)p + off[q]); };
+    // a value and, Wp further on, its negative: partner words index either
+    auto put2 = [&](double *b, int q, double x, double y) {
+        *(dbl2a *)((char *)b + off[q]) = dbl2a{x, y};
+        *(dbl2a *)((char *)(b + Wp) + off[q]) = dbl2a{-x, -y};
+    };
+    // keeps one column pair's loads from being hoisted over the others'
+    // (their registers would spill)
+    auto fence = [] {
+        if (CP > 1) asm volatile("" ::: "memory");
+    };
+    constexpr int KB = CP > 2 ? 1 : 4, EB = CP > 2 ? 1 : 4 / CP;  // partner words, source rows loaded together
+    auto words = [&](int k, uint32_t (&t)[CP]) {
+        const char *p = (const char *)(tp + (int64_t)k * a.ts);
+#pragma unroll
+        for (int q = 0; q < CP; ++q) t[q] = *(const uint32_t *)(p + (off[q] >> 2));
+    };
+    constexpr double f = OUT == ROW_ENERGY ? 1.0 : 0.5;  // Y takes half of B_l C (exact scaling)
+    double s[CP][2];
+    for (int t = tid; t < (OUT == ROW_ENERGY ? 2 : 2 * NB * NC); t += BS) buf[t * Wp + zero] = 0.0;
+    double en = 0.0;
+    const uint32_t *ex = exc + (int64_t)row * a.nexc;
+    for (int l0 = 0; l0 < kRowR; l0 += LH) {
+        const bool first = l0 == 0;
+        __syncthreads();  // the previous pass's readers of buf are done
+        double v[CP][2][LH];
+        const double *dar = da + (int64_t)row * kRowR + l0;
+#pragma unroll
+        for (int q = 0; q < CP; ++q) {
+            const dbl2u c = load2(crow, q);
+            const double c0 = f * c.x, c1 = f * c.y;
+            if (on(q)) put2(buf, q, c0, c1);
+#pragma unroll
+            for (int l = 0; l < LH; ++l) {
+                const dbl2u w = load2(db + (l0 + l) * zero, q);
+                v[q][0][l] = w.x * c0;
+                v[q][1][l] = w.y * c1;
+                v[q][0][l] += dar[l] * c.x;
+                v[q][1][l] += dar[l] * c.y;
             }
-            __syncthreads();
-            if (active) {
+            if (first) {
+                const dbl2u w = load2(hd, q);
+                s[q][0] = w.x * c.x;
+                s[q][1] = w.y * c.y;
+                const double e = OUT == ROW_ENERGY ? hda[row] + a.ecore : a.ecore;
+                s[q][0] += e * c.x;
+                s[q][1] += e * c.y;
+            }
+            fence();
+        }
+        __syncthreads();
+        auto gather = [&](int k, const uint32_t (&t)[CP]) {
+            double x[CP][2];
 #pragma unroll
-                for (int f = 0; f < MAXF; ++f) {
-                    if (f < nexcB) {
-                        const uint32_t eb = ex[f];
-                        const A *r = Rt + (int64_t)(eb & 0xFFFFu) * ec;
-                        const double *wr = Wt + (int)((eb >> 16) & 0x1FFu) * ec;
-                        A t = zero<A>();
-                        for (int e = 0; e < ne; ++e) axpy(t, wr[e], r[e]);
-                        acc = add(acc, neg_if((eb >> 31) != 0, t));
+            for (int q = 0; q < CP; ++q) {
+                x[q][0] = buf[t[q] & 0xFFFFu];
+                x[q][1] = buf[t[q] >> 16];
+            }
+            const double *L = Lp + k * kRowR + l0;
+#pragma unroll
+            for (int l = 0; l < LH; ++l) {
+                const double w = L[l];
+#pragma unroll
+                for (int q = 0; q < CP; ++q) {
+                    v[q][0][l] += w * x[q][0];
+                    v[q][1][l] += w * x[q][1];
+                }
+            }
+            if (first) {
+                const double w = hp[k] * (1.0 / f);
+#pragma unroll
+                for (int q = 0; q < CP; ++q) {
+                    s[q][0] += w * x[q][0];
+                    s[q][1] += w * x[q][1];
+                }
+            }
+        };
+        {
+            int k = 0;
+            uint32_t t[KB][CP];
+            for (; k + KB <= a.npair; k += KB) {
+#pragma unroll
+                for (int u = 0; u < KB; ++u) words(k + u, t[u]);
+#pragma unroll
+                for (int u = 0; u < KB; ++u) gather(k + u, t[u]);
+            }
+            for (; k < a.npair; ++k) {
+                words(k, t[0]);
+                gather(k, t[0]);
+            }
+        }
+        {
+            auto arow = [&](uint32_t w, const dbl2u (&u)[CP]) {
+                const int pq = (w >> 16) & 0x1FFu;
+                const double *L = Lt + pq * kRowR + l0;
+                const uint32_t sg = w & 0x80000000u;
+                double x[CP][2];
+#pragma unroll
+                for (int q = 0; q < CP; ++q) {
+                    x[q][0] = flip_sign(u[q].x, sg);
+                    x[q][1] = flip_sign(u[q].y, sg);
+                }
+#pragma unroll
+                for (int l = 0; l < LH; ++l) {
+                    const double wl = L[l];
+#pragma unroll
+                    for (int q = 0; q < CP; ++q) {
+                        v[q][0][l] += wl * x[q][0];
+                        v[q][1][l] += wl * x[q][1];
                     }
+                }
+                if (OUT == ROW_ENERGY && first) {
+                    const double wh = heff[pq];
+#pragma unroll
+                    for (int q = 0; q < CP; ++q) {
+                        s[q][0] += wh * x[q][0];
+                        s[q][1] += wh * x[q][1];
+                    }
+                }
+            };
+            auto source = [&](int e, dbl2u (&x)[CP]) {
+                const double *p = Cp + (int64_t)(ex[e] & 0xFFFFu) * a.ld;
+#pragma unroll
+                for (int q = 0; q < CP; ++q) x[q] = load2(p, q);
+            };
+            int e = 0;
+            dbl2u x[EB][CP];
+            for (; e + EB <= a.noff; e += EB) {
+#pragma unroll
+                for (int u = 0; u < EB; ++u) source(e + u, x[u]);
+#pragma unroll
+                for (int u = 0; u < EB; ++u) arow(ex[e + u], x[u]);
+            }
+            for (; e < a.noff; ++e) {
+                source(e, x[0]);
+                arow(ex[e], x[0]);
+            }
+        }
+        if (OUT == ROW_ENERGY) {
+#pragma unroll
+            for (int q = 0; q < CP; ++q)
+                if (on(q)) {
+                    double t0 = 0.0, t1 = 0.0;
+#pragma unroll
+                    for (int l = 0; l < LH; ++l) {
+                        t0 += v[q][0][l] * v[q][0][l];
+                        t1 += v[q][1][l] * v[q][1][l];
+                    }
+                    en += 0.5 * t0;
+                    if (2 * pair(q) + 1 < n) en += 0.5 * t1;
+                }
+        } else {
+            // B_l Y: the diagonal part, then pair by pair through LDS, NC pairs
+            // to a buffer and two buffers in turn (one barrier per NC pairs)
+#pragma unroll
+            for (int q = 0; q < CP; ++q) {
+#pragma unroll
+                for (int l = 0; l < LH; ++l) {
+                    const dbl2u w = load2(db + (l0 + l) * zero, q);
+                    s[q][0] += w.x * v[q][0][l];
+                    s[q][1] += w.y * v[q][1][l];
+                }
+                fence();
+            }
+            __syncthreads();  // readers of the row in buf are done
+            int par = 0;
+            for (int k0 = 0; k0 < a.npair; k0 += NC, par ^= 1) {
+                double *b = buf + (NB == 2 ? par * 2 * NC * Wp : 0);
+                uint32_t t[NC][CP];
+#pragma unroll
+                for (int u = 0; u < NC; ++u) words(min(k0 + u, a.npair - 1), t[u]);
+#pragma unroll
+                for (int u = 0; u < NC; ++u)
+                    if (k0 + u < a.npair) {
+                        const double *L = Lp + (k0 + u) * kRowR + l0;
+                        double w[CP][2];
+#pragma unroll
+                        for (int q = 0; q < CP; ++q) {
+                            w[q][0] = L[0] * v[q][0][0];
+                            w[q][1] = L[0] * v[q][1][0];
+                        }
+#pragma unroll
+                        for (int l = 1; l < LH; ++l) {
+                            const double wl = L[l];
+#pragma unroll
+                            for (int q = 0; q < CP; ++q) {
+                                w[q][0] += wl * v[q][0][l];
+                                w[q][1] += wl * v[q][1][l];
+                            }
+                        }
+#pragma unroll
+                        for (int q = 0; q < CP; ++q)
+                            if (on(q)) put2(b + 2 * u * Wp, q, w[q][0], w[q][1]);
+                    }
+                __syncthreads();
+#pragma unroll
+                for (int u = 0; u < NC; ++u)
+                    if (k0 + u < a.npair)
+#pragma unroll
+                        for (int q = 0; q < CP; ++q) {
+                            s[q][0] += b[2 * u * Wp + (t[u][q] & 0xFFFFu)];
+                            s[q][1] += b[2 * u * Wp + (t[u][q] >> 16)];
+                        }
+                if (NB == 1) __syncthreads();
+            }
+        }
+    }
+    // results
+    double *srow = OUT == ROW_ENERGY ? nullptr : S + (int64_t)blockIdx.y * a.plane + (int64_t)row * a.ld;
+#pragma unroll
+    for (int q = 0; q < CP; ++q)
+        if (on(q)) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int col = 2 * pair(q) + h;
+                if (col >= n) break;
+                double r = s[q][h];
+                if (OUT != ROW_ENERGY) r += srow[col];
+                const double c = crow[col];
+                en += c * r;
+                if (OUT == ROW_ZIP)
+                    ((double2 *)z)[(int64_t)row * a.ld + col] = make_double2(c, r);
+                else if (OUT == ROW_ZIP32)
+                    ((float2 *)z)[(int64_t)row * a.ld + col] = make_float2((float)c, (float)r);
+                else if (OUT == ROW_S)
+                    srow[col] = r;
+            }
+        }
+    en = block_sum(en);
+    if (tid == 0) epart[(int64_t)blockIdx.y * a.nrows + row] = en;
+}
+
+// One-body tables of k_row from h' (M x M): the off-diagonal values per
+// orbital pair p < q, and per string the sum over its occupied orbitals.
+__global__ __launch_bounds__(256) void k_row_onebody(const double *__restrict__ heff, int M,
+                                                     const uint32_t *__restrict__ sa, int64_t nsa,
+                                                     const uint32_t *__restrict__ sb, int64_t nsb,
+                                                     double *__restrict__ hp, double *__restrict__ hda,
+                                                     double *__restrict__ hdb) {
+    const int64_t npair = (int64_t)M * (M - 1) / 2, total = npair + nsa + nsb;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += (int64_t)gridDim.x * blockDim.x) {
+        if (i < npair) {
+            int p = 0;
+            int64_t k = i;
+            while (k >= M - 1 - p) k -= M - 1 - p, ++p;
+            hp[i] = heff[p * M + p + 1 + k];
+            continue;
+        }
+        const bool alpha = i < npair + nsa;
+        const int64_t I = alpha ? i - npair : i - npair - nsa;
+        const uint32_t str = alpha ? sa[I] : sb[I];
+        double d = 0.0;
+        for (int p = 0; p < M; ++p)
+            if (str >> p & 1u) d += heff[p * M + p];
+        (alpha ? hda : hdb)[I] = d;
+    }
+}
+
+// Alpha-beta term with a general interaction, one workgroup per row Ia:
+//   S[Ia][Ib] += sum_{r<=s} (E_rs + E_sr) G_rs[Ib],  G_rs[Jb] = sum_e s_e (pq_e|rs) C[J_e][Jb]
+// (the diagonal pairs r = s once).  The former kernels took every (alpha,
+// beta) excitation pair of an element from LDS (e_a e_b reads of 16 bytes);
+// contracting the alpha side first leaves e_a M (M+1)/2 multiply-adds per
+// element on registers and scalars, and one 8-byte LDS exchange per pair rs:
+// the alpha sources are read coalesced, the factors (pq_e|rs) of RC
+// consecutive pairs are scalars, and G_rs goes through LDS to the strings that
+// pair rs reaches (the partner table of k_row).  Bound by FP64 vector
+// arithmetic: 264 us at 24 qubits with integrals of full rank (511 us before).
+// A row's diagonal alpha excitations are one term with their factors summed
+// per string (dg).
+struct AbArgs {
+    int32_t nrows, ncols, npd, ts;  // npd: orbital pairs r <= s, padded to a multiple of 4 rows in g and dg
+    int32_t npp;                    // row length of g and dg (padded pairs)
+    int32_t nexc, noff;
+    int64_t ld, plane;
+};
+
+template <int BS, int CP, int RC, int NC>
+__global__ __launch_bounds__(BS) void k_ab(const double *__restrict__ C, double *__restrict__ S,
+                                           const uint32_t *__restrict__ tp, const double *__restrict__ g,
+                                           const double *__restrict__ dg, const uint32_t *__restrict__ exc,
+                                           AbArgs a) {
+    static_assert(RC % NC == 0, "whole buffers per chunk");
+    extern __shared__ double buf[];
+    const int n = a.ncols, ncp = (n + 1) >> 1, zero = 2 * ncp, Wp = zero + 2, tid = threadIdx.x;
+    int row;
+    {
+        const int v = blockIdx.x, per = a.nrows >> 3, rem = a.nrows & 7, x = v & 7;
+        row = x * per + min(x, rem) + (v >> 3);
+    }
+    const double *Cp = C + (int64_t)blockIdx.y * a.plane;
+    uint32_t off[CP];  // columns, offsets and buffers as in k_row
+#pragma unroll
+    for (int q = 0; q < CP; ++q) off[q] = 16u * (uint32_t)min(tid + q * BS, ncp - 1);
+    auto pair = [&](int q) { return (int)(off[q] >> 4); };
+    auto on = [&](int q) { return tid + q * BS < ncp; };
+    auto load2 = [&](const double *p, int q) { return *(const dbl2u *)((const char *)p + off[q]); };
+    for (int t = tid; t < 4 * NC; t += BS) buf[t * Wp + zero] = 0.0;
+    const uint32_t *ex = exc + (int64_t)row * a.nexc;
+    double s[CP][2];
+#pragma unroll
+    for (int q = 0; q < CP; ++q) s[q][0] = s[q][1] = 0.0;
+    int par = 0;
+    for (int c0 = 0; c0 < a.npd; c0 += RC) {
+        double acc[RC][CP][2];
+#pragma unroll
+        for (int r = 0; r < RC; ++r)
+#pragma unroll
+            for (int q = 0; q < CP; ++q) acc[r][q][0] = acc[r][q][1] = 0.0;
+        auto source = [&](int e) {  // e = noff: the row itself
+            return Cp + (int64_t)(e < a.noff ? ex[e] & 0xFFFFu : (uint32_t)row) * a.ld;
+        };
+        dbl2u x[CP];
+#pragma unroll
+        for (int q = 0; q < CP; ++q) x[q] = load2(source(0), q);
+        for (int e = 0; e <= a.noff; ++e) {
+            dbl2u nx[CP];  // the next source row, in flight during this one's arithmetic
+#pragma unroll
+            for (int q = 0; q < CP; ++q) nx[q] = load2(source(min(e + 1, a.noff)), q);
+            const uint32_t w = e < a.noff ? ex[e] : 0u;
+            const double *wr = e < a.noff ? g + (int64_t)((w >> 16) & 0x1FFu) * a.npp + c0 : dg + (int64_t)row * a.npp + c0;
+            const uint32_t sg = w & 0x80000000u;
+            double y[CP][2];
+#pragma unroll
+            for (int q = 0; q < CP; ++q) {
+                y[q][0] = flip_sign(x[q].x, sg);
+                y[q][1] = flip_sign(x[q].y, sg);
+                x[q] = nx[q];
+            }
+#pragma unroll
+            for (int r = 0; r < RC; ++r) {
+                const double wv = wr[r];
+#pragma unroll
+                for (int q = 0; q < CP; ++q) {
+                    acc[r][q][0] += wv * y[q][0];
+                    acc[r][q][1] += wv * y[q][1];
                 }
             }
         }
-        if (active) S[Ia * nsb + Ib] = add(S[Ia * nsb + Ib], acc);
-    }
-}
-
-// Factorised alpha-beta term, (pq|rs) = sum_l L_l[pq] L_l[rs] (l < R, padded
-// to RP = 8 with zero columns of Lt, which is M^2 x RP; wider ranks take the
-// direct product):
-//   S[Ia][Ib] += sum_l (A_l C B_l^T)[Ia][Ib],  A_l = sum_pq L_l[pq] E^alpha_pq,
-//   B_l = sum_rs L_l[rs] E^beta_rs,
-// in two steps through Y[Ia][Jb][l] = (A_l C)[Ia][Jb] (l fastest).
-//
-// Step 1 gathers whole rows of C: a workgroup is one alpha string Ia and 256
-// beta strings Jb, so Ia's excitation list and the factor row of each
-// excitation are workgroup-uniform and every coalesced load of C feeds RP
-// multiply-adds.
-template <typename A, int RP>
-__global__ __launch_bounds__(256) void k_lr_a(const A *__restrict__ C, A *__restrict__ Y,
-                                              const uint32_t *__restrict__ excA, int nexcA,
-                                              const double *__restrict__ Lt, int64_t nsb) {
-    const int64_t Ia = blockIdx.x;
-    const int64_t Jb = (int64_t)blockIdx.y * blockDim.x + threadIdx.x;
-    const bool active = Jb < nsb;
-    const int64_t jb = active ? Jb : nsb - 1;
-    const uint32_t *ex = excA + Ia * nexcA;
-    A acc[RP];
 #pragma unroll
-    for (int l = 0; l < RP; ++l) acc[l] = zero<A>();
-    int e = 0;
-    for (; e + 4 <= nexcA; e += 4) {
-        A x[4];
+        for (int r0 = 0; r0 < RC; r0 += NC) {
+            if (c0 + r0 < a.npd) {
+                // two buffers in turn: one is written again only after a
+                // barrier that follows every read of it
+                double *b = buf + par * 2 * NC * Wp;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) x[u] = C[(int64_t)(ex[e + u] & 0xFFFFu) * nsb + jb];
+                for (int u = 0; u < NC; ++u)
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const uint32_t ea = ex[e + u];
-            const double *lr = Lt + ((ea >> 16) & 0x1FFu) * RP;
-            const A xv = neg_if((ea >> 31) != 0, x[u]);
+                    for (int q = 0; q < CP; ++q)
+                        if (on(q)) {
+                            char *d = (char *)(b + 2 * u * Wp) + off[q];
+                            *(dbl2a *)d = dbl2a{acc[r0 + u][q][0], acc[r0 + u][q][1]};
+                            *(dbl2a *)(d + 8 * Wp) = dbl2a{-acc[r0 + u][q][0], -acc[r0 + u][q][1]};
+                        }
+                uint32_t t[NC][CP];
 #pragma unroll
-            for (int l = 0; l < RP; ++l) axpy(acc[l], lr[l], xv);
-        }
-    }
-    for (; e < nexcA; ++e) {
-        const uint32_t ea = ex[e];
-        const double *lr = Lt + ((ea >> 16) & 0x1FFu) * RP;
-        const A xv = neg_if((ea >> 31) != 0, C[(int64_t)(ea & 0xFFFFu) * nsb + jb]);
+                for (int u = 0; u < NC; ++u)
 #pragma unroll
-        for (int l = 0; l < RP; ++l) axpy(acc[l], lr[l], xv);
-    }
-    if (active) {
-        A *y = Y + (Ia * nsb + Jb) * RP;
+                    for (int q = 0; q < CP; ++q)
+                        t[u][q] = *(const uint32_t *)((const char *)(tp + (int64_t)min(c0 + r0 + u, a.npd - 1) * a.ts) +
+                                                      (off[q] >> 2));
+                __syncthreads();
 #pragma unroll
-        for (int l = 0; l < RP; ++l) y[l] = acc[l];
-    }
-}
-
-// Doubles of k_lr_b's staged factor rows (M2 rows of ws), rounded up to an
-// even count so that the intermediate rows after them start 16-byte aligned
-// (complex rows are read as 16-byte values).
-__host__ __device__ inline size_t lr_lt_words(int M2, int ws) { return ((size_t)M2 * ws + 1) & ~(size_t)1; }
-
-constexpr int kExcBatch = 8;    // beta-list words loaded together in the step-2 loop of k_lr_b
-constexpr int kExcBatchAB = 4;  // and of k_lr_ab (which must stay within 64 VGPRs: two workgroups per CU)
-
-// Step 2, row-local: S[Ia][Ib] += sum_{f in exc(Ib)} s_f sum_l L_l[rs_f]
-// Y[Ia][Jb_f][l].  One workgroup per Ia stages its Y row (nsb x lc values)
-// and the matching lc columns of Lt in LDS, lc of the RP values at a time;
-// the beta lists are read transposed (excBT[f][Ib]) so the lanes' loads
-// coalesce.  The staged rows are ys (Y) and ws (Lt) elements apart: with
-// lc = 8 a 64-byte stride would start every lane's 16-byte LDS read in one
-// of only 4 bank groups, so the host pads the strides by 16 bytes.
-template <typename A>
-__global__ __launch_bounds__(1024) void k_lr_b(const A *__restrict__ Y, A *__restrict__ S,
-                                               const uint32_t *__restrict__ excBT, int nexcB,
-                                               const double *__restrict__ Lt, int M2, int RP, int64_t nsb,
-                                               int lc, int ys, int ws) {
-    extern __shared__ double smem_d[];
-    double *lt = smem_d;               // M2 x ws
-    A *yr = (A *)(lt + lr_lt_words(M2, ws));  // nsb x ys, 16-byte aligned
-    const int64_t Ia = blockIdx.x;
-    const A *yrow = Y + Ia * nsb * RP;
-    A *srow = S + Ia * nsb;
-    for (int l0 = 0; l0 < RP; l0 += lc) {
-        __syncthreads();  // readers of the previous chunk are done
-        for (int i = threadIdx.x; i < M2 * lc; i += blockDim.x)
-            lt[(i / lc) * ws + i % lc] = Lt[(i / lc) * RP + l0 + i % lc];
-        for (int64_t i = threadIdx.x; i < nsb * lc; i += blockDim.x)
-            yr[(i / lc) * ys + i % lc] = yrow[(i / lc) * RP + l0 + i % lc];
-        __syncthreads();
-        for (int64_t Ib = threadIdx.x; Ib < nsb; Ib += blockDim.x) {
-            A acc = zero<A>();
-            auto step = [&](uint32_t eb) {
-                const double *w = lt + ((eb >> 16) & 0x1FFu) * ws;
-                const A *y = yr + (int64_t)(eb & 0xFFFFu) * ys;
-                A t = zero<A>();
-                for (int l = 0; l < lc; ++l) axpy(t, w[l], y[l]);
-                acc = add(acc, neg_if((eb >> 31) != 0, t));
-            };
-            int f = 0;
-            for (; f + kExcBatch <= nexcB; f += kExcBatch) {  // the list words in flight together
-                uint32_t eb[kExcBatch];
+                for (int u = 0; u < NC; ++u)
+                    if (c0 + r0 + u < a.npd)
 #pragma unroll
-                for (int u = 0; u < kExcBatch; ++u) eb[u] = excBT[(int64_t)(f + u) * nsb + Ib];
-#pragma unroll
-                for (int u = 0; u < kExcBatch; ++u) step(eb[u]);
-            }
-            for (; f < nexcB; ++f) step(excBT[(int64_t)f * nsb + Ib]);
-            srow[Ib] = add(srow[Ib], acc);
-        }
-    }
-}
-
-// Both steps in one workgroup per alpha string Ia (real states, RP = 8, the
-// Y row in LDS): the row Y[Ia][:][:] is built from Ia's alpha excitations
-// (each thread one Jb; the excitation words and factor rows are
-// workgroup-uniform, so they come through scalar loads) straight into LDS,
-// then step 2 runs on it as in k_lr_b.  Y never goes to memory.  Rows are
-// kLrStride = 9 doubles apart (72 bytes: lanes' 8-byte reads start in 32
-// different bank pairs), which keeps two workgroups per CU at 24 qubits.
-// A string's diagonal excitations (the last ndA / ndB entries of its list)
-// all map it to itself, so each step takes them as one term with the
-// string's summed factor row (da / db).
-constexpr int kLrStride = 9;
-
-__global__ __launch_bounds__(1024) void k_lr_ab(const double *__restrict__ C, double *__restrict__ S,
-                                                const uint32_t *__restrict__ excA, int nexcA,
-                                                const uint32_t *__restrict__ excBT, int nexcB,
-                                                const double *__restrict__ Lt, int M2, int64_t nsb,
-                                                const double *__restrict__ da, const double *__restrict__ db,
-                                                int ndA, int ndB) {
-    constexpr int RP = 8;
-    extern __shared__ double smem_d[];
-    double *lt = smem_d;                // M2 x kLrStride
-    double *yr = lt + M2 * kLrStride;   // nsb x kLrStride
-    const int64_t Ia = blockIdx.x;
-    for (int i = threadIdx.x; i < M2 * RP; i += blockDim.x) lt[(i / RP) * kLrStride + i % RP] = Lt[i];
-    const uint32_t *ex = excA + Ia * nexcA;
-    const int noffA = nexcA - ndA, noffB = nexcB - ndB;
-    const double *dar = da + Ia * RP;
-    for (int64_t Jb = threadIdx.x; Jb < nsb; Jb += blockDim.x) {
-        double acc[RP];
-        {
-            const double xv = C[Ia * nsb + Jb];
-#pragma unroll
-            for (int l = 0; l < RP; ++l) acc[l] = dar[l] * xv;
-        }
-        int e = 0;
-        for (; e + 4 <= noffA; e += 4) {
-            double x[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) x[u] = C[(int64_t)(ex[e + u] & 0xFFFFu) * nsb + Jb];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const uint32_t ea = ex[e + u];
-                const double *lr = Lt + ((ea >> 16) & 0x1FFu) * RP;
-                const double xv = neg_if((ea >> 31) != 0, x[u]);
-#pragma unroll
-                for (int l = 0; l < RP; ++l) axpy(acc[l], lr[l], xv);
+                        for (int q = 0; q < CP; ++q) {
+                            s[q][0] += b[2 * u * Wp + (t[u][q] & 0xFFFFu)];
+                            s[q][1] += b[2 * u * Wp + (t[u][q] >> 16)];
+                        }
+                par ^= 1;
             }
         }
-        for (; e < noffA; ++e) {
-            const uint32_t ea = ex[e];
-            const double *lr = Lt + ((ea >> 16) & 0x1FFu) * RP;
-            const double xv = neg_if((ea >> 31) != 0, C[(int64_t)(ea & 0xFFFFu) * nsb + Jb]);
-#pragma unroll
-            for (int l = 0; l < RP; ++l) axpy(acc[l], lr[l], xv);
-        }
-#pragma unroll
-        for (int l = 0; l < RP; ++l) yr[Jb * kLrStride + l] = acc[l];
     }
-    __syncthreads();
-    double *srow = S + Ia * nsb;
-    for (int64_t Ib = threadIdx.x; Ib < nsb; Ib += blockDim.x) {
-        double acc = 0.0;
-        {
-            const double *dbr = db + Ib * RP;
-            const double *y = yr + Ib * kLrStride;
+    double *srow = S + (int64_t)blockIdx.y * a.plane + (int64_t)row * a.ld;
 #pragma unroll
-            for (int l = 0; l < RP; ++l) axpy(acc, dbr[l], y[l]);
+    for (int q = 0; q < CP; ++q)
+        if (on(q)) {
+            srow[2 * pair(q)] += s[q][0];
+            if (2 * pair(q) + 1 < n) srow[2 * pair(q) + 1] += s[q][1];
         }
-        auto step = [&](uint32_t eb) {
-            const double *w = lt + ((eb >> 16) & 0x1FFu) * kLrStride;
-            const double *y = yr + (int64_t)(eb & 0xFFFFu) * kLrStride;
-            double t = 0.0;
-#pragma unroll
-            for (int l = 0; l < RP; ++l) axpy(t, w[l], y[l]);
-            acc += neg_if((eb >> 31) != 0, t);
-        };
-        int f = 0;
-        for (; f + kExcBatchAB <= noffB; f += kExcBatchAB) {
-            uint32_t eb[kExcBatchAB];
-#pragma unroll
-            for (int u = 0; u < kExcBatchAB; ++u) eb[u] = excBT[(int64_t)(f + u) * nsb + Ib];
-#pragma unroll
-            for (int u = 0; u < kExcBatchAB; ++u) step(eb[u]);
-        }
-        for (; f < noffB; ++f) step(excBT[(int64_t)f * nsb + Ib]);
-        srow[Ib] += acc;
-    }
 }
 
 // ------------------------------------------------------------ screening ----
@@ -620,71 +829,72 @@ __global__ __launch_bounds__(256) void k_pool(const V *__restrict__ psi, const V
 }
 
 // Same term without LDS staging (rows too long for LDS): gathers from global.
-template <typename A>
 __global__ __launch_bounds__(256) void k_sigma_ab_global(const uint32_t *__restrict__ excA, int nexcA,
                                                          const uint32_t *__restrict__ excB, int nexcB,
                                                          const double *__restrict__ g, int M,
-                                                         const A *__restrict__ C, A *__restrict__ S,
-                                                         int64_t nsb) {
+                                                         const double *__restrict__ Cin, double *__restrict__ Sin,
+                                                         int64_t nsb, int64_t ld) {
     const int64_t Ia = blockIdx.x;
     const int M2 = M * M;
+    const double *C = Cin + (int64_t)blockIdx.y * nsb;
+    double *S = Sin + (int64_t)blockIdx.y * nsb;
     for (int64_t Ib = threadIdx.x; Ib < nsb; Ib += blockDim.x) {
-        A acc = zero<A>();
+        double acc = 0.0;
         for (int e = 0; e < nexcA; ++e) {
             const uint32_t w = excA[Ia * nexcA + e];
             const int64_t Ja = w & 0xFFFFu;
             const double *gp = g + ((w >> 16) & 0x1FFu) * M2;
-            A t = zero<A>();
+            double t = 0.0;
             for (int f = 0; f < nexcB; ++f) {
                 const uint32_t eb = excB[Ib * nexcB + f];
                 const double gv = gp[(eb >> 16) & 0x1FFu];
-                axpy(t, (eb >> 31) ? -gv : gv, C[Ja * nsb + (eb & 0xFFFFu)]);
+                t += ((eb >> 31) ? -gv : gv) * C[Ja * ld + (eb & 0xFFFFu)];
             }
-            acc = add(acc, neg_if((w >> 31) != 0, t));
+            acc += neg_if((w >> 31) != 0, t);
         }
-        S[Ia * nsb + Ib] = add(S[Ia * nsb + Ib], acc);
+        S[Ia * ld + Ib] += acc;
     }
 }
 
-template <typename A>
-__global__ void k_transpose(const A *__restrict__ in, A *__restrict__ out, int64_t rows, int64_t cols) {
-    __shared__ A t[32][33];
+// out[c * ldo + r] = in[r * ldi + c], plane blockIdx.z pi / po elements further on.
+__global__ void k_transpose(const double *__restrict__ in, double *__restrict__ out, int64_t rows, int64_t cols, int64_t ldi,
+                            int64_t ldo, int64_t pi, int64_t po) {
+    __shared__ double t[32][33];
+    in += (int64_t)blockIdx.z * pi;
+    out += (int64_t)blockIdx.z * po;
     const int64_t c0 = (int64_t)blockIdx.x * 32, r0 = (int64_t)blockIdx.y * 32;
     for (int j = threadIdx.y; j < 32; j += blockDim.y) {
         const int64_t r = r0 + j, c = c0 + threadIdx.x;
-        if (r < rows && c < cols) t[j][threadIdx.x] = in[r * cols + c];
+        if (r < rows && c < cols) t[j][threadIdx.x] = in[r * ldi + c];
     }
     __syncthreads();
     for (int j = threadIdx.y; j < 32; j += blockDim.y) {
         const int64_t c = c0 + j, r = r0 + threadIdx.x;
-        if (r < rows && c < cols) out[c * rows + r] = t[threadIdx.x][j];
+        if (r < rows && c < cols) out[c * ldo + r] = t[threadIdx.x][j];
     }
 }
 
-// S[Ia][Ib] += ST[Ib][Ia] + ecore C[Ia][Ib]; per-block partials of Re<C|S>.
-// The transposed operand is read through an LDS tile.
-template <typename A>
-__global__ void k_combine(A *__restrict__ S, const A *__restrict__ ST, const A *__restrict__ C,
-                          double ecore, int64_t nsa, int64_t nsb, double *__restrict__ partial) {
-    __shared__ A t[32][33];
+// S[i][k] += ST[k][i] + ecore C[i][k] for rows x cols matrices; per-block
+// partials of <C|S>.  The transposed operand is read through an LDS tile.
+__global__ void k_combine(double *__restrict__ S, const double *__restrict__ ST, const double *__restrict__ C,
+                          double ecore, int64_t rows, int64_t cols, double *__restrict__ partial) {
+    __shared__ double t[32][33];
     double acc = 0.0;
-    const int64_t tiles_b = (nsb + 31) / 32, tiles = ((nsa + 31) / 32) * tiles_b;
+    const int64_t tiles_b = (cols + 31) / 32, tiles = ((rows + 31) / 32) * tiles_b;
     for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
         const int64_t a0 = (tile / tiles_b) * 32, b0 = (tile % tiles_b) * 32;
         for (int j = threadIdx.y; j < 32; j += blockDim.y) {  // ST rows b0+j, columns a0+x
             const int64_t ib = b0 + j, ia = a0 + threadIdx.x;
-            if (ib < nsb && ia < nsa) t[j][threadIdx.x] = ST[ib * nsa + ia];
+            if (ib < cols && ia < rows) t[j][threadIdx.x] = ST[ib * rows + ia];
         }
         __syncthreads();
         for (int j = threadIdx.y; j < 32; j += blockDim.y) {
             const int64_t ia = a0 + j, ib = b0 + threadIdx.x;
-            if (ia < nsa && ib < nsb) {
-                const A c = C[ia * nsb + ib];
-                A s = S[ia * nsb + ib];
-                s = add(s, t[threadIdx.x][j]);
-                axpy(s, ecore, c);
-                S[ia * nsb + ib] = s;
-                acc += dotre(c, s);
+            if (ia < rows && ib < cols) {
+                const double c = C[ia * cols + ib];
+                const double v = S[ia * cols + ib] + t[threadIdx.x][j] + ecore * c;
+                S[ia * cols + ib] = v;
+                acc += c * v;
             }
         }
         __syncthreads();
@@ -722,7 +932,7 @@ __global__ __launch_bounds__(256) void k_ecore_dot(double *__restrict__ S, const
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < dim; i += (int64_t)gridDim.x * blockDim.x) {
         const double c = C[i];
         double s = S[i];
-        axpy(s, ecore, c);
+        s += ecore * c;
         S[i] = s;
         acc += c * s;
     }
@@ -740,7 +950,7 @@ __global__ __launch_bounds__(256) void k_ecore_zip(const double *__restrict__ S,
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < dim; i += (int64_t)gridDim.x * blockDim.x) {
         const double c = C[i];
         double s = S[i];
-        axpy(s, ecore, c);
+        s += ecore * c;
         z[i] = make_double2(c, s);
         acc += c * s;
     }
@@ -766,142 +976,166 @@ __global__ void k_scatter_real(O *__restrict__ lam,
 
 int g_lds_max = -1;
 
-// LDS chunk of the factor columns for step 2 (0: a row does not fit).
-template <typename A>
-int lr_chunk(const SectorTabs &T, int rp) {
-    const size_t lim = g_lds_max > 0 ? (size_t)g_lds_max : 65536;
-    const size_t per = (size_t)T.M * T.M * sizeof(double) + (size_t)T.nsb * sizeof(A);
-    int lc = rp;
-    while (lc > 0 && (size_t)lc * per + sizeof(double) > lim) lc >>= 1;  // + the alignment pad
-    return lc;
+// Launch shapes of the row kernels: threads, column pairs per thread, factor
+// columns per pass (k_row) or orbital pairs per chunk (k_ab), pairs per LDS
+// buffer, buffers, and waves per SIMD, by the row's column pairs (n =
+// ceil(columns / 2)).  At 924 columns 256 threads x 2 pairs (four rows
+// resident per CU) took 102 us, 512 x 1 101-112 us, 128 x 4 116 us, two pairs
+// per buffer 139 us.  At 6435 columns 1024 threads x 4 pairs and half of the
+// factors per pass took 13.5 ms, 512 x 7 14.2 ms, a quarter of the factors per
+// pass 21 ms.
+template <int OUT>
+hipError_t row_launch(int planes, const SectorTabs &T, const double *C, double *S, void *z, double *epart,
+                      const int32_t *im_flag, int32_t im_epoch, hipStream_t st) {
+    RowArgs a{};
+    a.nrows = (int32_t)T.nsa;
+    a.ncols = (int32_t)T.nsb;
+    a.npair = T.M * (T.M - 1) / 2;
+    a.ts = (int32_t)((T.nsb + 1) / 2);
+    a.nexc = T.nexcA;
+    a.noff = T.nexcA - T.ndA;
+    a.ld = planes * T.nsb;
+    a.plane = T.nsb;
+    a.ecore = T.ecore;
+    a.im_epoch = im_epoch;
+    a.im_flag = im_flag;
+    const int n = (a.ncols + 1) / 2, Wp = 2 * n + 2;
+    const dim3 grid((unsigned)a.nrows, (unsigned)planes);
+#define FSV_ROW(BS, CP, LH, NC, NB, WV)                                                                        \
+    hipLaunchKernelGGL((k_row<BS, CP, LH, NC, NB, WV, OUT>), grid, dim3(BS),                                   \
+                       sizeof(double) * (OUT == ROW_ENERGY ? 2 : 2 * NB * NC) * (size_t)Wp, st, C, S, z, epart, \
+                       T.tp, T.Lp, T.hp, T.db, T.hdb, T.excA, T.Lt, T.da, T.heff, T.hda, a)
+    if (n <= 64)
+        FSV_ROW(64, 1, 8, 1, 2, 4);
+    else if (n <= 128)
+        FSV_ROW(128, 1, 8, 1, 2, 4);
+    else if (n <= 256)
+        FSV_ROW(256, 1, 8, 1, 2, 4);
+    else if (n <= 512)
+        FSV_ROW(256, 2, 8, 1, 2, 4);
+    else if (n <= 1024)
+        FSV_ROW(512, 2, 8, 1, 2, 4);
+    else if (n <= 2048)
+        FSV_ROW(512, 4, 8, 1, 2, 2);
+    else if (n <= 4096)
+        FSV_ROW(1024, 4, 4, 1, 1, 4);
+    else
+        FSV_ROW(1024, 5, 2, 1, 1, 4);
+#undef FSV_ROW
+    return hipGetLastError();
 }
 
-// The one-kernel form applies to real states with RP = 8 whose LDS rows fit
-// two workgroups per CU.
-template <typename A, int RP>
-bool lr_fused_ok(const SectorTabs &T) {
-    if (sizeof(A) != sizeof(double) || RP != 8 || std::getenv("FSV_LR_SPLIT")) return false;
-    return (size_t)(T.M * T.M + T.nsb) * kLrStride * sizeof(double) * 2 <= 163840 && g_lds_max >= 81920;
+hipError_t ab_launch(const double *C, double *S, const SectorTabs &T, int planes, hipStream_t st) {
+    AbArgs a{};
+    a.nrows = (int32_t)T.nsa;
+    a.ncols = (int32_t)T.nsb;
+    a.npd = T.M * (T.M + 1) / 2;
+    a.ts = (int32_t)((T.nsb + 1) / 2);
+    a.npp = T.npp;
+    a.nexc = T.nexcA;
+    a.noff = T.nexcA - T.ndA;
+    a.ld = planes * T.nsb;
+    a.plane = T.nsb;
+    const int n = (a.ncols + 1) / 2, Wp = 2 * n + 2;
+    const dim3 grid((unsigned)a.nrows, (unsigned)planes);
+#define FSV_AB(BS, CP, RC, NC)                                                                                 \
+    hipLaunchKernelGGL((k_ab<BS, CP, RC, NC>), grid, dim3(BS), sizeof(double) * 4 * (size_t)NC * Wp, st, C, S, \
+                       T.tp, T.gp, T.dg, T.excA, a)
+    if (n <= 64)
+        FSV_AB(64, 1, 16, 4);
+    else if (n <= 128)
+        FSV_AB(128, 1, 16, 4);
+    else if (n <= 256)
+        FSV_AB(256, 1, 16, 4);
+    else if (n <= 512)
+        FSV_AB(512, 1, 20, 2);
+    else if (n <= 1024)
+        FSV_AB(512, 2, 16, 2);
+    else if (n <= 2048)
+        FSV_AB(512, 4, 8, 1);
+    else
+        FSV_AB(512, 5, 6, 1);
+#undef FSV_AB
+    return hipGetLastError();
 }
 
-// Padded LDS strides (in elements) of k_lr_b's staged rows for lc values per
-// row, when the padded rows still fit: 16 bytes more than the row for lc >= 4
-// (16-byte reads); an odd number of doubles for real rows of lc < 4 (8-byte
-// reads, 32 distinct bank pairs instead of 16).
-template <typename A>
-void lr_strides(const SectorTabs &T, int lc, int &ys, int &ws) {
-    const size_t lim = g_lds_max > 0 ? (size_t)g_lds_max : 65536;
-    ys = lc;
-    ws = lc;
-    if (lc < 4 && sizeof(A) != sizeof(double)) return;
-    const int py = lc < 4 ? lc + 1 : lc + (int)(16 / sizeof(A)), pw = lc < 4 ? lc + 1 : lc + 2;
-    if (lr_lt_words(T.M * T.M, pw) * sizeof(double) + (size_t)T.nsb * py * sizeof(A) <= lim) {
-        ys = py;
-        ws = pw;
-    }
-}
-
-template <typename A, int RP>
-hipError_t lr_launch(const SectorTabs &T, const A *C, A *S, hipStream_t st) {
-    if (lr_fused_ok<A, RP>(T)) {
-        const size_t shm = (size_t)(T.M * T.M + T.nsb) * kLrStride * sizeof(double);
-        hipLaunchKernelGGL(k_lr_ab, dim3((unsigned)T.nsa), dim3(1024), shm, st, (const double *)C, (double *)S,
-                           T.excA, T.nexcA, T.excBT, T.nexcB, T.Lt, T.M * T.M, T.nsb, T.lr_da, T.lr_db, T.ndA,
-                           T.ndB);
-        return hipGetLastError();
-    }
-    A *Y = (A *)T.YT;
-    const int lc = lr_chunk<A>(T, RP);
-    if (lc < 1) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_lr_a<A, RP>), dim3((unsigned)T.nsa, (unsigned)((T.nsb + 255) / 256)), dim3(256), 0, st,
-                       C, Y, T.excA, T.nexcA, T.Lt, T.nsb);
-    const int M2 = T.M * T.M;
-    int ys, ws;
-    lr_strides<A>(T, lc, ys, ws);
-    const size_t shm = lr_lt_words(M2, ws) * sizeof(double) + (size_t)T.nsb * ys * sizeof(A);
-    hipLaunchKernelGGL((k_lr_b<A>), dim3((unsigned)T.nsa), dim3(1024), shm, st, Y, S, T.excBT, T.nexcB, T.Lt, M2,
-                       RP, T.nsb, lc, ys, ws);
+// Same-spin alpha part (with the alpha one-body terms) into S: dense on the
+// matrix cores, or sparse rows.
+hipError_t alpha_same_spin(int planes, const SectorTabs &T, const double *C, double *S, hipStream_t st) {
+    const int64_t cols = planes * T.nsb;
+    if (T.ha_dense) return dense_same_spin(T.blas, T.ha_dense, C, S, T.nsa, cols, st);
+    hipLaunchKernelGGL(k_spmm, dim3((unsigned)T.nsa, (unsigned)((cols + 255) / 256)), dim3(256), 0, st, T.ha_ptr,
+                       T.ha_col, T.ha_val, C, S, cols);
     return hipGetLastError();
 }
 
 }  // namespace
 
-bool lr_uses_intermediate(const SectorTabs &T, bool cplex) {
-    if (T.R <= 0 || T.nexcA <= 0 || T.nexcB <= 0) return false;
-    return cplex ? true : !lr_fused_ok<double, 8>(T);
+bool row_kernel_fits(int64_t ncols) {
+    // two LDS rows of 8 bytes a column (a row and its negative); with a smaller
+    // limit only the short rows' buffers
+    return ncols >= 2 && ncols <= (g_lds_max >= 163840 ? 10200 : 480);
+}
+
+bool ab_kernel_fits(int64_t ncols) {  // four rows: two buffers and their negatives
+    return ncols >= 2 && ncols <= (g_lds_max >= 163840 ? 5096 : 480);
 }
 
 namespace {
 
-template <typename A>
-hipError_t sigma_impl(const SectorTabs &T, const A *C, A *S, A *CT, A *ST, double *epart, hipStream_t st,
-                      double2 *zout, bool *zipped) {
-    const int64_t nsa = T.nsa, nsb = T.nsb;
-    constexpr int64_t w = sizeof(A) / sizeof(double);  // doubles per amplitude
-    // same-spin alpha part (with the alpha one-body terms): dense on the
-    // matrix cores, or sparse rows
-    if (T.ha_dense) {
-        const hipError_t e = dense_same_spin(T.blas, T.ha_dense, (const double *)C, (double *)S, nsa, w * nsb, st);
+hipError_t sigma_impl(int planes, const SectorTabs &T, const double *C, double *S, double *CT, double *ST,
+                      double *epart, hipStream_t st, void *zout, bool zip32, bool *zipped) {
+    const int64_t nsa = T.nsa, nsb = T.nsb, rows = planes * nsa;
+    if (T.R > 0) {
+        const hipError_t e = alpha_same_spin(planes, T, C, S, st);
         if (e != hipSuccess) return e;
-    } else {
-        hipLaunchKernelGGL(k_spmm<A>, dim3((unsigned)nsa, (unsigned)((nsb + 255) / 256)), dim3(256), 0, st,
-                           T.ha_ptr, T.ha_col, T.ha_val, C, S, nsb);
+        if (zout && planes == 1) {
+            if (zipped) *zipped = true;
+            return zip32 ? row_launch<ROW_ZIP32>(1, T, C, S, zout, epart, nullptr, 0, st)
+                         : row_launch<ROW_ZIP>(1, T, C, S, zout, epart, nullptr, 0, st);
+        }
+        return row_launch<ROW_S>(planes, T, C, S, nullptr, epart, nullptr, 0, st);
     }
-    // alpha-beta part, directly or through the factors of (pq|rs)
-    if (T.nexcA > 0 && T.nexcB > 0 && T.R == 0) {
-        const int lds = g_lds_max > 0 ? g_lds_max : 65536;
-        const int64_t per = nsb * (int64_t)sizeof(A) + (int64_t)T.M * T.M * (int64_t)sizeof(double);
-        int64_t ec = lds / per;
-        if (ec > T.nexcA) ec = T.nexcA;
-        const size_t shm = (size_t)(ec * per);
-        // Register-resident lists pay off while each workgroup covers the row
-        // in at most two column groups (the staged rows are reloaded per group).
-        if (ec >= 1 && T.nexcB <= 48 && nsb <= 2048)
-            hipLaunchKernelGGL((k_sigma_ab_reg<A, 48, 1024>), dim3((unsigned)nsa), dim3(1024), shm, st, T.excA,
-                               T.nexcA, T.excB, T.nexcB, T.g, T.M, C, S, nsb, (int)ec);
-        else if (ec >= 1 && T.nexcB <= 64 && nsb <= 1024)
-            hipLaunchKernelGGL((k_sigma_ab_reg<A, 64, 512>), dim3((unsigned)nsa), dim3(512), shm, st, T.excA,
-                               T.nexcA, T.excB, T.nexcB, T.g, T.M, C, S, nsb, (int)ec);
-        else if (ec >= 1)
-            hipLaunchKernelGGL(k_sigma_ab<A>, dim3((unsigned)nsa), dim3(512), shm, st, T.excA,
-                               T.nexcA, T.excB, T.nexcB, T.g, T.M, C, S, nsb, (int)ec);
-        else  // a source row does not fit in LDS
-            hipLaunchKernelGGL(k_sigma_ab_global<A>, dim3((unsigned)nsa), dim3(256), 0, st, T.excA, T.nexcA,
-                               T.excB, T.nexcB, T.g, T.M, C, S, nsb);
+    hipError_t e = alpha_same_spin(planes, T, C, S, st);
+    if (e != hipSuccess) return e;
+    if (T.nexcA > 0 && T.nexcB > 0) {
+        if (T.gp) {
+            e = ab_launch(C, S, T, planes, st);
+            if (e != hipSuccess) return e;
+        } else {  // rows too long for k_ab's LDS buffers, or of a single column
+            const int lds = g_lds_max > 0 ? g_lds_max : 65536;
+            const int64_t per = nsb * (int64_t)sizeof(double) + (int64_t)T.M * T.M * (int64_t)sizeof(double);
+            int64_t ec = lds / per;
+            if (ec > T.nexcA) ec = T.nexcA;
+            const dim3 grid((unsigned)nsa, (unsigned)planes);
+            if (ec >= 1)
+                hipLaunchKernelGGL(k_sigma_ab, grid, dim3(512), (size_t)(ec * per), st, T.excA, T.nexcA, T.excB,
+                                   T.nexcB, T.g, T.M, C, S, nsb, planes * nsb, (int)ec);
+            else  // a source row does not fit in LDS
+                hipLaunchKernelGGL(k_sigma_ab_global, grid, dim3(256), 0, st, T.excA, T.nexcA, T.excB, T.nexcB, T.g,
+                                   T.M, C, S, nsb, planes * nsb);
+        }
     }
-    if (T.nexcA > 0 && T.nexcB > 0 && T.R > 0) {
-        if (T.R > 8) return hipErrorInvalidValue;  // wider factorisations take the direct product
-        const hipError_t e = lr_launch<A, 8>(T, C, S, st);
+    const unsigned ng = combine_grid(nsa * nsb);
+    if (T.hb_dense_t) {
+        // the beta GEMM accumulates into S directly
+        e = dense_beta_accumulate(T.blas, T.hb_dense_t, C, S, rows, nsb, st);
         if (e != hipSuccess) return e;
-    }
-    if (T.hb_dense_t && sizeof(A) == sizeof(double)) {
-        // real state: the beta GEMM accumulates into S directly
-        const hipError_t e = dense_beta_accumulate(T.blas, T.hb_dense_t, (const double *)C, (double *)S, nsa, nsb, st);
-        if (e != hipSuccess) return e;
-        if (zout) {
-            hipLaunchKernelGGL(k_ecore_zip, dim3(combine_grid(nsa * nsb)), dim3(256), 0, st, (const double *)S,
-                               (const double *)C, T.ecore, nsa * nsb, zout, epart);
+        if (zout && !zip32 && planes == 1) {
+            hipLaunchKernelGGL(k_ecore_zip, dim3(ng), dim3(256), 0, st, S, C, T.ecore, rows * nsb, (double2 *)zout,
+                               epart);
             if (zipped) *zipped = true;
         } else {
-            hipLaunchKernelGGL(k_ecore_dot, dim3(combine_grid(nsa * nsb)), dim3(256), 0, st, (double *)S,
-                               (const double *)C, T.ecore, nsa * nsb, epart);
+            hipLaunchKernelGGL(k_ecore_dot, dim3(ng), dim3(256), 0, st, S, C, T.ecore, rows * nsb, epart);
         }
         return hipGetLastError();
     }
     // same-spin beta part on the transpose, then combine
-    {
-        const dim3 grid((unsigned)((nsb + 31) / 32), (unsigned)((nsa + 31) / 32));
-        hipLaunchKernelGGL(k_transpose<A>, grid, dim3(32, 8), 0, st, C, CT, nsa, nsb);
-    }
-    if (T.hb_dense) {
-        const hipError_t e = dense_same_spin(T.blas, T.hb_dense, (const double *)CT, (double *)ST, nsb, w * nsa, st);
-        if (e != hipSuccess) return e;
-    } else {
-        hipLaunchKernelGGL(k_spmm<A>, dim3((unsigned)nsb, (unsigned)((nsa + 255) / 256)), dim3(256), 0, st,
-                           T.hb_ptr, T.hb_col, T.hb_val, CT, ST, nsa);
-    }
-    hipLaunchKernelGGL(k_combine<A>, dim3(combine_grid(nsa * nsb)), dim3(32, 8), 0, st, S, ST, C, T.ecore,
-                       nsa, nsb, epart);
+    hipLaunchKernelGGL(k_transpose, dim3((unsigned)((nsb + 31) / 32), (unsigned)((rows + 31) / 32)),
+                       dim3(32, 8), 0, st, C, CT, rows, nsb, nsb, rows, (int64_t)0, (int64_t)0);
+    hipLaunchKernelGGL(k_spmm, dim3((unsigned)nsb, (unsigned)((rows + 255) / 256)), dim3(256), 0, st, T.hb_ptr,
+                       T.hb_col, T.hb_val, CT, ST, rows);
+    hipLaunchKernelGGL(k_combine, dim3(ng), dim3(32, 8), 0, st, S, ST, C, T.ecore, rows, nsb, epart);
     return hipGetLastError();
 }
 
@@ -949,16 +1183,24 @@ hipError_t convert_impl(const void *in, void *out, int64_t n, hipStream_t st) {
 void init_sigma_kernels() {
     if (g_lds_max > 0) return;
     g_lds_max = 65536;
-    std::vector<const void *> fns = {(const void *)k_sigma_ab<double>, (const void *)k_sigma_ab<double2>,
-                                     (const void *)k_sigma_ab_reg<double, 48, 1024>,
-                                     (const void *)k_sigma_ab_reg<double2, 48, 1024>,
-                                     (const void *)k_sigma_ab_reg<double, 64, 512>,
-                                     (const void *)k_sigma_ab_reg<double2, 64, 512>,
-                                     (const void *)k_lr_b<double>, (const void *)k_lr_b<double2>,
-                                     (const void *)k_lr_ab};
+    std::vector<const void *> fns = {(const void *)k_sigma_ab};
+#define FSV_ROW_FNS(BS, CP, LH, NC, NB, WV)                                \
+    fns.push_back((const void *)k_row<BS, CP, LH, NC, NB, WV, ROW_ENERGY>); \
+    fns.push_back((const void *)k_row<BS, CP, LH, NC, NB, WV, ROW_S>);      \
+    fns.push_back((const void *)k_row<BS, CP, LH, NC, NB, WV, ROW_ZIP>);    \
+    fns.push_back((const void *)k_row<BS, CP, LH, NC, NB, WV, ROW_ZIP32>)
+    FSV_ROW_FNS(512, 2, 8, 1, 2, 4);
+    FSV_ROW_FNS(512, 4, 8, 1, 2, 2);
+    FSV_ROW_FNS(1024, 4, 4, 1, 1, 4);
+    FSV_ROW_FNS(1024, 5, 2, 1, 1, 4);
+#undef FSV_ROW_FNS
+    fns.push_back((const void *)k_ab<512, 1, 20, 2>);
+    fns.push_back((const void *)k_ab<512, 2, 16, 2>);
+    fns.push_back((const void *)k_ab<512, 4, 8, 1>);
+    fns.push_back((const void *)k_ab<512, 5, 6, 1>);
     bool ok = true;
     for (const void *f : fns)
-        ok = ok && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 163840) == hipSuccess;
+        ok = ok && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, f == fns[0] ? 163840 : 163328) == hipSuccess;
     if (ok) g_lds_max = 163840;  // a gfx950 CU's LDS
     (void)hipGetLastError();
 }
@@ -1017,14 +1259,27 @@ hipError_t launch_convert(int vi, const void *in, int vo, void *out, int64_t n, 
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_sector_sigma(bool cplex, const SectorTabs &T, const void *C, void *S, void *CT, void *ST,
-                               double *epart, hipStream_t st, void *zout, bool *zipped) {
+hipError_t launch_sector_sigma(int planes, const SectorTabs &T, const double *C, double *S, double *CT, double *ST,
+                               double *epart, hipStream_t st, void *zout, int zvt, bool *zipped) {
     if (zipped) *zipped = false;
-    if (cplex)
-        return sigma_impl<double2>(T, (const double2 *)C, (double2 *)S, (double2 *)CT, (double2 *)ST, epart, st,
-                                   nullptr, nullptr);
-    return sigma_impl<double>(T, (const double *)C, (double *)S, (double *)CT, (double *)ST, epart, st,
-                              (double2 *)zout, zipped);
+    return sigma_impl(planes, T, C, S, CT, ST, epart, st, zout, zvt == V_F32, zipped);
+}
+
+hipError_t launch_sector_energy(int planes, const SectorTabs &T, const double *C, double *S, double *CT, double *ST,
+                                double *epart, const int32_t *im_flag, int32_t im_epoch, hipStream_t st) {
+    if (T.R > 0) return row_launch<ROW_ENERGY>(planes, T, C, nullptr, nullptr, epart, im_flag, im_epoch, st);
+    return sigma_impl(planes, T, C, S, CT, ST, epart, st, nullptr, false, nullptr);
+}
+
+int sigma_partials(const SectorTabs &T, int planes) {
+    return T.R > 0 ? (int)(planes * T.nsa) : (int)combine_grid(T.nsa * T.nsb);
+}
+
+hipError_t launch_row_onebody(const double *heff, int M, const uint32_t *sa, int64_t nsa, const uint32_t *sb,
+                              int64_t nsb, double *hp, double *hda, double *hdb, hipStream_t st) {
+    hipLaunchKernelGGL(k_row_onebody, dim3(blocks_for((int64_t)M * (M - 1) / 2 + nsa + nsb, 256)), dim3(256), 0, st,
+                       heff, M, sa, nsa, sb, nsb, hp, hda, hdb);
+    return hipGetLastError();
 }
 
 hipError_t launch_pool(int vtype, const void *psi, const void *lam, const PairOp *ops, const uint32_t *lists,
@@ -1054,12 +1309,11 @@ hipError_t launch_csr_dense(const int64_t *rowptr, const int32_t *col, const dou
     return hipGetLastError();
 }
 
-hipError_t launch_ctranspose(bool cplex, const void *in, void *out, int64_t rows, int64_t cols, hipStream_t st) {
-    const dim3 grid((unsigned)((cols + 31) / 32), (unsigned)((rows + 31) / 32));
-    if (cplex)
-        hipLaunchKernelGGL(k_transpose<double2>, grid, dim3(32, 8), 0, st, (const double2 *)in, (double2 *)out, rows, cols);
-    else
-        hipLaunchKernelGGL(k_transpose<double>, grid, dim3(32, 8), 0, st, (const double *)in, (double *)out, rows, cols);
+hipError_t launch_plane_transpose(const double *in, double *out, int64_t rows, int64_t cols, int planes,
+                                  hipStream_t st) {
+    hipLaunchKernelGGL(k_transpose,
+                       dim3((unsigned)((cols + 31) / 32), (unsigned)((rows + 31) / 32), (unsigned)planes), dim3(32, 8), 0,
+                       st, in, out, rows, cols, planes * cols, planes * rows, cols, rows);
     return hipGetLastError();
 }
 

@@ -1,0 +1,65 @@
+"""H times a state through the row kernels, at row lengths around their launch
+shapes, against the oracle.
+
+Tolerances: energies 1e-10 Ha, adjoint gradients 1e-9, as for every product
+path (sums of at most a few thousand terms of unit-norm states)."""
+
+import numpy as np
+import pytest
+
+from oracle import sector
+from workloads import random_problem
+from tests.gpu_helpers import dense_from_sector, oracle_energy_grad, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def fsv(gpu):
+    import paper_2405_11567_amd as m
+    m.load()
+    return m
+
+
+def _problem(m, na, nb, rank, seed):
+    p = random_problem(2 * m, 2 * nb, 6, seed=seed, theta_std=0.4, replace=True, ordering=seed % 2)
+    # na differs from nb: operators are drawn again for the actual counts
+    from workloads import uccsd_pool
+    rng = np.random.default_rng(seed)
+    pool = uccsd_pool(m, na, nb)
+    p.n_alpha, p.n_beta = na, nb
+    p.ops = np.ascontiguousarray(pool[rng.integers(0, len(pool), 6)])
+    p.theta = rng.normal(0, 0.4, 6)
+    p.e_core = 0.25
+    if rank:
+        f = np.stack([(lambda l: l + l.T)(rng.normal(0, 0.05, (m, m))) for _ in range(rank)]).reshape(rank, m * m)
+        p.g = (f.T @ f).reshape(m, m, m, m)
+    return p
+
+
+# rows of 2, 3, 10, 84, 126, 210 (odd pairs), 462, 715 (odd), 924, 1287, 1716 and
+# 3003 columns; then few columns under 1287 and 3003 alpha strings
+@pytest.mark.parametrize("m,na,nb,rank", [
+    (2, 1, 1, 0), (3, 1, 1, 0), (5, 2, 2, 0), (9, 1, 3, 0), (9, 2, 4, 0), (10, 1, 4, 0), (11, 1, 5, 0),
+    (13, 1, 4, 0), (12, 1, 6, 0), (13, 1, 5, 0), (13, 1, 6, 0), (14, 1, 6, 0), (13, 5, 1, 0), (14, 6, 1, 0),
+    (3, 1, 1, 6), (5, 2, 2, 15), (9, 1, 3, 20), (9, 2, 4, 45), (11, 1, 5, 30), (13, 1, 4, 40), (12, 1, 6, 78),
+    (13, 1, 5, 30), (14, 1, 6, 20)])
+def test_row_products(fsv, m, na, nb, rank):
+    import torch
+    p = _problem(m, na, nb, rank, seed=900 + 17 * m + nb)
+    say("row products", m, na, nb, rank)
+    plan = fsv.Plan(p)
+    e, g = plan.energy_grad(p.theta)
+    e_ref, g_ref = oracle_energy_grad(p)
+    assert abs(e - e_ref) < 1e-10 and np.abs(g - g_ref).max() < 1e-9
+    psi = plan.ansatz_apply(p.theta)
+    assert abs(plan.energy(psi) - e_ref) < 1e-10
+    # a complex state, and a real one again after it
+    rng = np.random.default_rng(m)
+    d = sector.dim(m, na, nb)
+    vec = rng.normal(size=d) + 1j * rng.normal(size=d)
+    vec /= np.linalg.norm(vec)
+    full, _ = dense_from_sector(vec, p)
+    t = torch.from_numpy(full).to(plan.device)
+    assert abs(plan.energy(t) - sector.energy(vec, p.h, p.g, p.e_core, na, nb, p.ordering)) < 1e-10
+    assert abs(plan.energy(psi) - e_ref) < 1e-10
