@@ -235,6 +235,12 @@ struct fsv_pool {
     uint32_t *d_lists = nullptr;
     double *d_part = nullptr, *d_out = nullptr;
     int *d_counts = nullptr;
+    // screening by rows (U > 0): groups, their operators, tasks, partial offsets
+    int U = 0, n_gen = 0, n_plain = 0;
+    PoolGroup *d_groups = nullptr;
+    int32_t *d_gops = nullptr;
+    int2 *d_tasks = nullptr;
+    int64_t *d_off = nullptr;
     double *h_pin = nullptr;  // E, then the n screening values
     hipGraphExec_t graph = nullptr;
     const void *g_psi = nullptr, *g_lam = nullptr;
@@ -2425,27 +2431,95 @@ int fsv_pool_create(fsv_pool **out, fsv_plan *P, const int32_t *ops, int32_t n_o
         }
     // workgroups per operator: ~16 pairs per thread for the largest, at most 64
     Q->gx = (int)std::min(64.0, std::max(1.0, std::ceil(maxpairs / (256.0 * 16.0))));
-    auto dal = [&](void **p, size_t bytes) -> int {
+    auto put = [&](const void *src, size_t bytes, void **p) -> int {
         if (hipMalloc(p, std::max<size_t>(bytes, 4)) != hipSuccess) {
             (void)hipGetLastError();
             return fail(FSV_ENOMEM, "hipMalloc of %zu bytes for the pool failed", bytes);
         }
         Q->mem.push_back(*p);
+        if (src && bytes && hipMemcpy(*p, src, bytes, hipMemcpyHostToDevice) != hipSuccess) {
+            (void)hipGetLastError();
+            return fail(FSV_EDEVICE, "pool upload failed");
+        }
         return FSV_OK;
     };
-    std::vector<int> counts(n_ops, Q->gx);
-    if ((rc = dal((void **)&Q->d_ops, sizeof(PairOp) * pops.size())) ||
-        (rc = dal((void **)&Q->d_lists, 4 * lists.size())) ||
-        (rc = dal((void **)&Q->d_part, sizeof(double) * (size_t)n_ops * Q->gx)) ||
-        (rc = dal((void **)&Q->d_out, sizeof(double) * (size_t)n_ops)) ||
-        (rc = dal((void **)&Q->d_counts, sizeof(int) * (size_t)n_ops))) {
+    Q->U = pool_rows_u(P->svt, P->nsb);
+    if (Q->U > 0) {
+        // groups of the operators that move the same alpha electrons
+        std::map<uint64_t, int> of;
+        std::vector<std::vector<int32_t>> gen, plain;
+        std::vector<PoolGroup> groups;
+        for (int t = 0; t < n_ops; ++t) {
+            uint64_t ann = 0, cre = 0;
+            bool beta = false;
+            for (int x = 0; x < 4; ++x) {
+                const int so = ops[4 * t + x];
+                if (so >= 0 && so % 2 == 0) (x < 2 ? cre : ann) |= 1ull << (so / 2);
+                beta = beta || (so >= 0 && so % 2 == 1);
+            }
+            const auto in = of.emplace(ann << 32 | cre, (int)groups.size());
+            if (in.second) {
+                PoolGroup g{};
+                g.offA = (ann | cre) ? pops[t].offA : -1;
+                g.nA = (ann | cre) ? pops[t].nA : (int32_t)P->nsa;
+                groups.push_back(g);
+                gen.emplace_back();
+                plain.emplace_back();
+            }
+            (beta ? gen : plain)[in.first->second].push_back(t);
+        }
+        std::vector<int32_t> gops;
+        std::vector<int2> tasks;
+        std::vector<int64_t> off(n_ops + 1, 0);
+        // the longest tasks (most operators) first
+        std::vector<int> order(groups.size());
+        for (size_t i = 0; i < order.size(); ++i) order[i] = (int)i;
+        std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return gen[a].size() > gen[b].size(); });
+        for (int i : order) {
+            PoolGroup &g = groups[i];
+            g.op0 = (int32_t)gops.size();
+            g.ngen = (int32_t)gen[i].size();
+            g.nplain = (int32_t)plain[i].size();
+            g.parts = g.ngen ? std::max(1, 8 / g.ngen) : 1;
+            // a wavefront's operators have lists of like length
+            std::stable_sort(gen[i].begin(), gen[i].end(), [&](int32_t a, int32_t b) { return pops[a].nB > pops[b].nB; });
+            gops.insert(gops.end(), gen[i].begin(), gen[i].end());
+            gops.insert(gops.end(), plain[i].begin(), plain[i].end());
+            const int U = g.ngen ? Q->U : kPoolU, chunks = (g.nA + U - 1) / U;
+            for (int c = 0; c < chunks; ++c) tasks.push_back(make_int2(i, c * U));
+            (g.ngen ? Q->n_gen : Q->n_plain) += chunks;
+            for (int32_t t : gen[i]) off[t + 1] = (int64_t)chunks * g.parts;
+            for (int32_t t : plain[i]) off[t + 1] = chunks;
+        }
+        for (int t = 0; t < n_ops; ++t) off[t + 1] += off[t];
+        for (const PoolGroup &g : groups)  // group bounds, as the kernel reads them
+            if (g.offA >= 0 && g.offA + g.nA > (int64_t)lists.size()) {
+                delete Q;
+                return fail(FSV_EINVAL, "internal: pool group out of range");
+            }
+        if ((rc = put(groups.data(), sizeof(PoolGroup) * groups.size(), (void **)&Q->d_groups)) ||
+            (rc = put(gops.data(), 4 * gops.size(), (void **)&Q->d_gops)) ||
+            (rc = put(tasks.data(), sizeof(int2) * tasks.size(), (void **)&Q->d_tasks)) ||
+            (rc = put(off.data(), 8 * off.size(), (void **)&Q->d_off)) ||
+            (rc = put(nullptr, sizeof(double) * (size_t)off[n_ops], (void **)&Q->d_part))) {
+            delete Q;
+            return rc;
+        }
+    } else {
+        std::vector<int> counts(n_ops, Q->gx);
+        if ((rc = put(nullptr, sizeof(double) * (size_t)n_ops * Q->gx, (void **)&Q->d_part)) ||
+            (rc = put(counts.data(), sizeof(int) * counts.size(), (void **)&Q->d_counts))) {
+            delete Q;
+            return rc;
+        }
+    }
+    if ((rc = put(pops.data(), sizeof(PairOp) * pops.size(), (void **)&Q->d_ops)) ||
+        (rc = put(lists.data(), 4 * lists.size(), (void **)&Q->d_lists)) ||
+        (rc = put(nullptr, sizeof(double) * (size_t)n_ops, (void **)&Q->d_out))) {
         delete Q;
         return rc;
     }
-    if (hipMemcpy(Q->d_ops, pops.data(), sizeof(PairOp) * pops.size(), hipMemcpyHostToDevice) != hipSuccess ||
-        (!lists.empty() && hipMemcpy(Q->d_lists, lists.data(), 4 * lists.size(), hipMemcpyHostToDevice) != hipSuccess) ||
-        hipMemcpy(Q->d_counts, counts.data(), sizeof(int) * counts.size(), hipMemcpyHostToDevice) != hipSuccess ||
-        hipHostMalloc((void **)&Q->h_pin, sizeof(double) * ((size_t)n_ops + 1), hipHostMallocDefault) != hipSuccess) {
+    if (hipHostMalloc((void **)&Q->h_pin, sizeof(double) * ((size_t)n_ops + 1), hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
         delete Q;
         return fail(FSV_EDEVICE, "pool upload failed");
@@ -2480,8 +2554,15 @@ int fsv_pool_gradients(fsv_pool *Q, const double *theta, void *psi, void *lam, d
         int r;
         if ((r = enq_forward(P, psi))) return r;
         if ((r = enq_sigma(P, psi, lam))) return r;
-        HIPCHECK(launch_pool(P.svt, psi, lam, Q->d_ops, Q->d_lists, Q->n, Q->gx, P.nsa, P.nsb, Q->d_part, P.work));
-        HIPCHECK(launch_reduce_rows(Q->d_part, Q->d_counts, Q->gx, Q->n, 2.0, Q->d_out, P.work));
+        if (Q->U > 0 && Q->n_gen + Q->n_plain > 0) {
+            HIPCHECK(launch_pool_rows(P.svt, psi, lam, Q->d_ops, Q->d_lists, Q->d_groups, Q->d_gops, Q->d_tasks,
+                                      Q->n_gen, Q->n_plain, Q->U, P.nsb, Q->d_off, Q->d_part, Q->n, Q->d_out, P.work));
+        } else if (Q->U > 0) {  // no operator moves any pair of this sector
+            HIPCHECK(launch_fill_zero(Q->d_out, sizeof(double) * (size_t)Q->n, P.work));
+        } else {
+            HIPCHECK(launch_pool(P.svt, psi, lam, Q->d_ops, Q->d_lists, Q->n, Q->gx, P.nsa, P.nsb, Q->d_part, P.work));
+            HIPCHECK(launch_reduce_rows(Q->d_part, Q->d_counts, Q->gx, Q->n, 2.0, Q->d_out, P.work));
+        }
         return FSV_OK;
     };
     if (!P.use_graph) {

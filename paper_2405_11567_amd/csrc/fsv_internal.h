@@ -238,6 +238,22 @@ hipError_t launch_row_onebody(const double *heff, int M, const uint32_t *sa, int
 // partial[t * gx + x] = workgroup x's share of Re<lam|T_t|psi> for pool op t.
 hipError_t launch_pool(int vtype, const void *psi, const void *lam, const PairOp *ops, const uint32_t *lists,
                        int n_ops, int gx, int64_t nsa, int64_t nsb, double *partial, hipStream_t st);
+// Screening by rows.  A group holds the pool operators (gops[op0 ...], ngen
+// with a beta list, then nplain without one) that share the row pairs at
+// lists[offA ...] (offA = -1: every row with itself); its tasks (group, first
+// row pair) take U row pairs each (kPoolU in groups with ngen = 0, whose tasks
+// come last), and operator t's partials (chunks x parts, one part for plain
+// operators) start at partial[off[t]].
+constexpr int kPoolU = 4;
+struct PoolGroup {
+    int32_t op0, ngen, nplain, nA, parts, pad;
+    int64_t offA;
+};
+int pool_rows_u(int vtype, int64_t nsb);  // 0: rows too long
+hipError_t launch_pool_rows(int vtype, const void *psi, const void *lam, const PairOp *ops, const uint32_t *lists,
+                            const PoolGroup *groups, const int32_t *gops, const int2 *tasks, int n_gen, int n_plain,
+                            int U, int64_t nsb, const int64_t *off, double *partial, int n_ops, double *out,
+                            hipStream_t st);
 // String Hamiltonian values val[e] = v2[e] + one-body part of descriptor
 // desc[e] with h~ = ht (M x M): -1 none, -2 - I the diagonal of row I (sum of
 // h~_ii over the occupied orbitals of string str[I]), otherwise h~[desc &

@@ -828,7 +828,167 @@ __global__ __launch_bounds__(256) void k_pool(const V *__restrict__ psi, const V
     if (threadIdx.x == 0) partial[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = acc;
 }
 
-// Same term without LDS staging (rows too long for LDS): gathers from global.
+// Screening by rows: the pool's operators are grouped by their alpha part (all
+// that move the same alpha electrons share their row pairs), and a workgroup
+// stages U of the group's row pairs of psi and lam in LDS and takes every
+// operator of the group through them, one wavefront per operator (or several,
+// on interleaved pairs, where the group is small).  k_pool read the four
+// amplitudes of each pair of each operator from L2: 3.6 GB for the 1818
+// operators at 24 qubits, 877 us.  Here the rows are read once per group (0.8
+// GB) and the pairs come from LDS (32 bytes per pair of an operator with a
+// beta part): 266 us, about half in each of the two launches, bound by the
+// latency of short loops (four steps of list words and LDS reads per operator
+// and workgroup).  Operators without a beta part need no LDS: their term is a
+// dot product of whole rows, taken while they are read.
+template <typename V>
+__global__ __launch_bounds__(512) void k_pool_rows(const V *__restrict__ psi, const V *__restrict__ lam,
+                                                   const PairOp *__restrict__ ops,
+                                                   const uint32_t *__restrict__ lists,
+                                                   const PoolGroup *__restrict__ groups,
+                                                   const int32_t *__restrict__ gops,
+                                                   const int2 *__restrict__ tasks, int U, int nsb,
+                                                   const int64_t *__restrict__ off, double *__restrict__ partial) {
+    extern __shared__ double smem_d[];
+    V *rows = (V *)smem_d;  // [u][psi source, psi target, lam source, lam target][nsb]
+    const int2 task = tasks[blockIdx.x];
+    const PoolGroup g = groups[task.x];
+    const int u0 = task.y, nu = min(U, g.nA - u0), chunk = u0 / U;
+    const V *p1[kPoolU], *p2[kPoolU], *l1[kPoolU], *l2[kPoolU];
+#pragma unroll
+    for (int u = 0; u < kPoolU; ++u) {
+        int64_t ia = u0 + min(u, nu - 1), ia2 = ia;
+        if (g.offA >= 0) {
+            const uint32_t e = lists[g.offA + ia];
+            ia = e & 0x7FFFu;
+            ia2 = (e >> 15) & 0x7FFFu;
+        }
+        p1[u] = psi + ia * nsb;
+        p2[u] = psi + ia2 * nsb;
+        l1[u] = lam + ia * nsb;
+        l2[u] = lam + ia2 * nsb;
+    }
+    auto signA = [&](const PairOp &op, int u) {  // sign0 and the row pair's sign, in bit 31
+        return (op.sign0 < 0 ? 0x80000000u : 0u) ^ (op.nA >= 0 && u < nu ? lists[op.offA + u0 + u] & 0x80000000u : 0u);
+    };
+    // the rows to LDS, and the operators without a beta part (two at a time;
+    // a qubit excitation may list its strings' signs)
+    for (int i0 = 0; i0 < max(g.nplain, 1); i0 += 2) {
+        uint32_t sg[2][kPoolU];
+        const uint32_t *list[2] = {nullptr, nullptr};
+        int t[2] = {0, 0};
+        double acc[2] = {0.0, 0.0};
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+            if (i0 + b < g.nplain) {
+                t[b] = gops[g.op0 + g.ngen + i0 + b];
+                const PairOp op = ops[t[b]];
+                if (op.nB >= 0) list[b] = lists + op.offB;
+#pragma unroll
+                for (int u = 0; u < kPoolU; ++u) sg[b][u] = signA(op, u);
+            }
+        for (int v = threadIdx.x; v < nsb; v += blockDim.x) {
+            double x[2] = {0.0, 0.0};
+#pragma unroll
+            for (int u = 0; u < kPoolU; ++u)
+                if (u < nu) {
+                    const V a = p1[u][v], b = p2[u][v], c = l1[u][v], d = l2[u][v];
+                    if (g.ngen && i0 == 0) {
+                        V *r = rows + u * 4 * nsb;
+                        r[v] = a;
+                        r[nsb + v] = b;
+                        r[2 * nsb + v] = c;
+                        r[3 * nsb + v] = d;
+                    }
+                    const double o = dotre(d, a) - dotre(c, b);
+#pragma unroll
+                    for (int b2 = 0; b2 < 2; ++b2)
+                        if (i0 + b2 < g.nplain) x[b2] += flip_sign(o, sg[b2][u]);
+                }
+#pragma unroll
+            for (int b = 0; b < 2; ++b)
+                if (i0 + b < g.nplain) acc[b] += list[b] ? flip_sign(x[b], list[b][v] & 0x80000000u) : x[b];
+        }
+#pragma unroll
+        for (int b = 0; b < 2; ++b)
+            if (i0 + b < g.nplain) {
+                const double r = block_sum(acc[b]);
+                if (threadIdx.x == 0) partial[off[t[b]] + chunk] = r;
+            }
+    }
+    if (g.ngen == 0) return;
+    __syncthreads();
+    // four operators per wavefront at a time: their list words load together
+    // and their sums share one butterfly
+    constexpr int B = 4;
+    const int lane = threadIdx.x & (kWave - 1), nw = blockDim.x / kWave;
+    const int wid = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), items = g.ngen * g.parts;
+    for (int w0 = wid; w0 < items; w0 += B * nw) {
+        const uint32_t *list[B];
+        int nb[B], t[B], part[B], most = 0;
+        uint32_t sg[B][kPoolU];  // sign0 and the row pair's sign, in bit 31
+        double acc[B];
+#pragma unroll
+        for (int b = 0; b < B; ++b) {
+            const int w = min(w0 + b * nw, items - 1), i = w / g.parts;
+            part[b] = w - i * g.parts;
+            t[b] = gops[g.op0 + i];
+            const PairOp op = ops[t[b]];
+            nb[b] = w0 + b * nw < items ? op.nB : 0;
+            list[b] = lists + op.offB;
+#pragma unroll
+            for (int u = 0; u < kPoolU; ++u) sg[b][u] = signA(op, u);
+            acc[b] = 0.0;
+            most = max(most, nb[b]);
+        }
+        for (int v0 = 0; v0 < most; v0 += kWave * g.parts) {
+            uint32_t e[B];
+            bool in[B];
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                const int v = v0 + part[b] * kWave + lane;
+                in[b] = v < nb[b];
+                e[b] = in[b] ? list[b][v] : 0u;
+            }
+#pragma unroll
+            for (int b = 0; b < B; ++b) {
+                const int ib = (int)(e[b] & 0x7FFFu), ib2 = (int)((e[b] >> 15) & 0x7FFFu);
+                double x = 0.0;
+#pragma unroll
+                for (int u = 0; u < kPoolU; ++u)
+                    if (u < nu) {
+                        const V *r = rows + u * 4 * nsb;
+                        const double o = dotre(r[3 * nsb + ib2], r[ib]) - dotre(r[2 * nsb + ib], r[nsb + ib2]);
+                        x += flip_sign(o, (e[b] ^ sg[b][u]) & 0x80000000u);
+                    }
+                acc[b] += in[b] ? x : 0.0;
+            }
+        }
+        // lane l ends with the total of operator 2 (l & 1) + (l >> 1 & 1)
+        const bool b0 = lane & 1, b1 = lane & 2;
+        const double k0 = (b0 ? acc[2] : acc[0]) + __shfl_xor(b0 ? acc[0] : acc[2], 1, kWave);
+        const double k1 = (b0 ? acc[3] : acc[1]) + __shfl_xor(b0 ? acc[1] : acc[3], 1, kWave);
+        double r = (b1 ? k1 : k0) + __shfl_xor(b1 ? k0 : k1, 2, kWave);
+#pragma unroll
+        for (int m = 4; m < kWave; m <<= 1) r += __shfl_xor(r, m, kWave);
+#pragma unroll
+        for (int b = 0; b < B; ++b)
+            if (lane == (b >> 1 | (b & 1) << 1) && w0 + b * nw < items)
+                partial[off[t[b]] + (int64_t)chunk * g.parts + part[b]] = r;
+    }
+}
+
+// out[t] = 2 x the sum of operator t's partials, in order.
+__global__ __launch_bounds__(256) void k_pool_reduce(const int64_t *__restrict__ off,
+                                                     const double *__restrict__ partial, double *__restrict__ out) {
+    const int t = blockIdx.x;
+    double acc = 0.0;
+    for (int64_t i = off[t] + threadIdx.x; i < off[t + 1]; i += blockDim.x) acc += partial[i];
+    acc = block_sum(acc);
+    if (threadIdx.x == 0) out[t] = 2.0 * acc;
+}
+
+// Alpha-beta term without LDS staging (rows too long for LDS): gathers from
+// global memory.
 __global__ __launch_bounds__(256) void k_sigma_ab_global(const uint32_t *__restrict__ excA, int nexcA,
                                                          const uint32_t *__restrict__ excB, int nexcB,
                                                          const double *__restrict__ g, int M,
@@ -1198,6 +1358,8 @@ void init_sigma_kernels() {
     fns.push_back((const void *)k_ab<512, 2, 16, 2>);
     fns.push_back((const void *)k_ab<512, 4, 8, 1>);
     fns.push_back((const void *)k_ab<512, 5, 6, 1>);
+    fns.push_back((const void *)k_pool_rows<double>);
+    fns.push_back((const void *)k_pool_rows<float>);
     bool ok = true;
     for (const void *f : fns)
         ok = ok && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, f == fns[0] ? 163840 : 163328) == hipSuccess;
@@ -1293,6 +1455,45 @@ hipError_t launch_pool(int vtype, const void *psi, const void *lam, const PairOp
                            nsa, nsb, partial);
     else
         return hipErrorInvalidValue;
+    return hipGetLastError();
+}
+
+int pool_rows_u(int vtype, int64_t nsb) {
+    // row pairs per workgroup: two workgroups of 512 threads per CU while the
+    // rows allow it, at least one row pair in a CU's LDS
+    const int64_t per = 4 * nsb * vtype_bytes(vtype), lim = g_lds_max >= 163840 ? 163328 : 65024;
+    if ((vtype != V_F64 && vtype != V_F32) || per > lim) return 0;
+    int64_t u = 81664 / per;
+    return (int)(u < 1 ? 1 : (u > kPoolU ? kPoolU : u));
+}
+
+template <typename V>
+static hipError_t pool_rows_impl(const void *psi, const void *lam, const PairOp *ops, const uint32_t *lists,
+                                 const PoolGroup *groups, const int32_t *gops, const int2 *tasks, int n_gen,
+                                 int n_plain, int U, int64_t nsb, const int64_t *off, double *partial,
+                                 hipStream_t st) {
+    // groups with beta lists stage their rows in LDS; the others hold none, so
+    // that more of their workgroups run at once
+    if (n_gen > 0)
+        hipLaunchKernelGGL(k_pool_rows<V>, dim3((unsigned)n_gen), dim3(512), (size_t)U * 4 * nsb * sizeof(V), st,
+                           (const V *)psi, (const V *)lam, ops, lists, groups, gops, tasks, U, (int)nsb, off, partial);
+    if (n_plain > 0)
+        hipLaunchKernelGGL(k_pool_rows<V>, dim3((unsigned)n_plain), dim3(256), 0, st, (const V *)psi, (const V *)lam,
+                           ops, lists, groups, gops, tasks + n_gen, kPoolU, (int)nsb, off, partial);
+    return hipGetLastError();
+}
+
+hipError_t launch_pool_rows(int vtype, const void *psi, const void *lam, const PairOp *ops, const uint32_t *lists,
+                            const PoolGroup *groups, const int32_t *gops, const int2 *tasks, int n_gen, int n_plain,
+                            int U, int64_t nsb, const int64_t *off, double *partial, int n_ops, double *out,
+                            hipStream_t st) {
+    const hipError_t e =
+        vtype == V_F64 ? pool_rows_impl<double>(psi, lam, ops, lists, groups, gops, tasks, n_gen, n_plain, U, nsb, off,
+                                                partial, st)
+                       : pool_rows_impl<float>(psi, lam, ops, lists, groups, gops, tasks, n_gen, n_plain, U, nsb, off,
+                                               partial, st);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_pool_reduce, dim3((unsigned)n_ops), dim3(256), 0, st, off, partial, out);
     return hipGetLastError();
 }
 

@@ -63,3 +63,27 @@ def test_row_products(fsv, m, na, nb, rank):
     t = torch.from_numpy(full).to(plan.device)
     assert abs(plan.energy(t) - sector.energy(vec, p.h, p.g, p.e_core, na, nb, p.ordering)) < 1e-10
     assert abs(plan.energy(psi) - e_ref) < 1e-10
+
+
+# rows of 2, 21 (odd), 126, 462 and 924 columns; sectors whose row pairs leave
+# remainders of the workgroups' share; one operator, repeated ones, a whole pool
+@pytest.mark.parametrize("m,na,nb,excitation,ordering,precision", [
+    (2, 1, 1, 0, 0, 0), (7, 2, 2, 1, 0, 0), (9, 4, 4, 0, 1, 0), (9, 3, 4, 1, 1, 0), (11, 3, 5, 1, 0, 0),
+    (12, 2, 6, 0, 0, 0), (12, 6, 2, 1, 0, 0), (9, 4, 4, 1, 0, 1)])
+def test_pool_rows(fsv, m, na, nb, excitation, ordering, precision):
+    from workloads import uccsd_pool
+    p = _problem(m, na, nb, 0, seed=700 + 11 * m + na)
+    p.ordering, p.excitation = ordering, excitation
+    full = np.asarray(uccsd_pool(m, na, nb), dtype=np.int32)
+    rng = np.random.default_rng(m)
+    some = full[rng.integers(0, len(full), min(len(full), 70))]  # repeats
+    say("pool rows", m, na, nb, excitation, ordering, precision)
+    psi = sector.ansatz(m, na, nb, p.ops, p.theta, ordering, excitation)
+    ref = sector.pool_gradients(psi, p.h, p.g, p.e_core, full, na, nb, ordering, excitation)
+    at = {tuple(o): t for t, o in enumerate(full)}
+    plan = fsv.Plan(p, precision=precision)
+    tol = 1e-9 if precision == 0 else 1e-4  # FP32 states: as the FP32 energies
+    for ops in (full, full[-1:], some):
+        _, g = plan.pool(ops).gradients(p.theta)
+        want = ref[[at[tuple(o)] for o in ops]]
+        assert np.abs(g - want).max() < tol
