@@ -145,8 +145,10 @@ int fsv_plan_set_engine(fsv_plan *plan, int engine);
  * sweep (adjoint = 1).  Each rotation exp(theta (tau - tau^+)) mixes only
  * the two amplitudes of each of its active pairs, so consecutive operators can
  * be applied together in one launch:
- *  - component packets (the default for sector states of at most 2^22
- *    amplitudes; FSV_FUSE=packets requests them up to 2^26, where every run
+ *  - the whole sweep in one workgroup that keeps the state in LDS (the default
+ *    for sector states of at most 8192 amplitudes): one run;
+ *  - component packets (the default for larger sector states of at most 2^22
+ *    amplitudes, FSV_FUSE=packets for smaller ones; FSV_FUSE=packets also requests them up to 2^26, where every run
  *    becomes a packet run: at 30 qubits an evaluation takes 71 instead of
  *    83 ms, but planning takes ~3 minutes and the programs 13 GB of device
  *    memory; FSV_VERBOSE prints a line per planned run): the connected components of the graph joining the amplitudes

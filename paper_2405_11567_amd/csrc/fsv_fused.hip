@@ -546,6 +546,7 @@ void init_fused_kernels() {
         if (hipFuncGetAttributes(&fa, f) == hipSuccess) lim -= fa.sharedSizeBytes;
         (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lim);
     }
+    (void)init_whole_kernels(163328);
     (void)hipGetLastError();
 }
 

@@ -204,7 +204,8 @@ struct fsv_plan {
     size_t fuse_budget_fwd = 65536, fuse_budget_rev = 98304;
     // 0 LDS tiles where the cost model gains, 1 never (FSV_NO_FUSE), 2 every tile
     // run (FSV_FORCE_FUSE), 3 component packets (the default for states of at
-    // most packet_default_dim() amplitudes, where the cost model decides)
+    // most packet_default_dim() amplitudes, where the cost model decides), 4
+    // whole sweeps in one workgroup (the default where the state fits)
     int fuse_mode = 0;
 
     // graphs
@@ -996,6 +997,17 @@ int enq_reverse_dense(fsv_plan &P, void *psi, void *lam) {
 // operator.  t0, t1 (optional, profiling): a packet run's kernel start and end
 // times, or events recorded before and after the group's launches.
 int enq_group_fwd(fsv_plan &P, void *c, const FGroup &g, hipEvent_t t0 = nullptr, hipEvent_t t1 = nullptr) {
+    if (g.fused == 3) {
+        WholeInit in;
+        in.n = P.n_init;
+        in.idx = P.d_init_sidx;
+        in.val = P.d_init_sval;
+        in.ref = P.ref_phase;
+        if (t0) HIPCHECK(hipEventRecord(t0, P.work));
+        HIPCHECK(launch_whole(P.svt, false, c, P.ffwd, g, P.d_cs, in, nullptr, 0, P.work));
+        if (t1) HIPCHECK(hipEventRecord(t1, P.work));
+        return FSV_OK;
+    }
     if (g.fused == 2) {
         HIPCHECK(launch_packets(P.svt, false, c, P.ffwd, g, P.d_cs, nullptr, 0, P.work, t0, t1));
         return FSV_OK;
@@ -1030,6 +1042,12 @@ int enq_group_rev(fsv_plan &P, void *c, void *lam_c, const FGroup &g, hipEvent_t
     const int G = max_grid();
     if (reverse_on_pairs(P)) {
         void *z = P.d_C;
+        if (g.fused == 3) {
+            if (t0) HIPCHECK(hipEventRecord(t0, P.work));
+            HIPCHECK(launch_whole(P.svt, true, z, P.frev, g, P.d_cs, WholeInit{}, P.d_gpart, G, P.work));
+            if (t1) HIPCHECK(hipEventRecord(t1, P.work));
+            return FSV_OK;
+        }
         if (g.fused) {
             HIPCHECK(launch_packets(P.svt, true, z, P.frev, g, P.d_cs, P.d_gpart, G, P.work, t0, t1, store));
             return FSV_OK;
@@ -1071,6 +1089,8 @@ FGroup forward_run(const fsv_plan &P, const FGroup &g) {
 }
 
 int enq_forward_sector(fsv_plan &P, void *c) {
+    if (!P.ffwd.groups.empty() && P.ffwd.groups[0].fused == 3)  // starts from the initial state by itself
+        return enq_group_fwd(P, c, P.ffwd.groups[0]);
     HIPCHECK(launch_fill_zero(c, (size_t)P.dim * vtype_bytes(P.svt), P.work));
     // The reference is string 0 x string 0.  Its alpha-first amplitude carries
     // the ordering sign so that the dense image starts at exactly +1 |ref>.
@@ -1311,6 +1331,11 @@ int launch_energy_only(fsv_plan &P, void *psi) {
     return FSV_OK;
 }
 
+// Whether whole sweeps run in one workgroup: the state's pairs fit a CU's LDS.
+bool whole_fits(const fsv_plan &P) {
+    return P.dim <= whole_max_dim(vtype_bytes(P.svt));
+}
+
 // Fused runs of both sweeps for the current LDS budgets, and the gradient
 // partial counts of the adjoint sweep that they imply.
 int rebuild_fused(fsv_plan &P) {
@@ -1326,7 +1351,10 @@ int rebuild_fused(fsv_plan &P) {
         o.cus = cus;
     (void)hipGetLastError();
     int rc;
-    if (P.fuse_mode == 3 && P.dim <= packet_max_dim()) {
+    if (P.fuse_mode == 4) {  // both sweeps run the same program
+        if ((rc = build_whole(P.nsa, P.nsb, P.pops, P.h_plists, o.es, P.frev))) return rc;
+        P.ffwd.share(P.frev);
+    } else if (P.fuse_mode == 3 && P.dim <= packet_max_dim()) {
         // both sweeps run the same packet runs; above the default size (only
         // on request) every run is one: the cost model's rates are those of
         // cache-resident states, and at 30 qubits every run pays
@@ -1494,7 +1522,7 @@ int build_device(fsv_plan &P) {
     if ((rc = dalloc(P, &P.d_ccount, (size_t)std::max(P.K, 1)))) return rc;
     if ((rc = upload(P, P.d_plists, plists.data(), plists.size()))) return rc;
     if ((rc = upload(P, P.d_pops, P.pops.data(), P.pops.size()))) return rc;
-    P.fuse_mode = P.dim <= packet_default_dim() ? 3 : 0;
+    P.fuse_mode = whole_fits(P) ? 4 : (P.dim <= packet_default_dim() ? 3 : 0);
     if (const char *e = std::getenv("FSV_FUSE")) {
         if (!std::strcmp(e, "tiles")) P.fuse_mode = 0;
         if (!std::strcmp(e, "packets")) P.fuse_mode = 3;
@@ -1825,6 +1853,7 @@ int autotune_sector(fsv_plan &P, void *psi, void *lam, std::string &rep) {
                                {0, 65536, 98304},  {0, 65536, 131072},  {0, 98304, 163840},
                                {0, 163840, 163840}};
     if (P.dim <= packet_default_dim()) cands.push_back({3, 0, 0});
+    if (whole_fits(P)) cands.push_back({4, 0, 0});
     const Cand keep{P.fuse_mode, P.fuse_budget_fwd, P.fuse_budget_rev};
     std::vector<double> th(P.K, 0.1);
     int rc;
@@ -1859,6 +1888,8 @@ int autotune_sector(fsv_plan &P, void *psi, void *lam, std::string &rep) {
         const int fr = fused_runs(P.ffwd, &fo), rr = fused_runs(P.frev, &ro);
         if (c.mode == 1)
             snprintf(line, sizeof line, "one launch per operator: %.3f ms\n", ms);
+        else if (c.mode == 4)
+            snprintf(line, sizeof line, "whole sweeps in one workgroup: %.3f ms\n", ms);
         else if (c.mode == 3)
             snprintf(line, sizeof line, "component packets: %d runs (%d ops): %.3f ms\n", rr, ro, ms);
         else
@@ -1877,7 +1908,10 @@ int autotune_sector(fsv_plan &P, void *psi, void *lam, std::string &rep) {
     if (rc) return rc;
     if (rc2) return rc2;
     snprintf(line, sizeof line, "chosen: %s, LDS %zu / %zu KiB\n",
-             bestc.mode == 1 ? "per operator" : (bestc.mode == 3 ? "component packets" : "fused runs"),
+             bestc.mode == 1   ? "per operator"
+             : bestc.mode == 3 ? "component packets"
+             : bestc.mode == 4 ? "whole sweeps"
+                               : "fused runs",
              P.fuse_budget_fwd / 1024, P.fuse_budget_rev / 1024);
     rep += line;
     return FSV_OK;
@@ -2000,7 +2034,7 @@ int fsv_plan_runs(const fsv_plan *P, int adjoint, int32_t *run_start, int32_t *f
         for (int k = g.k0; k < g.k0 + g.nops; ++k) {
             if (run_start) run_start[k] = g.k0;
             if (fused_tiles)
-                fused_tiles[k] = g.fused == 2 ? g.n_packets : (g.fused ? g.n_orbits * g.n_blocks : 0);
+                fused_tiles[k] = g.fused >= 2 ? g.n_packets : (g.fused ? g.n_orbits * g.n_blocks : 0);
         }
     return (int)S.groups.size();
 }

@@ -276,8 +276,9 @@ void init_sigma_kernels();
 // ---- fused operator runs on the sector state (fsv_fused.hip, fsv_packet.hip) ----
 constexpr int kPacketAmps = 256;  // amplitudes (index slots) of one packet
 // A run of consecutive operators applied tile by tile in LDS (fused = 1), by
-// connected-component packets (fused = 2), or a single operator left to the
-// per-operator kernels (fused = 0, nops = 1).  A tile run keeps, per alpha
+// connected-component packets (fused = 2), a whole sweep in one workgroup
+// (fused = 3, launch_whole), or a single operator left to the per-operator
+// kernels (fused = 0, nops = 1).  A tile run keeps, per alpha
 // orbit, a program of astride words (row count, row ranks, per-operator local
 // alpha pairs) and, per beta block, one of bstride words (first column, width,
 // per-operator local beta pairs).  A packet run keeps n_packets index lists
@@ -391,6 +392,23 @@ int build_packets(int64_t nsa, int64_t nsb, const std::vector<PairOp> &pops, con
 hipError_t launch_packets(int vtype, bool adjoint, void *state, const FusedSched &S, const FGroup &g,
                           const double *cs, double *gpart, int gstride, hipStream_t st, hipEvent_t t0 = nullptr,
                           hipEvent_t t1 = nullptr, bool store = true);
+// A whole sweep in one workgroup (fused = 3: rmax steps, wr threads, lmax
+// amplitudes) for states of at most whole_max_dim(bytes per amplitude)
+// amplitudes.  Forward: initialises the state itself (n entries idx / val, or
+// the amplitude ref at index 0) and writes psi; adjoint: reads the (psi, lam)
+// pairs and writes only gradient partials.
+struct WholeInit {
+    int32_t n = 0;
+    const int64_t *idx = nullptr;
+    const double *val = nullptr;
+    double ref = 1.0;
+};
+int64_t whole_max_dim(int es);
+int build_whole(int64_t nsa, int64_t nsb, const std::vector<PairOp> &pops, const std::vector<uint32_t> &lists, int es,
+                FusedSched &S);
+hipError_t launch_whole(int vtype, bool adjoint, void *state, const FusedSched &S, const FGroup &g, const double *cs,
+                        const WholeInit &in, double *gpart, int gstride, hipStream_t st);
+bool init_whole_kernels(int bytes);  // dynamic LDS the kernels may use
 void init_fused_kernels();
 size_t fused_lds_limit();
 // Forward (psi) or adjoint (psi, lam, gradient partials gpart[k * gstride + tile]).

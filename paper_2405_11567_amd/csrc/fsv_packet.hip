@@ -280,6 +280,130 @@ __global__ __launch_bounds__(kWave) void k_pkt(T *__restrict__ psi, typename Slo
     }
 }
 
+// A whole sweep in one workgroup, for states whose (psi, lam) pairs fit a CU's
+// LDS (whole_max_dim).  A packet launch on such a state is all latency (16
+// qubits: 5.1 us forward and 6.8 us adjoint for 15 operators), and the runs'
+// cap on operators, not their components, ends them.  Here the state stays in
+// LDS, operators follow each other with a workgroup barrier, and the program
+// (one 32-bit word per pair and thread: two slots, in the order that makes the
+// rotation positive, and two flags for the last step of an operator in either
+// sweep order; equal slots: no pair) is loaded 16 steps ahead.  An operator
+// with more pairs than threads takes several steps, without barriers between
+// them: its pairs are disjoint.  Bound by each step's chain of LDS read,
+// rotation, LDS write and barrier, 0.4 us adjoint and 0.25 us forward.  16
+// qubits, 360 operators: 163 + 106 us instead of 24 runs' 163 + 121 us;
+// evaluations of shorter sequences, whose runs are shorter too, gain more (100
+// operators at 16 qubits FP32 164 -> 121 us, 60 at 12 qubits 124 -> 74 us, 26
+// at 8 qubits 72 -> 50 us).  Ordering an operator's pairs against LDS bank
+// conflicts did not help (169 us).
+constexpr int kWholeSteps = 16;  // steps per block: loaded together, their gradient terms summed together
+constexpr int kWholeThreads = 512;  // adjoint at 16 qubits with at most 256: 234 us, 512: 163, 1024: 190
+constexpr uint32_t kWholeFwd = 0x8000u, kWholeAdj = 0x80000000u;  // operator ends with this step (sweep order)
+constexpr uint32_t kWholeSlot = 0x7FFFu;  // > whole_max_dim()
+
+struct WholeArgs {
+    int32_t nsteps, dim, gstride, n_init;
+    const double *cs;
+    const int64_t *init_idx;
+    const double *init_val;
+    double ref;  // forward, n_init = 0: the reference amplitude (index 0)
+};
+
+template <typename T, bool ADJ>
+__global__ __launch_bounds__(kWholeThreads) void k_whole(T *__restrict__ psi, const typename Slot2<T>::V *__restrict__ z,
+                                                const uint32_t *__restrict__ words, const int2 *__restrict__ steps,
+                                                WholeArgs a, double *__restrict__ gpart) {
+    using V2 = typename Slot2<T>::V;
+    extern __shared__ double lds[];
+    double *scs = lds;                       // two blocks of kWholeSteps (cos, sin)
+    T *tp = (T *)(lds + 4 * kWholeSteps);    // forward: psi
+    V2 *tv = (V2 *)tp;                       // adjoint: (psi, lam)
+    const int t = threadIdx.x, bs = blockDim.x, lane = t & (kWave - 1), wid = t / kWave;
+    const int nblk = (a.nsteps + kWholeSteps - 1) / kWholeSteps;
+    auto step_at = [&](int i) { return ADJ ? a.nsteps - 1 - i : i; };  // i: sweep order
+    uint32_t w[kWholeSteps], wn[kWholeSteps];
+    auto load = [&](int blk, uint32_t (&v)[kWholeSteps]) {
+#pragma unroll
+        for (int j = 0; j < kWholeSteps; ++j) {
+            const int i = blk * kWholeSteps + j;
+            v[j] = i < a.nsteps ? words[(int64_t)step_at(i) * bs + t] : 0u;
+        }
+    };
+    auto angle = [&](int blk) {  // thread t < 2 kWholeSteps: one cos or sin of the block
+        const int i = min(blk * kWholeSteps + (t >> 1), a.nsteps - 1);
+        return a.cs[2 * steps[step_at(i)].x + (t & 1)];
+    };
+    load(0, w);
+    if (t < 2 * kWholeSteps) scs[t] = angle(0);
+    if (ADJ) {
+        for (int i = t; i < a.dim; i += bs) tv[i] = z[i];
+    } else {
+        for (int i = t; i < a.dim; i += bs) tp[i] = (T)0;
+        __syncthreads();
+        if (a.n_init) {
+            for (int i = t; i < a.n_init; i += bs) tp[a.init_idx[i]] = (T)a.init_val[i];
+        } else if (t == 0) {
+            tp[0] = (T)a.ref;
+        }
+    }
+    __syncthreads();
+    for (int blk = 0; blk < nblk; ++blk) {
+        double next = 0.0;
+        if (blk + 1 < nblk) {  // the next block, in flight during this one
+            load(blk + 1, wn);
+            if (t < 2 * kWholeSteps) next = angle(blk + 1);
+        }
+        const double *cs = scs + (blk & 1) * 2 * kWholeSteps;
+        double acc[kWholeSteps];
+        double c0 = cs[0], s0 = cs[1];
+#pragma unroll
+        for (int j = 0; j < kWholeSteps; ++j) {
+            acc[j] = 0.0;
+            if (blk * kWholeSteps + j < a.nsteps) {
+                const T c = (T)c0, s = (T)s0;
+                const int xs = (int)(w[j] & kWholeSlot), xd = (int)((w[j] >> 16) & kWholeSlot);
+                if (xs != xd) {
+                    if (ADJ) {
+                        const V2 A = tv[xs], B = tv[xd];
+                        T va = A.x, la = A.y, vb = B.x, lb = B.y;
+                        acc[j] += (double)lb * (double)va - (double)la * (double)vb;
+                        rotp(va, vb, c, -s);  // U^+ = U(-theta)
+                        rotp(la, lb, c, -s);
+                        tv[xs] = Slot2<T>::make(va, la);
+                        tv[xd] = Slot2<T>::make(vb, lb);
+                    } else {
+                        T va = tp[xs], vb = tp[xd];
+                        rotp(va, vb, c, s);
+                        tp[xs] = va;
+                        tp[xd] = vb;
+                    }
+                }
+                if (j + 1 < kWholeSteps) {  // ahead of the barrier
+                    c0 = cs[2 * j + 2];
+                    s0 = cs[2 * j + 3];
+                }
+                if (__builtin_amdgcn_readfirstlane((int)w[j]) & (int)(ADJ ? kWholeAdj : kWholeFwd)) __syncthreads();
+            }
+        }
+        if (ADJ) {
+            const double g = wave_sum16(acc);
+            const int i = blk * kWholeSteps + wave_sum16_index(lane);
+            if (lane < 16 && i < a.nsteps) {
+                const int2 st = steps[step_at(i)];
+                gpart[(size_t)st.x * a.gstride + st.y + wid] = g;
+            }
+        }
+        if (blk + 1 < nblk) {
+            if (t < 2 * kWholeSteps) scs[((blk + 1) & 1) * 2 * kWholeSteps + t] = next;
+            __syncthreads();
+#pragma unroll
+            for (int j = 0; j < kWholeSteps; ++j) w[j] = wn[j];
+        }
+    }
+    if (!ADJ)
+        for (int i = t; i < a.dim; i += bs) psi[i] = tp[i];
+}
+
 // Batched form: one launch carries one run of many independent instances.
 // Each packet's header also holds (word kBHdr + ...) its instance's first
 // amplitude in the arena (two words), the instance dimension (lam follows
@@ -1082,6 +1206,108 @@ int build_batch_packets(const std::vector<BatchPacketInst> &insts, const std::ve
         }
     }
     return FSV_OK;
+}
+
+// 8192: FP64 at 7056 amplitudes takes 135 us instead of the packets' 150 us
+// (100 operators), FP32 at 15876 237 us instead of 172 us.
+int64_t whole_max_dim(int es) {
+    return std::min<int64_t>(8192, (int64_t)(fused_lds_limit() - 1024) / (2 * es));
+}
+
+int build_whole(int64_t nsa, int64_t nsb, const std::vector<PairOp> &pops, const std::vector<uint32_t> &lists, int es,
+                FusedSched &S) {
+    S.release();
+    const int K = (int)pops.size();
+    const int64_t dim = nsa * nsb;
+    if (dim > whole_max_dim(es)) return fail(FSV_EINVAL, "internal: state too large for one workgroup");
+    auto pairs_of = [&](const PairOp &p) { return (p.nA >= 0 ? p.nA : nsa) * (p.nB >= 0 ? p.nB : nsb); };
+    // A step of nw wavefronts measured 0.21 + 0.0175 nw us (adjoint, FP64):
+    // fewest threads that do not take more steps than they save.
+    int nw = 1;
+    int64_t best = -1;
+    for (int v = 1; v <= kWholeThreads / kWave; ++v) {
+        int64_t cost = 0;
+        for (const PairOp &p : pops) cost += (pairs_of(p) + v * kWave - 1) / (v * kWave) * (12 + v);
+        if (best < 0 || cost < best) best = cost, nw = v;
+    }
+    const int bs = nw * kWave;
+    std::vector<uint32_t> words, steps, pairs;  // steps: operator, first gradient slot
+    std::vector<uint8_t> used(dim);
+    S.count.assign(K, 0);
+    for (int k = 0; k < K; ++k) {
+        pairs.clear();
+        bool good = true;
+        std::fill(used.begin(), used.end(), 0);
+        for_pairs(pops[k], lists, nsa, nsb, [&](int32_t s, int32_t d, bool neg) {
+            good = good && s >= 0 && d >= 0 && s < dim && d < dim && s != d && !used[s] && !used[d];
+            if (!good) return false;
+            used[s] = used[d] = 1;
+            pairs.push_back(neg ? (uint32_t)d | ((uint32_t)s << 16) : (uint32_t)s | ((uint32_t)d << 16));
+            return true;
+        });
+        if (!good) return fail(FSV_EINVAL, "internal: pairs of operator %d", k);
+        const int ns = (int)((pairs.size() + bs - 1) / bs);
+        const size_t w0 = words.size();
+        words.insert(words.end(), pairs.begin(), pairs.end());
+        words.resize(w0 + (size_t)ns * bs, 0u);
+        for (int i = 0; i < bs; ++i) {
+            words[w0 + i] |= kWholeAdj;
+            words[w0 + (size_t)(ns - 1) * bs + i] |= kWholeFwd;
+        }
+        for (int i = 0; i < ns; ++i) {
+            steps.push_back((uint32_t)k);
+            steps.push_back((uint32_t)(i * nw));
+        }
+        S.count[k] = ns * nw;
+    }
+    FGroup g{};
+    g.k0 = 0;
+    g.nops = K;
+    g.fused = 3;
+    g.n_packets = 1;
+    g.wr = bs;
+    g.rmax = (int32_t)(steps.size() / 2);
+    g.lmax = (int32_t)dim;
+    if (K > 0) S.groups.push_back(g);
+    int rc;
+    if ((rc = upload_words(words, S, &S.d_aprog)) || (rc = upload_words(steps, S, &S.d_bprog))) {
+        S.release();
+        return rc;
+    }
+    S.packets = true;
+    return FSV_OK;
+}
+
+namespace {
+
+template <typename T, bool ADJ>
+hipError_t whole_impl(void *state, const FusedSched &S, const FGroup &g, const double *cs, const WholeInit &in,
+                      double *gpart, int gstride, hipStream_t st) {
+    using V2 = typename Slot2<T>::V;
+    WholeArgs a{g.rmax, g.lmax, gstride, in.n, cs, in.idx, in.val, in.ref};
+    const size_t shm = sizeof(double) * 4 * kWholeSteps + (size_t)g.lmax * (ADJ ? 2 : 1) * sizeof(T);
+    hipLaunchKernelGGL((k_whole<T, ADJ>), dim3(1), dim3((unsigned)g.wr), shm, st, ADJ ? (T *)nullptr : (T *)state,
+                       ADJ ? (const V2 *)state : (const V2 *)nullptr, S.d_aprog, (const int2 *)S.d_bprog, a, gpart);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t launch_whole(int vtype, bool adjoint, void *state, const FusedSched &S, const FGroup &g, const double *cs,
+                        const WholeInit &in, double *gpart, int gstride, hipStream_t st) {
+    if (vtype == V_F64)
+        return adjoint ? whole_impl<double, true>(state, S, g, cs, in, gpart, gstride, st)
+                       : whole_impl<double, false>(state, S, g, cs, in, gpart, gstride, st);
+    return adjoint ? whole_impl<float, true>(state, S, g, cs, in, gpart, gstride, st)
+                   : whole_impl<float, false>(state, S, g, cs, in, gpart, gstride, st);
+}
+
+bool init_whole_kernels(int bytes) {
+    bool ok = true;
+    for (const void *f : {(const void *)k_whole<double, true>, (const void *)k_whole<double, false>,
+                          (const void *)k_whole<float, true>, (const void *)k_whole<float, false>})
+        ok = ok && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
+    return ok;
 }
 
 size_t batch_packet_lds(int wr, bool adjoint) {

@@ -87,3 +87,42 @@ def test_pool_rows(fsv, m, na, nb, excitation, ordering, precision):
         _, g = plan.pool(ops).gradients(p.theta)
         want = ref[[at[tuple(o)] for o in ops]]
         assert np.abs(g - want).max() < tol
+
+
+# whole sweeps in one workgroup (states of at most 8192 amplitudes): 1 operator,
+# 16 and 17 (a block of steps and its remainder), operators of one pair and of
+# several steps; 8281 amplitudes: packets either way
+@pytest.mark.parametrize("m,na,nb,k,precision", [
+    (2, 1, 1, 1, 0), (4, 2, 2, 16, 0), (4, 2, 2, 17, 1), (6, 1, 3, 33, 0), (9, 3, 3, 17, 0), (9, 3, 3, 40, 1),
+    (13, 2, 2, 16, 0), (14, 2, 2, 17, 0)])
+def test_whole_sweeps(fsv, m, na, nb, k, precision, monkeypatch):
+    import dataclasses
+    from workloads import uccsd_pool
+    from tests.gpu_helpers import random_dets
+    p = _problem(m, na, nb, 0, seed=500 + m)
+    pool = uccsd_pool(m, na, nb)
+    rng = np.random.default_rng(m + k)
+    p = dataclasses.replace(p, ops=np.ascontiguousarray(pool[rng.integers(0, len(pool), k)]),
+                            theta=rng.normal(0, 0.3, k))
+    say("whole sweeps", m, na, nb, k, precision)
+    plan = fsv.Plan(p, precision=precision)
+    dim = sector.dim(m, na, nb)
+    if dim <= 8192:
+        assert all((r == 0).all() and (t == 1).all() for r, t in (plan.runs(), plan.runs(adjoint=True)))
+    monkeypatch.setenv("FSV_FUSE", "packets")
+    ref = fsv.Plan(p, precision=precision)
+    e_ref, g_ref = oracle_energy_grad(p)
+    tol_e, tol_g = (1e-10, 1e-9) if precision == 0 else (1e-4, 1e-4)
+    for warm in (False, True):
+        if warm:
+            dets, coef = random_dets(p, min(5, dim), seed=k)
+            plan.set_initial_state(dets, coef)
+            ref.set_initial_state(dets, coef)
+        for _ in range(2):
+            e, g = plan.energy_grad(p.theta)
+            e2, g2 = ref.energy_grad(p.theta)
+            # the same rotations in the same order; gradient terms of a unit-norm
+            # state summed in another order
+            assert abs(e - e2) < 1e-12 and np.abs(g - g2).max() < 1e-11
+            if not warm:
+                assert abs(e - e_ref) < tol_e and np.abs(g - g_ref).max() < tol_g
