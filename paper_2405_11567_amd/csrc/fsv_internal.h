@@ -194,7 +194,7 @@ struct SectorTabs {
     const double *Lp, *heff, *hp, *hda, *hdb;
     // Direct product: (pq|rs) with rs packed in the order of tp (M^2 x npp,
     // zero beyond the pairs), and per alpha string its diagonal rows summed
-    // (nsa x npp); nullptr: rows that k_ab does not take.
+    // (nsa x npp); nullptr: rows that k_abm and k_ab do not take.
     const double *gp, *dg;
     int npp;
 };
@@ -220,7 +220,7 @@ hipError_t launch_convert(int vt_in, const void *in, int vt_out, void *out, int6
 // *zipped is set.
 unsigned combine_grid(int64_t dim);
 int sigma_partials(const SectorTabs &T, int planes);
-// Whether rows of ncols columns fit k_row (factorised) and k_ab (direct).
+// Whether rows of ncols columns fit k_row (factorised) and k_abm or k_ab (direct).
 bool row_kernel_fits(int64_t ncols);
 bool ab_kernel_fits(int64_t ncols);
 hipError_t launch_sector_sigma(int planes, const SectorTabs &T, const double *C, double *S, double *CT,

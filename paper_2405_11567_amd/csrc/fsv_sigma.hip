@@ -677,16 +677,14 @@ __global__ __launch_bounds__(256) void k_row_onebody(const double *__restrict__ 
 
 // Alpha-beta term with a general interaction, one workgroup per row Ia:
 //   S[Ia][Ib] += sum_{r<=s} (E_rs + E_sr) G_rs[Ib],  G_rs[Jb] = sum_e s_e (pq_e|rs) C[J_e][Jb]
-// (the diagonal pairs r = s once).  The former kernels took every (alpha,
-// beta) excitation pair of an element from LDS (e_a e_b reads of 16 bytes);
-// contracting the alpha side first leaves e_a M (M+1)/2 multiply-adds per
-// element on registers and scalars, and one 8-byte LDS exchange per pair rs:
-// the alpha sources are read coalesced, the factors (pq_e|rs) of RC
-// consecutive pairs are scalars, and G_rs goes through LDS to the strings that
-// pair rs reaches (the partner table of k_row).  Bound by FP64 vector
-// arithmetic: 264 us at 24 qubits with integrals of full rank (511 us before).
-// A row's diagonal alpha excitations are one term with their factors summed
-// per string (dg).
+// (the diagonal pairs r = s once).  Contracting the alpha side first leaves e_a
+// M (M+1)/2 multiply-adds per element and one 8-byte LDS exchange per pair rs,
+// to the strings that pair rs reaches (the partner table of k_row); taking
+// every (alpha, beta) excitation pair of an element from LDS, e_a e_b reads of
+// 16 bytes, took 511 us at 24 qubits with integrals of full rank.  A row's
+// diagonal alpha excitations are one term with their factors summed per string
+// (dg).  Rows of up to 2048 columns: k_abm; longer ones, whose accumulators it
+// has no registers for: k_ab.
 struct AbArgs {
     int32_t nrows, ncols, npd, ts;  // npd: orbital pairs r <= s, padded to a multiple of 4 rows in g and dg
     int32_t npp;                    // row length of g and dg (padded pairs)
@@ -694,6 +692,7 @@ struct AbArgs {
     int64_t ld, plane;
 };
 
+// On vector registers, the factors of RC consecutive pairs as scalars.
 template <int BS, int CP, int RC, int NC>
 __global__ __launch_bounds__(BS) void k_ab(const double *__restrict__ C, double *__restrict__ S,
                                            const uint32_t *__restrict__ tp, const double *__restrict__ g,
@@ -798,6 +797,118 @@ __global__ __launch_bounds__(BS) void k_ab(const double *__restrict__ C, double 
             srow[2 * pair(q)] += s[q][0];
             if (2 * pair(q) + 1 < n) srow[2 * pair(q) + 1] += s[q][1];
         }
+}
+
+// G (orbital pairs rs x columns) on the matrix cores: the product of the row's
+// factors (rs x sources, with the excitations' signs) and its gathered alpha
+// sources (sources x columns).  A chunk is 16 pairs rs; each of W wavefronts
+// holds NT 16 x 16 tiles of it.  Two neighbouring tiles take the even and the
+// odd columns of 32, so that a lane's 16-byte load feeds both.  Result register
+// r of a lane is pair 4 r + lane / 16, so G goes through LDS four pairs at a
+// time, and two workgroups share a CU at 924 columns (59 KB of LDS, 113
+// registers), one exchanging while the other multiplies.  Bound by the matrix
+// cores: 150 us at 24 qubits (924 rows and columns, 37 terms, 78 pairs), of
+// which the products take 120 us at the 45 TFLOP/s that back-to-back FP64 MFMA
+// reach on this card.  With vector arithmetic (k_ab, whose factors are scalar
+// loads that it waits for) the rows of 70 / 126 / 252 / 462 / 924 / 1716 columns
+// took 24 / 29 / 46 / 88 / 203 / 267 us, here 10.6 / 12 / 17 / 45 / 150 / 146;
+// products of tiles without columns skipped: 163 -> 150.
+struct AbSource {
+    const double *a;      // factors
+    uint32_t off, sign;  // its row, in bytes; sign bit
+};
+
+template <int W, int NT>
+__global__ __launch_bounds__(W *kWave, 4) void k_abm(
+    const double *__restrict__ C, double *__restrict__ S, const uint32_t *__restrict__ tp,
+    const double *__restrict__ g, const double *__restrict__ dg, const uint32_t *__restrict__ exc, AbArgs a) {
+    static_assert(NT % 2 == 0 && NT <= 8, "tiles in pairs; one column pair per thread in the exchange");
+    using f64x4 = __attribute__((ext_vector_type(4))) double;
+    constexpr int BS = W * kWave;
+    extern __shared__ double buf[];
+    const int n = a.ncols, ncp = (n + 1) >> 1, zero = 2 * ncp, Wp = zero + 2, tid = threadIdx.x;
+    const int lane = tid & (kWave - 1), m = lane & 15, kq = lane >> 4;
+    AbSource *src = (AbSource *)(buf + 8 * Wp);
+    int row;
+    {
+        const int v = blockIdx.x, per = a.nrows >> 3, rem = a.nrows & 7, x = v & 7;
+        row = x * per + min(x, rem) + (v >> 3);
+    }
+    const double *Cp = C + (int64_t)blockIdx.y * a.plane;
+    const uint32_t *ex = exc + (int64_t)row * a.nexc;
+    const int ks = (a.noff + 4) >> 2;  // steps of four sources: the excitations, then the row itself
+    for (int e = tid; e < 4 * ks; e += BS) {
+        const uint32_t w = e < a.noff ? ex[e] : 0u;
+        src[e] = AbSource{e < a.noff ? g + (int64_t)((w >> 16) & 0x1FFu) * a.npp : dg + (int64_t)row * a.npp,
+                          (e < a.noff ? w & 0xFFFFu : (uint32_t)row) * (uint32_t)a.ld * 8u, w & 0x80000000u};
+    }
+    if (tid < 8) buf[tid * Wp + zero] = 0.0;
+    uint32_t off[NT / 2];  // byte offset of each tile pair's column pair (kept in range; the surplus is not stored)
+#pragma unroll
+    for (int t = 0; t < NT / 2; ++t) off[t] = 16u * (uint32_t)min(((tid / kWave) * (NT / 2) + t) * 16 + m, ncp - 1);
+    const int nt = __builtin_amdgcn_readfirstlane((ncp + 15) / 16 - (tid / kWave) * (NT / 2));  // tile pairs with columns
+    auto store = [&](int t) { return ((tid / kWave) * (NT / 2) + t) * 16 + m < ncp; };
+    const bool on = tid < ncp;  // the exchange: thread tid has column pair tid
+    const int mine = min(tid, ncp - 1);
+    double s0 = 0.0, s1 = 0.0;
+    __syncthreads();
+    for (int c0 = 0; c0 < a.npd; c0 += 16) {
+        f64x4 acc[NT];
+#pragma unroll
+        for (int t = 0; t < NT; ++t) acc[t] = f64x4{0.0, 0.0, 0.0, 0.0};
+        double av;
+        dbl2u x[NT / 2];
+        auto load = [&](int k) {
+            const AbSource e = src[4 * k + kq];
+            av = flip_sign(e.a[c0 + m], e.sign);
+            if (4 * k + kq > a.noff) av = 0.0;  // padding: the row itself again, without weight
+#pragma unroll
+            for (int t = 0; t < NT / 2; ++t) x[t] = *(const dbl2u *)((const char *)Cp + (e.off + off[t]));
+        };
+        load(0);
+#pragma unroll 2
+        for (int k = 0; k < ks; ++k) {
+            const double ca = av;
+            dbl2u cx[NT / 2];
+#pragma unroll
+            for (int t = 0; t < NT / 2; ++t) cx[t] = x[t];
+            load(min(k + 1, ks - 1));  // in flight during this step's products
+#pragma unroll
+            for (int t = 0; t < NT / 2; ++t) {
+                if (t >= nt) continue;
+                acc[2 * t] = __builtin_amdgcn_mfma_f64_16x16x4f64(ca, cx[t].x, acc[2 * t], 0, 0, 0);
+                acc[2 * t + 1] = __builtin_amdgcn_mfma_f64_16x16x4f64(ca, cx[t].y, acc[2 * t + 1], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            if (c0 + 4 * r < a.npd) {
+                uint32_t t4[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) t4[u] = tp[(int64_t)min(c0 + 4 * r + u, a.npd - 1) * a.ts + mine];
+                __syncthreads();  // the previous four pairs have been read
+#pragma unroll
+                for (int t = 0; t < NT / 2; ++t)
+                    if (store(t)) {
+                        double *d = (double *)((char *)(buf + 2 * kq * Wp) + off[t]);
+                        *(dbl2a *)d = dbl2a{acc[2 * t][r], acc[2 * t + 1][r]};
+                        *(dbl2a *)(d + Wp) = dbl2a{-acc[2 * t][r], -acc[2 * t + 1][r]};
+                    }
+                __syncthreads();
+#pragma unroll
+                for (int u = 0; u < 4; ++u)
+                    if (c0 + 4 * r + u < a.npd) {
+                        s0 += buf[2 * u * Wp + (t4[u] & 0xFFFFu)];
+                        s1 += buf[2 * u * Wp + (t4[u] >> 16)];
+                    }
+            }
+        }
+    }
+    double *srow = S + (int64_t)blockIdx.y * a.plane + (int64_t)row * a.ld;
+    if (on) {
+        srow[2 * tid] += s0;
+        if (2 * tid + 1 < n) srow[2 * tid + 1] += s1;
+    }
 }
 
 // ------------------------------------------------------------ screening ----
@@ -1201,20 +1312,27 @@ hipError_t ab_launch(const double *C, double *S, const SectorTabs &T, int planes
 #define FSV_AB(BS, CP, RC, NC)                                                                                 \
     hipLaunchKernelGGL((k_ab<BS, CP, RC, NC>), grid, dim3(BS), sizeof(double) * 4 * (size_t)NC * Wp, st, C, S, \
                        T.tp, T.gp, T.dg, T.excA, a)
-    if (n <= 64)
-        FSV_AB(64, 1, 16, 4);
-    else if (n <= 128)
-        FSV_AB(128, 1, 16, 4);
-    else if (n <= 256)
-        FSV_AB(256, 1, 16, 4);
-    else if (n <= 512)
-        FSV_AB(512, 1, 20, 2);
-    else if (n <= 1024)
-        FSV_AB(512, 2, 16, 2);
+#define FSV_ABM(W, NT)                                                                                            \
+    hipLaunchKernelGGL((k_abm<W, NT>), grid, dim3(W * kWave),                                                     \
+                       sizeof(double) * 8 * (size_t)Wp + sizeof(AbSource) * 4 * (size_t)((a.noff + 4) / 4), st, C, \
+                       S, T.tp, T.gp, T.dg, T.excA, a)
+    // k_abm holds a row's offset in 32 bits
+    const bool wide = a.nrows * a.ld >= (int64_t)1 << 29;
+    if (!wide && n <= 64)
+        FSV_ABM(4, 2);
+    else if (!wide && n <= 128)
+        FSV_ABM(4, 4);
+    else if (!wide && n <= 256)
+        FSV_ABM(8, 4);
+    else if (!wide && n <= 512)
+        FSV_ABM(8, 8);
+    else if (!wide && n <= 1024)
+        FSV_ABM(16, 8);
     else if (n <= 2048)
         FSV_AB(512, 4, 8, 1);
     else
         FSV_AB(512, 5, 6, 1);
+#undef FSV_ABM
 #undef FSV_AB
     return hipGetLastError();
 }
@@ -1354,8 +1472,8 @@ void init_sigma_kernels() {
     FSV_ROW_FNS(1024, 4, 4, 1, 1, 4);
     FSV_ROW_FNS(1024, 5, 2, 1, 1, 4);
 #undef FSV_ROW_FNS
-    fns.push_back((const void *)k_ab<512, 1, 20, 2>);
-    fns.push_back((const void *)k_ab<512, 2, 16, 2>);
+    fns.push_back((const void *)k_abm<8, 8>);
+    fns.push_back((const void *)k_abm<16, 8>);
     fns.push_back((const void *)k_ab<512, 4, 8, 1>);
     fns.push_back((const void *)k_ab<512, 5, 6, 1>);
     fns.push_back((const void *)k_pool_rows<double>);

@@ -65,6 +65,17 @@ def test_row_products(fsv, m, na, nb, rank):
     assert abs(plan.energy(psi) - e_ref) < 1e-10
 
 
+# general integrals: rows of 126, 210, 252, 330, 495, 1001, 1716 and 2002 columns
+# (either side of each launch shape); 1, 4, 5, 9 and 13 sources (a step of four
+# and its remainders, no excitation at all), 6, 10 and more orbital pairs (a
+# chunk of 16 and its remainder)
+@pytest.mark.parametrize("m,na,nb,rank", [
+    (3, 3, 1, 6), (4, 4, 2, 10), (9, 8, 4, 20), (10, 9, 4, 20), (10, 10, 5, 20), (11, 1, 4, 30), (12, 2, 4, 12),
+    (14, 1, 4, 20), (13, 12, 6, 20), (14, 13, 5, 12)])
+def test_general_rows(fsv, m, na, nb, rank):
+    test_row_products(fsv, m, na, nb, rank)
+
+
 # rows of 2, 21 (odd), 126, 462 and 924 columns; sectors whose row pairs leave
 # remainders of the workgroups' share; one operator, repeated ones, a whole pool
 @pytest.mark.parametrize("m,na,nb,excitation,ordering,precision", [
