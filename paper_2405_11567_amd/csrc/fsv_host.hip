@@ -2205,14 +2205,16 @@ int rdm1(fsv_plan *P, const void *psi, double *gamma_out) {
     const int M2 = P->M * P->M;
     if ((rc = enq_gather(*P, psi))) return rc;
     if (P->nexcA > 0) {
-        HIPCHECK(launch_rdm_overlap((const double *)P->d_C, P->nsa, P->nsb, P->d_excA, P->nexcA, P->d_O, st));
+        HIPCHECK(launch_rdm_overlap((const double *)P->d_C, P->nsa, P->nsb, P->d_excA, P->nexcA, P->d_im_flag,
+                                    P->im_epoch, P->d_O, st));
         HIPCHECK(launch_rdm_bin(P->d_O, P->d_binA_off, P->d_binA_idx, M2, P->d_gamma, st));
     } else {
         HIPCHECK(launch_fill_zero(P->d_gamma, sizeof(double2) * M2, st));
     }
     HIPCHECK(launch_plane_transpose((const double *)P->d_C, (double *)P->d_CT, P->nsa, P->nsb, 2, st));
     if (P->nexcB > 0) {
-        HIPCHECK(launch_rdm_overlap((const double *)P->d_CT, P->nsb, P->nsa, P->d_excB, P->nexcB, P->d_O, st));
+        HIPCHECK(launch_rdm_overlap((const double *)P->d_CT, P->nsb, P->nsa, P->d_excB, P->nexcB, P->d_im_flag,
+                                    P->im_epoch, P->d_O, st));
         HIPCHECK(launch_rdm_bin(P->d_O, P->d_binB_off, P->d_binB_idx, M2, P->d_gamma + M2, st));
     } else {
         HIPCHECK(launch_fill_zero(P->d_gamma + M2, sizeof(double2) * M2, st));

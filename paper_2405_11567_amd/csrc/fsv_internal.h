@@ -146,7 +146,8 @@ hipError_t launch_scatter(int precision, void *lam, const double *S, const uint6
                           const uint64_t *Xb, const uint32_t *sa, const uint32_t *PPb,
                           int64_t nsa, int64_t nsb, hipStream_t st);
 hipError_t launch_rdm_overlap(const double *A, int64_t nrows, int64_t ncols,
-                              const uint32_t *exc, int nexc, double2 *O, hipStream_t st);
+                              const uint32_t *exc, int nexc, const int32_t *im_flag, int32_t im_epoch,
+                              double2 *O, hipStream_t st);
 hipError_t launch_rdm_bin(const double2 *O, const int32_t *off, const int32_t *idx, int nbins,
                           double2 *out, hipStream_t st);
 

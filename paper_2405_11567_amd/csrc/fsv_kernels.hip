@@ -364,29 +364,95 @@ __global__ void k_scatter(typename C2<R>::T *__restrict__ lam, const double *__r
 }
 
 // ------------------------------------------------------------- 1-RDM ----
-// O[I*nexc + e] = s_e * sum_c conj(A[I][c]) A[J_e][c]; one wavefront per (I, e).
-// Rows of A: ncols real parts, then ncols imaginary parts.
-__global__ __launch_bounds__(256) void k_rdm_overlap(const double *__restrict__ A, int64_t ncols,
+// O[I*nexc + e] = s_e * sum_c conj(A[I][c]) A[J_e][c], one workgroup per row I.
+// Rows of A: ncols real parts, then ncols imaginary parts (zero unless *im_flag
+// equals im_epoch).  The overlap of two rows serves both of their excitations,
+// so each pair is taken by one of its rows (even differences by the lower,
+// odd ones by the higher, which spreads them evenly) and written to both;
+// a row's diagonal excitations share its norm.  A wavefront takes kRdmRows
+// sources at a time, which share the reads of row I.  Bound by the latency of
+// the row reads from L2: 2 x 29 us at 24 qubits for a real state, where one
+// wavefront per (I, e) reading both planes took 2 x 80 us (256 threads: 36 us,
+// two sources at a time: 35 us, the column loop unrolled by 8: 37 us).
+constexpr int kRdmRows = 3;
+
+__global__ __launch_bounds__(512) void k_rdm_overlap(const double *__restrict__ A, int64_t ncols,
                                                      const uint32_t *__restrict__ exc, int nexc,
+                                                     const int32_t *__restrict__ im_flag, int32_t im_epoch,
                                                      double2 *__restrict__ O) {
-    const int64_t I = blockIdx.x;
-    const int lane = threadIdx.x % kWave, wid = threadIdx.x / kWave;
-    const int nw = blockDim.x / kWave;
-    for (int e = wid; e < nexc; e += nw) {
-        const uint32_t w = exc[I * nexc + e];
-        const int64_t J = w & 0xFFFFu;
-        const double *a = A + 2 * I * ncols, *b = A + 2 * J * ncols;
-        double re = 0.0, im = 0.0;
-        for (int64_t c = lane; c < ncols; c += kWave) {
-            const double ax = a[c], ay = a[ncols + c], bx = b[c], by = b[ncols + c];
-            re += ax * bx + ay * by;
-            im += ax * by - ay * bx;
+    extern __shared__ uint32_t rdm_lds[];
+    uint32_t *words = rdm_lds, *mine = rdm_lds + nexc, *count = mine + nexc;
+    const uint32_t I = blockIdx.x;
+    const int tid = threadIdx.x, lane = tid % kWave, wid = tid / kWave, nw = blockDim.x / kWave;
+    const bool cplx = *im_flag == im_epoch;
+    auto taken = [&](uint32_t w) {
+        const uint32_t J = w & 0xFFFFu;
+        return J != I && (I < J) == (((I ^ J) & 1u) == 0u);
+    };
+    for (int e = tid; e < nexc; e += blockDim.x) words[e] = exc[(int64_t)I * nexc + e];
+    __syncthreads();
+    for (int e = tid; e < nexc; e += blockDim.x) {
+        uint32_t at = 0;
+#pragma unroll 8
+        for (int k = 0; k < e; ++k) at += taken(words[k]) ? 1u : 0u;
+        const bool t = taken(words[e]);
+        if (t) mine[at] = (uint32_t)e;
+        if (e == nexc - 1) *count = at + (t ? 1u : 0u);
+    }
+    __syncthreads();
+    const double *a = A + 2 * (int64_t)I * ncols;
+    const int n = (int)*count, groups = (n + kRdmRows - 1) / kRdmRows;
+    for (int g = wid; g <= groups; g += nw) {
+        double re[kRdmRows], im[kRdmRows];
+        const double *b[kRdmRows];
+        uint32_t w[kRdmRows], back[kRdmRows];  // back: this lane's excitation of the source row
+        int e[kRdmRows];
+#pragma unroll
+        for (int u = 0; u < kRdmRows; ++u) {
+            re[u] = im[u] = 0.0;
+            e[u] = g < groups ? (int)mine[min(g * kRdmRows + u, n - 1)] : 0;
+            w[u] = words[e[u]];
+            b[u] = A + 2 * (int64_t)(g < groups ? w[u] & 0xFFFFu : I) * ncols;
+            back[u] = exc[(int64_t)(g < groups ? w[u] & 0xFFFFu : I) * nexc + min(lane, nexc - 1)];
         }
-        re = wave_sum(re);
-        im = wave_sum(im);
-        if (lane == 0) {
-            const bool neg = w >> 31;
-            O[I * nexc + e] = make_double2(neg ? -re : re, neg ? -im : im);
+        if (g == groups) {  // the norm
+            for (int64_t c = lane; c < ncols; c += kWave) {
+                const double ax = a[c], ay = cplx ? a[ncols + c] : 0.0;
+                re[0] += ax * ax + ay * ay;
+            }
+            const double t = wave_sum(re[0]);
+            for (int k = lane; k < nexc; k += kWave)
+                if ((words[k] & 0xFFFFu) == I)
+                    O[(int64_t)I * nexc + k] = make_double2(words[k] >> 31 ? -t : t, 0.0);
+            continue;
+        }
+        if (cplx) {
+            for (int64_t c = lane; c < ncols; c += kWave) {
+                const double ax = a[c], ay = a[ncols + c];
+#pragma unroll
+                for (int u = 0; u < kRdmRows; ++u) {
+                    const double bx = b[u][c], by = b[u][ncols + c];
+                    re[u] += ax * bx + ay * by;
+                    im[u] += ax * by - ay * bx;
+                }
+            }
+        } else {
+            for (int64_t c = lane; c < ncols; c += kWave) {
+                const double ax = a[c];
+#pragma unroll
+                for (int u = 0; u < kRdmRows; ++u) re[u] += ax * b[u][c];
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < kRdmRows; ++u) {
+            const double x = wave_sum(re[u]), y = cplx ? wave_sum(im[u]) : 0.0;
+            if (g * kRdmRows + u >= n) continue;
+            if (lane == 0) O[(int64_t)I * nexc + e[u]] = w[u] >> 31 ? make_double2(-x, -y) : make_double2(x, y);
+            const int64_t J = w[u] & 0xFFFFu;
+            for (int k = lane; k < nexc; k += kWave) {  // the excitation of row J that leads back
+                const uint32_t r = k < kWave ? back[u] : exc[J * nexc + k];
+                if ((r & 0xFFFFu) == I) O[J * nexc + k] = r >> 31 ? make_double2(-x, y) : make_double2(x, -y);
+            }
         }
     }
 }
@@ -586,8 +652,10 @@ hipError_t launch_scatter(int precision, void *lam, const double *S, const uint6
 }
 
 hipError_t launch_rdm_overlap(const double *A, int64_t nrows, int64_t ncols,
-                              const uint32_t *exc, int nexc, double2 *O, hipStream_t st) {
-    hipLaunchKernelGGL(k_rdm_overlap, dim3((unsigned)nrows), dim3(256), 0, st, A, ncols, exc, nexc, O);
+                              const uint32_t *exc, int nexc, const int32_t *im_flag, int32_t im_epoch, double2 *O,
+                              hipStream_t st) {
+    hipLaunchKernelGGL(k_rdm_overlap, dim3((unsigned)nrows), dim3(512), sizeof(uint32_t) * (2 * (size_t)nexc + 1), st,
+                       A, ncols, exc, nexc, im_flag, im_epoch, O);
     return hipGetLastError();
 }
 

@@ -76,6 +76,25 @@ def test_general_rows(fsv, m, na, nb, rank):
     test_row_products(fsv, m, na, nb, rank)
 
 
+# 1-RDMs of a real and of a complex state: no excitation between strings, one to
+# 30 of them per row, rows shorter and longer than a wavefront
+@pytest.mark.parametrize("m,na,nb", [
+    (2, 1, 1), (4, 4, 2), (4, 4, 3), (6, 3, 1), (9, 8, 4), (10, 5, 5), (11, 1, 4), (11, 5, 10), (12, 1, 6)])
+def test_rdm_rows(fsv, m, na, nb):
+    import torch
+    p = _problem(m, na, nb, 0, seed=60 + m)
+    say("rdm rows", m, na, nb)
+    plan = fsv.Plan(p)
+    rng = np.random.default_rng(m)
+    d = sector.dim(m, na, nb)
+    for vec in (rng.normal(size=d) + 1j * rng.normal(size=d), rng.normal(size=d) + 0j):
+        vec /= np.linalg.norm(vec)
+        full, _ = dense_from_sector(vec, p)
+        gam = plan.rdm1(torch.from_numpy(full).to(plan.device))
+        # sums of at most a few thousand terms of a unit-norm state
+        assert np.abs(gam - sector.rdm1(vec, m, na, nb, p.ordering)).max() < 1e-12
+
+
 # rows of 2, 21 (odd), 126, 462 and 924 columns; sectors whose row pairs leave
 # remainders of the workgroups' share; one operator, repeated ones, a whole pool
 @pytest.mark.parametrize("m,na,nb,excitation,ordering,precision", [
