@@ -171,6 +171,7 @@ struct fsv_plan {
     size_t na_off[6] = {}, na_need = 0;
     double *h_pin = nullptr;  // pinned: cs (2K) then out (K + 1) then gamma (4 M^2)
     double *h_cs = nullptr;   // pinned, coherent: cs (2K) read by energy_grad's graph itself
+    double *h_res = nullptr;  // behind h_cs: E and the gradients (K + 1), written by energy_grad's last kernel
     size_t pin_doubles = 0;
 
     // sector-compressed engine (default for energy_grad / ansatz_apply)
@@ -987,7 +988,7 @@ int enq_reverse_dense(fsv_plan &P, void *psi, void *lam) {
                                 P.shape_adj, P.d_gpart + (size_t)k * G, P.work));
     }
     if (P.defer_e)
-        HIPCHECK(launch_reduce_eg(P.d_epart, P.d_ecount + 1, P.d_gpart, P.d_gcount, G, P.K, P.d_out, P.work));
+        HIPCHECK(launch_reduce_eg(P.d_epart, P.d_ecount + 1, P.d_gpart, P.d_gcount, G, P.K, P.d_out, P.h_res, P.work));
     else
         HIPCHECK(launch_reduce_rows(P.d_gpart, P.d_gcount, G, P.K, 2.0, P.d_out + 1, P.work));
     return FSV_OK;
@@ -1131,7 +1132,7 @@ int enq_reverse_sector(fsv_plan &P, void *c, void *lam_c) {
         if (rc) return rc;
     }
     if (P.defer_e)
-        HIPCHECK(launch_reduce_eg(P.d_epart, P.d_ecount, P.d_gpart, P.d_ccount, G, P.K, P.d_out, P.work));
+        HIPCHECK(launch_reduce_eg(P.d_epart, P.d_ecount, P.d_gpart, P.d_ccount, G, P.K, P.d_out, P.h_res, P.work));
     else
         HIPCHECK(launch_reduce_rows(P.d_gpart, P.d_ccount, G, P.K, 2.0, P.d_out + 1, P.work));
     return FSV_OK;
@@ -1247,6 +1248,14 @@ int download_out(fsv_plan &P, double *E_out, double *grad_out, bool with_grad) {
     HIPCHECK(hipStreamSynchronize(P.work));
     if (E_out) *E_out = h[0];
     if (with_grad && grad_out) std::memcpy(grad_out, h + 1, sizeof(double) * P.K);
+    return FSV_OK;
+}
+
+// energy_grad's results, once its last kernel has written them to the host.
+int collect_out(fsv_plan &P, double *E_out, double *grad_out) {
+    HIPCHECK(hipStreamSynchronize(P.work));
+    if (E_out) *E_out = P.h_res[0];
+    if (grad_out) std::memcpy(grad_out, P.h_res + 1, sizeof(double) * P.K);
     return FSV_OK;
 }
 
@@ -1474,7 +1483,8 @@ int build_device(fsv_plan &P) {
     const size_t M2 = (size_t)M * M;
     P.pin_doubles = 2 * (size_t)P.K + (size_t)P.K + 1 + 4 * M2 + 8;
     HIPCHECK(hipHostMalloc((void **)&P.h_pin, sizeof(double) * P.pin_doubles, hipHostMallocDefault));
-    HIPCHECK(hipHostMalloc((void **)&P.h_cs, sizeof(double) * (2 * (size_t)P.K + 2), hipHostMallocCoherent));
+    HIPCHECK(hipHostMalloc((void **)&P.h_cs, sizeof(double) * (3 * (size_t)P.K + 3), hipHostMallocCoherent));
+    P.h_res = P.h_cs + 2 * (size_t)P.K + 2;
 
     // sector tables
     P.sa = strings_of(M, P.na);
@@ -2125,7 +2135,7 @@ int energy_grad(fsv_plan *P, const double *theta, void *psi, void *lam, double *
     if ((rc = need_workspace(*P))) return rc;
     if ((rc = stage_theta(*P, theta))) return rc;
     if ((rc = launch_energy_grad(*P, psi, lam))) return rc;
-    if ((rc = download_out(*P, E_out, grad_out, true))) return rc;
+    if ((rc = collect_out(*P, E_out, grad_out))) return rc;
     return FSV_OK;  // the host has waited for this call's work
 }
 
@@ -2142,7 +2152,8 @@ int energy_grad_noalloc(fsv_plan *P, const double *theta, void *psi, void *lam, 
     int rc;
     if ((rc = scratch_address(&base))) return rc;
     if ((rc = fence_in(*P, true))) return rc;
-    if ((rc = upload_theta(*P, theta))) return rc;
+    if ((rc = stage_theta(*P, theta))) return rc;
+    HIPCHECK(launch_copy_doubles(P->h_cs, P->d_cs, 2 * P->K, P->work));
     // the pass takes its parts from the scratch block: the plan's workspace
     // fields point there for the duration of the (eager) launches
     char *b = (char *)base;
@@ -2162,7 +2173,7 @@ int energy_grad_noalloc(fsv_plan *P, const double *theta, void *psi, void *lam, 
     P->d_gpart = sg;
     P->d_epart = se;
     if (rc) return rc;
-    if ((rc = download_out(*P, E_out, grad_out, true))) return rc;
+    if ((rc = collect_out(*P, E_out, grad_out))) return rc;
     return FSV_OK;  // the host has waited for this call's work
 }
 

