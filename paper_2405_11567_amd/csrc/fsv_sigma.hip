@@ -253,6 +253,100 @@ __global__ __launch_bounds__(256) void k_csr_dense(const int64_t *__restrict__ r
     for (int64_t k = rowptr[I] + threadIdx.x; k < rowptr[I + 1]; k += blockDim.x) row[col[k]] = val[k];
 }
 
+typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));
+
+// D (+)= A B for small row-major FP64 matrices (m x k times k x n), one
+// wavefront per 16 x 16 tile of D.  The library's tiles leave most of the chip
+// idle at these sizes: squares of 70 / 126 / 252 / 462 take it 8.0 / 11.6 / 18.6 /
+// 18.3 us, here 4.4 / 5.7 / 7.7 / 13.  Bound by the chain along k.  A wavefront
+// loads 16 k at a time (each lane four consecutive k of its row of A, so that a
+// row's 128 bytes are used at once, and the same k of its column of B),
+// kDtAhead such blocks ahead of the products (two: 16 us at 462, three: 14).
+// Whole blocks are addressed by offsets that fit 32 bits; clamping every k
+// instead took 27 us at 462.
+constexpr int kDtAhead = 4;
+
+template <bool ACC>
+__global__ __launch_bounds__(256) void k_dtile(const double *__restrict__ A, const double *__restrict__ B,
+                                               double *__restrict__ D, int m, int n, int k, int tn) {
+    using f64x4 = __attribute__((ext_vector_type(4))) double;
+    const int lane = threadIdx.x & (kWave - 1), c = lane & 15, q = lane >> 4;
+    const int tile = (int)(blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave);
+    const int row0 = tile / tn * 16, col0 = tile % tn * 16;
+    if (row0 >= m) return;
+    // byte offsets of the lane's row of A and column of B in a block (dtile_fits bounds them)
+    const uint32_t oa = 8u * (uint32_t)(min(row0 + c, m - 1) * k + 4 * q);
+    const uint32_t ob = 8u * (uint32_t)(4 * q * n + min(col0 + c, n - 1));
+    struct Block {
+        dbl2u a0, a1;
+        double b[4];
+    };
+    auto load = [&](int blk, Block &t) {
+        const char *pa = (const char *)(A + 16 * blk) + oa;
+        t.a0 = *(const dbl2u *)pa;
+        t.a1 = *(const dbl2u *)(pa + 16);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) t.b[j] = *(const double *)((const char *)(B + (int64_t)(16 * blk + j) * n) + ob);
+    };
+    f64x4 d{0.0, 0.0, 0.0, 0.0};
+    auto product = [&](const Block &x) {
+        d = __builtin_amdgcn_mfma_f64_16x16x4f64(x.a0.x, x.b[0], d, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f64_16x16x4f64(x.a0.y, x.b[1], d, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f64_16x16x4f64(x.a1.x, x.b[2], d, 0, 0, 0);
+        d = __builtin_amdgcn_mfma_f64_16x16x4f64(x.a1.y, x.b[3], d, 0, 0, 0);
+    };
+    const int nb = k / 16;  // whole blocks
+    if (nb) {
+        Block t[kDtAhead];
+#pragma unroll
+        for (int u = 0; u < kDtAhead; ++u) load(min(u, nb - 1), t[u]);
+        for (int blk = 0; blk < nb; blk += kDtAhead) {
+#pragma unroll
+            for (int u = 0; u < kDtAhead; ++u) {
+                const Block x = t[u];
+                load(min(blk + u + kDtAhead, nb - 1), t[u]);
+                if (blk + u < nb) product(x);
+            }
+        }
+    }
+    if (k & 15) {  // the rest of k; beyond it the last one again, without weight
+        Block x;
+        double av[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int kk = 16 * nb + 4 * q + j, kc = min(kk, k - 1);
+            const double v = A[(int64_t)min(row0 + c, m - 1) * k + kc];
+            av[j] = kk < k ? v : 0.0;
+            x.b[j] = B[(int64_t)kc * n + min(col0 + c, n - 1)];
+        }
+        x.a0 = dbl2u{av[0], av[1]};
+        x.a1 = dbl2u{av[2], av[3]};
+        product(x);
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int i = row0 + 4 * r + q;
+        if (i < m && col0 + c < n) {
+            double *p = D + (int64_t)i * n + col0 + c;
+            *p = ACC ? *p + d[r] : d[r];
+        }
+    }
+}
+
+// At most one tile per SIMD: 924 squared (3364 tiles) takes 77 us here and the
+// library 39.
+bool dtile_fits(int64_t m, int64_t n, int64_t k) {
+    return ((m + 15) / 16) * ((n + 15) / 16) <= 1024 && k <= 1024;
+}
+
+template <bool ACC>
+hipError_t launch_dtile(const double *A, const double *B, double *D, int64_t m, int64_t n, int64_t k, hipStream_t st) {
+    const int64_t tn = (n + 15) / 16, tiles = (m + 15) / 16 * tn;
+    hipLaunchKernelGGL(k_dtile<ACC>, dim3((unsigned)((tiles + 3) / 4)), dim3(256), 0, st, A, B, D, (int)m, (int)n,
+                       (int)k, (int)tn);
+    return hipGetLastError();
+}
+
 // Same-spin product on the matrix cores: out (rows x w*ncols, row-major) =
 // H (rows x rows, row-major, symmetric) * in (rows x w*ncols), as the
 // column-major product in' * H of rocBLAS (in' = in viewed column-major).
@@ -260,6 +354,7 @@ __global__ __launch_bounds__(256) void k_csr_dense(const int64_t *__restrict__ r
 // memset enters a captured graph.
 hipError_t dense_same_spin(void *blas, const double *H, const double *in, double *out, int64_t rows,
                            int64_t wcols, hipStream_t st) {
+    if (dtile_fits(rows, wcols, rows)) return launch_dtile<false>(H, in, out, rows, wcols, rows, st);
     rocblas_handle h = (rocblas_handle)blas;
     const double one = 1.0, zero = 0.0;
     if (rocblas_set_stream(h, st) != rocblas_status_success) return hipErrorInvalidHandle;
@@ -276,6 +371,7 @@ hipError_t dense_same_spin(void *blas, const double *H, const double *in, double
 // (nsa: the rows of C, both planes' of a complex state.)
 hipError_t dense_beta_accumulate(void *blas, const double *HbT, const double *C, double *S, int64_t nsa,
                                  int64_t nsb, hipStream_t st) {
+    if (dtile_fits(nsa, nsb, nsb)) return launch_dtile<true>(C, HbT, S, nsa, nsb, nsb, st);
     rocblas_handle h = (rocblas_handle)blas;
     const double one = 1.0;
     if (rocblas_set_stream(h, st) != rocblas_status_success) return hipErrorInvalidHandle;
@@ -364,7 +460,6 @@ __global__ __launch_bounds__(512) void k_sigma_ab(const uint32_t *__restrict__ e
 // string outside the pair's reach.
 constexpr int kRowR = 8;
 
-typedef double dbl2u __attribute__((ext_vector_type(2), aligned(8)));
 typedef double dbl2a __attribute__((ext_vector_type(2), aligned(16)));
 
 struct RowArgs {

@@ -76,6 +76,16 @@ def test_general_rows(fsv, m, na, nb, rank):
     test_row_products(fsv, m, na, nb, rank)
 
 
+# dense same-spin products of 36 to 495 strings (tiles with a remainder on every
+# side), few and many columns, either side of 1024 tiles, accumulated (general
+# integrals) and not
+@pytest.mark.parametrize("m,na,nb,rank", [
+    (9, 2, 4, 0), (8, 4, 4, 0), (8, 4, 4, 20), (9, 4, 5, 20), (10, 3, 5, 0), (12, 2, 5, 20), (12, 5, 2, 20),
+    (12, 4, 4, 0), (12, 4, 5, 0)])
+def test_same_spin_tiles(fsv, m, na, nb, rank):
+    test_row_products(fsv, m, na, nb, rank)
+
+
 # 1-RDMs of a real and of a complex state: no excitation between strings, one to
 # 30 of them per row, rows shorter and longer than a wavefront
 @pytest.mark.parametrize("m,na,nb", [
