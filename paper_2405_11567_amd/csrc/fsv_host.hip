@@ -146,6 +146,8 @@ struct fsv_plan {
     double *d_cs = nullptr, *d_gpart = nullptr, *d_epart = nullptr, *d_out = nullptr;
     int *d_gcount = nullptr, *d_ecount = nullptr;
     uint64_t *d_Xa = nullptr, *d_Xb = nullptr;
+    int32_t *d_ra = nullptr;  // rank of each alpha mask, -1 outside the sector
+    int2 *d_rb = nullptr;     // rank and prefix parity of each beta mask
     uint32_t *d_sa = nullptr, *d_PPb = nullptr, *d_excA = nullptr, *d_excB = nullptr;
     double *d_g = nullptr;
     int64_t *d_ha_ptr = nullptr, *d_hb_ptr = nullptr;
@@ -1204,8 +1206,8 @@ int enq_ansatz_dense_out(fsv_plan &P, void *psi) {
         HIPCHECK(launch_convert(V_F32, P.d_S, V_F64, P.d_C, P.dim, P.work));
         S = (const double *)P.d_C;
     }
-    HIPCHECK(launch_fill_zero(psi, ((size_t)1 << P.n) * P.amp_bytes, P.work));
-    HIPCHECK(launch_scatter_real(P.precision, psi, S, P.d_Xa, P.d_Xb, P.d_sa, P.d_PPb, P.nsa, P.nsb, P.work));
+    HIPCHECK(launch_dense_image(P.precision, P.ordering, psi, S, P.d_ra, P.d_rb, P.n, P.na, P.nb, P.nsb,
+                                P.work));
     return FSV_OK;
 }
 
@@ -1548,6 +1550,8 @@ int build_device(fsv_plan &P) {
     if ((rc = dalloc(P, &P.d_ecount, 2))) return rc;
     if ((rc = dalloc(P, &P.d_im_flag, 1))) return rc;
     if ((rc = dalloc(P, &P.d_out, (size_t)P.K + 1))) return rc;
+    if ((rc = dalloc(P, &P.d_ra, ra.size()))) return rc;
+    if ((rc = dalloc(P, &P.d_rb, rb.size()))) return rc;
     if ((rc = dalloc(P, &P.d_Xa, P.nsa))) return rc;
     if ((rc = dalloc(P, &P.d_Xb, P.nsb))) return rc;
     if ((rc = dalloc(P, &P.d_sa, P.nsa))) return rc;
@@ -1561,6 +1565,10 @@ int build_device(fsv_plan &P) {
     if ((rc = dalloc(P, &P.d_binB_idx, biB.size()))) return rc;
 
     if ((rc = upload(P, P.d_rot, P.rot.data(), P.rot.size()))) return rc;
+    std::vector<int2> rbp(rb.size(), make_int2(-1, 0));
+    for (int64_t i = 0; i < P.nsb; ++i) rbp[P.sb[i]] = make_int2((int)i, (int)PPb[i]);
+    if ((rc = upload(P, P.d_ra, ra.data(), ra.size()))) return rc;
+    if ((rc = upload(P, P.d_rb, rbp.data(), rbp.size()))) return rc;
     if ((rc = upload(P, P.d_Xa, Xa.data(), Xa.size()))) return rc;
     if ((rc = upload(P, P.d_Xb, Xb.data(), Xb.size()))) return rc;
     if ((rc = upload(P, P.d_sa, P.sa.data(), P.sa.size()))) return rc;

@@ -269,10 +269,11 @@ hipError_t launch_csr_dense(const int64_t *rowptr, const int32_t *col, const dou
 // cols values, row c of `out` planes x rows.
 hipError_t launch_plane_transpose(const double *in, double *out, int64_t rows, int64_t cols, int planes,
                                   hipStream_t st);
-// Real compact vector (double) -> dense complex buffer, like launch_scatter.
-hipError_t launch_scatter_real(int precision, void *lam, const double *S, const uint64_t *Xa,
-                               const uint64_t *Xb, const uint32_t *sa, const uint32_t *PPb,
-                               int64_t nsa, int64_t nsb, hipStream_t st);
+// Real compact vector (double) -> dense complex buffer of 2^n amplitudes, all of
+// them written.  ra, rb: per string mask of n/2 bits the string's rank or -1 (rb:
+// and its prefix parity).
+hipError_t launch_dense_image(int precision, int ordering, void *out, const double *S, const int32_t *ra,
+                              const int2 *rb, int n, int na, int nb, int64_t nsb, hipStream_t st);
 void init_sigma_kernels();
 
 // ---- fused operator runs on the sector state (fsv_fused.hip, fsv_packet.hip) ----

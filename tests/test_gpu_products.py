@@ -86,6 +86,25 @@ def test_same_spin_tiles(fsv, m, na, nb, rank):
     test_row_products(fsv, m, na, nb, rank)
 
 
+# dense images smaller than, equal to and larger than a chunk of 1024 amplitudes,
+# both orderings and types, chunks without a sector amplitude
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("ordering", [0, 1])
+@pytest.mark.parametrize("m,na,nb", [(2, 1, 1), (5, 2, 3), (6, 5, 1), (8, 1, 7), (10, 3, 2)])
+def test_dense_image(fsv, m, na, nb, ordering, precision):
+    p = _problem(m, na, nb, 0, seed=30 + m)
+    p.ordering = ordering
+    say("dense image", m, na, nb, ordering, precision)
+    plan = fsv.Plan(p, precision=precision)
+    psi = plan.new_state()
+    psi.fill_(7.0)  # every amplitude is written
+    got = plan.ansatz_apply(p.theta, psi).cpu().numpy()
+    want, _ = dense_from_sector(sector.ansatz(m, na, nb, p.ops, p.theta, ordering, 0), p)
+    # a few rotations of a unit-norm state
+    assert np.abs(got - want).max() < (1e-13 if precision == 0 else 1e-6)
+    assert (got[want == 0] == 0).sum() >= (1 << 2 * m) - sector.dim(m, na, nb)
+
+
 # 1-RDMs of a real and of a complex state: no excitation between strings, one to
 # 30 of them per row, rows shorter and longer than a wavefront
 @pytest.mark.parametrize("m,na,nb", [
