@@ -434,8 +434,8 @@ __global__ __launch_bounds__(512) void k_sigma_ab(const uint32_t *__restrict__ e
 // so all of H that is not purely alpha is local to a row of C once
 // Y_l = A_l C + 1/2 B_l C is known there:
 //   (H - H_alpha) C = h'_beta C + sum_l B_l Y_l,
-// added to the purely alpha part that S holds already.  One workgroup per row (alpha string Ia), each thread CP pairs of
-// neighbouring columns:
+// added to the purely alpha part that S holds already.  One workgroup per row
+// (alpha string Ia), each thread CP pairs of neighbouring columns:
 //  1. the row goes to LDS; B_l C gathers it through the partner table: for an
 //     orbital pair {p, q}, a string holding exactly one of them maps to the
 //     string holding the other, with one sign for E_pq and E_qp alike, so all
@@ -443,7 +443,7 @@ __global__ __launch_bounds__(512) void k_sigma_ab(const uint32_t *__restrict__ e
 //  2. A_l C reads whole rows of C (row-uniform lists and factors);
 //  3. B_l Y, pair by pair: every column's sum_l L_l[pq] Y_l goes to LDS (8
 //     bytes instead of the 8 values of Y_l), and the partner reads it.
-// Bound by FP64 vector arithmetic (the matrix cores have the same FP64 rate):
+// Bound by FP64 vector arithmetic (FP64 MFMA sustains less here, 45 against 65 TFLOP/s):
 // ~17 multiply-adds per element and orbital pair plus 8 per alpha excitation.
 // The former kernels read the 8 values of Y_l and the 8 factors of each beta
 // excitation from LDS per lane, and left both same-spin parts to GEMMs.  H C
@@ -454,8 +454,8 @@ __global__ __launch_bounds__(512) void k_sigma_ab(const uint32_t *__restrict__ e
 // dense state) 55 us instead of ~300 us.  30 qubits (6435 rows of 6435): 13.5
 // ms instead of 11.7 ms and a beta GEMM of 8.0 ms.  (The purely alpha part
 // could run the same way on the rows of C^T: 9.7 ms there against the GEMM's
-// 8.0 ms, ~60 against 39 us at 24 qubits, so it stays a GEMM.)  28 qubits, energy alone: 1.2 ms
-// instead of 7.4 ms.
+// 8.0 ms, ~60 against 39 us at 24 qubits, so it stays a GEMM.)  28 qubits,
+// energy alone: 1.2 ms instead of 7.4 ms.
 // The LDS slot after the row (2 ceil(ncols / 2)) holds zero: the partner of a
 // string outside the pair's reach.
 constexpr int kRowR = 8;
