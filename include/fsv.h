@@ -148,10 +148,11 @@ int fsv_plan_set_engine(fsv_plan *plan, int engine);
  *  - the whole sweep in one workgroup that keeps the state in LDS (the default
  *    for sector states of at most 8192 amplitudes): one run;
  *  - component packets (the default for larger sector states of at most 2^22
- *    amplitudes, FSV_FUSE=packets for smaller ones; FSV_FUSE=packets also requests them up to 2^26, where every run
- *    becomes a packet run: at 30 qubits an evaluation takes 71 instead of
- *    83 ms, but planning takes ~3 minutes and the programs 13 GB of device
- *    memory; FSV_VERBOSE prints a line per planned run): the connected components of the graph joining the amplitudes
+ *    amplitudes, FSV_FUSE=packets for smaller ones; FSV_FUSE=packets also
+ *    requests them up to 2^26, where every run becomes a packet run: at 30
+ *    qubits that took 11 ms off an evaluation, but planning takes ~3 minutes
+ *    and the programs 13 GB of device memory; FSV_VERBOSE prints a line per
+ *    planned run): the connected components of the graph joining the amplitudes
  *    that some operator of the run pairs are mutually independent; runs are
  *    extended while every component has at most 256 amplitudes, and whole
  *    components are packed into 256-amplitude packets, one wavefront each;
