@@ -289,7 +289,8 @@ __global__ __launch_bounds__(kWave) void k_pkt(T *__restrict__ psi, typename Slo
 // rotation positive, and two flags for the last step of an operator in either
 // sweep order; equal slots: no pair) is loaded 16 steps ahead.  An operator
 // with more pairs than threads takes several steps, without barriers between
-// them: its pairs are disjoint.  Bound by each step's chain of LDS read,
+// them: its pairs are disjoint.  One without pairs in the sector has no step
+// (a sweep of only such operators: the initial state, no gradient terms).  Bound by each step's chain of LDS read,
 // rotation, LDS write and barrier, 0.4 us adjoint and 0.25 us forward.  16
 // qubits, 360 operators: 163 + 106 us instead of 24 runs' 163 + 121 us;
 // evaluations of shorter sequences, whose runs are shorter too, gain more (100
@@ -334,7 +335,7 @@ __global__ __launch_bounds__(kWholeThreads) void k_whole(T *__restrict__ psi, co
         return a.cs[2 * steps[step_at(i)].x + (t & 1)];
     };
     load(0, w);
-    if (t < 2 * kWholeSteps) scs[t] = angle(0);
+    if (nblk > 0 && t < 2 * kWholeSteps) scs[t] = angle(0);
     if (ADJ) {
         for (int i = t; i < a.dim; i += bs) tv[i] = z[i];
     } else {
@@ -1246,6 +1247,7 @@ int build_whole(int64_t nsa, int64_t nsb, const std::vector<PairOp> &pops, const
             return true;
         });
         if (!good) return fail(FSV_EINVAL, "internal: pairs of operator %d", k);
+        if (pairs.empty()) continue;  // moves nothing in this sector: no step, no gradient term
         const int ns = (int)((pairs.size() + bs - 1) / bs);
         const size_t w0 = words.size();
         words.insert(words.end(), pairs.begin(), pairs.end());

@@ -185,3 +185,41 @@ def test_whole_sweeps(fsv, m, na, nb, k, precision, monkeypatch):
             assert abs(e - e2) < 1e-12 and np.abs(g - g2).max() < 1e-11
             if not warm:
                 assert abs(e - e_ref) < tol_e and np.abs(g - g_ref).max() < tol_g
+
+
+# operators without a pair in the sector (an alpha-alpha double on one alpha
+# electron): first, in the middle, behind whole blocks of 16 steps, last, two in
+# a row, and nothing else
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("before,empty,after", [(0, 1, 3), (2, 1, 2), (4, 2, 1), (3, 1, 0), (16, 1, 17), (0, 1, 0), (0, 3, 0)])
+def test_whole_sweeps_without_pairs(fsv, before, empty, after, precision):
+    import dataclasses
+    from workloads import uccsd_pool
+    from tests.gpu_helpers import random_dets
+    m, na, nb = 4, 1, 1
+    p = _problem(m, na, nb, 0, seed=541)
+    pool = uccsd_pool(m, na, nb)
+    rng = np.random.default_rng(before + 31 * after)
+    some = pool[rng.integers(0, len(pool), before + after)].reshape(-1, 4)
+    ops = np.concatenate([some[:before], np.tile([[4, 6, 2, 0]], (empty, 1)), some[before:]]).astype(np.int32)
+    k = len(ops)
+    p = dataclasses.replace(p, ops=np.ascontiguousarray(ops), theta=rng.normal(0, 0.3, k))
+    say("whole sweeps without pairs", before, empty, after, precision)
+    plan = fsv.Plan(p, precision=precision)
+    assert all((r == 0).all() and (t == 1).all() for r, t in (plan.runs(), plan.runs(adjoint=True)))
+    e_ref, g_ref = oracle_energy_grad(p)
+    tol_e, tol_g = (1e-10, 1e-9) if precision == 0 else (1e-4, 1e-4)
+    for _ in range(2):
+        e, g = plan.energy_grad(p.theta)
+        assert abs(e - e_ref) < tol_e and np.abs(g - g_ref).max() < tol_g
+        assert (g[before:before + empty] == 0.0).all()
+    dets, coef = random_dets(p, 5, seed=k)
+    plan.set_initial_state(dets, coef)
+    e, g = plan.energy_grad(p.theta)
+    keep = np.r_[:before, before + empty:k]
+    ref = fsv.Plan(dataclasses.replace(p, ops=np.ascontiguousarray(ops[keep]), theta=p.theta[keep]), precision=precision)
+    ref.set_initial_state(dets, coef)
+    # the same rotations and sums: the operators left out change no amplitude
+    e2, g2 = ref.energy_grad(p.theta[keep])
+    assert abs(e - e2) < 1e-12 and np.abs(g[keep] - g2).max(initial=0.0) < 1e-11
+    assert (g[before:before + empty] == 0.0).all()

@@ -115,3 +115,11 @@ def test_kernels_on_cpu_energy_c2(kexec):
     # captured graphs, replayed
     out = _gpu_tests_on_cpu(kexec, "tests/test_gpu_parity.py::test_energy_small_configs[0-C2]")
     assert "1 passed" in out
+
+
+def test_kernels_on_cpu_whole_sweeps_without_pairs(kexec):
+    # operators without a pair in the sector used to be written past the end of
+    # the program of a whole sweep, and a sweep of only such operators read a
+    # step that does not exist
+    out = _gpu_tests_on_cpu(kexec, "tests/test_gpu_products.py::test_whole_sweeps_without_pairs")
+    assert "14 passed" in out
