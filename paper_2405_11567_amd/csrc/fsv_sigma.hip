@@ -9,6 +9,7 @@
 
 #include <rocblas/rocblas.h>
 
+#include <algorithm>
 #include <cstdlib>
 #include <vector>
 
@@ -1733,10 +1734,11 @@ hipError_t launch_pool(int vtype, const void *psi, const void *lam, const PairOp
 
 int pool_rows_u(int vtype, int64_t nsb) {
     // row pairs per workgroup: two workgroups of 512 threads per CU while the
-    // rows allow it, at least one row pair in a CU's LDS
+    // rows allow it, at least one row pair in a CU's LDS (or in the 64 KiB that
+    // are left where a larger block is refused)
     const int64_t per = 4 * nsb * vtype_bytes(vtype), lim = g_lds_max >= 163840 ? 163328 : 65024;
     if ((vtype != V_F64 && vtype != V_F32) || per > lim) return 0;
-    int64_t u = 81664 / per;
+    int64_t u = std::min<int64_t>(81664, lim) / per;
     return (int)(u < 1 ? 1 : (u > kPoolU ? kPoolU : u));
 }
 

@@ -561,6 +561,10 @@ hipError_t hipFuncSetAttribute(const void *fn, hipFuncAttribute attr, int value)
     auto it = find_kernel(fn, "hipFuncSetAttribute");
     if (attr == hipFuncAttributeMaxDynamicSharedMemorySize) {
         if (value < 0 || value > 163840) return hipErrorInvalidValue;
+        // kernels whose (mangled) name contains FSV_STUB_LDS_REFUSE keep the
+        // 64 KiB that every kernel may use
+        const char *refuse = std::getenv("FSV_STUB_LDS_REFUSE");
+        if (refuse && value > 65536 && it->second.name.find(refuse) != std::string::npos) return hipErrorInvalidValue;
         it->second.max_dyn = value;
     }
     return hipSuccess;

@@ -400,8 +400,42 @@ def suite_placement():
     exercise_plan(p, stages=False, extras=False)
 
 
+def exercise_pool(p, precision=0):
+    plan = make_plan(p, precision)
+    sb = lib.fsv_state_bytes(plan)
+    psi, lam = Dev(sb), Dev(sb)
+    ops = np.ascontiguousarray(uccsd_pool(p.n_orb, p.n_alpha, p.n_beta)[:200], dtype=np.int32)
+    q = vp()
+    ok(lib.fsv_pool_create(ctypes.byref(q), plan, ops.ctypes.data_as(I32), len(ops), 0), "pool")
+    th = np.ascontiguousarray(p.theta)
+    e, g = ctypes.c_double(), np.zeros(len(ops))
+    ok(lib.fsv_pool_gradients(q, dp(th), psi.p, lam.p, ctypes.byref(e), dp(g)), "pool grads")
+    ok(lib.fsv_pool_destroy(q), "pool destroy")
+    psi.free()
+    lam.free()
+    ok(lib.fsv_plan_destroy(plan), "destroy")
+
+
+def electrons(n, na, nb, k, seed):
+    # na differs from nb: operators are drawn again for the actual counts
+    p = random_problem(n, 2 * nb, k, seed=seed, theta_std=0.3, replace=True)
+    pool = uccsd_pool(n // 2, na, nb)
+    p.n_alpha, p.n_beta = na, nb
+    p.ops = np.ascontiguousarray(pool[np.random.default_rng(seed).integers(0, len(pool), k)])
+    return p
+
+
+def suite_pools_short_lds():
+    # 64 KiB of dynamic LDS only (FSV_STUB_LDS_REFUSE): rows of 210, 792, 924
+    # and 1287 columns, whose row pairs would fill up to 80 KB of a larger one
+    for precision in (0, 1):
+        for n, na, nb in ((20, 2, 4), (24, 2, 5), (24, 1, 6), (26, 1, 5), (26, 1, 6)):
+            print("pool rows", n, na, nb, precision, flush=True)
+            exercise_pool(electrons(n, na, nb, 4, seed=n + nb), precision)
+
+
 SUITES = {"sigma": suite_sigma, "parity": suite_parity, "pools": suite_pools, "batch": suite_batch,
-          "c3": suite_c3, "placement": suite_placement}
+          "c3": suite_c3, "placement": suite_placement, "pools_short_lds": suite_pools_short_lds}
 
 if __name__ == "__main__":
     for name in sys.argv[1:]:

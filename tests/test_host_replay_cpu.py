@@ -38,8 +38,8 @@ def hostcheck():
     return rt_build.asan_runtime()
 
 
-def _replay(asan, *suites, timeout=900, busy_streams=False):
-    env = dict(os.environ)
+def _replay(asan, *suites, timeout=900, busy_streams=False, **stub_env):
+    env = dict(os.environ, **stub_env)
     if busy_streams:  # every stream query reports pending work, so the calls' fences run
         env["FSV_STUB_BUSY_STREAMS"] = "1"
     env["LD_PRELOAD"] = asan
@@ -80,6 +80,11 @@ def test_replay_with_busy_streams(hostcheck):
     # the calls skip their stream fences when a stream is idle; here no stream
     # is ever idle, so every fence's event record and wait are exercised
     _replay(hostcheck, "pools", "batch", busy_streams=True)
+
+
+def test_replay_pools_short_lds(hostcheck):
+    # where the larger LDS limit is refused, a pool's workgroups fit 64 KiB
+    _replay(hostcheck, "pools_short_lds", FSV_STUB_LDS_REFUSE="k_")
 
 
 @pytest.fixture(scope="module")
