@@ -546,7 +546,6 @@ void init_fused_kernels() {
         if (hipFuncGetAttributes(&fa, f) == hipSuccess) lim -= fa.sharedSizeBytes;
         (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lim);
     }
-    (void)init_whole_kernels(163328);
     (void)hipGetLastError();
 }
 

@@ -411,7 +411,6 @@ int build_whole(int64_t nsa, int64_t nsb, const std::vector<PairOp> &pops, const
                 FusedSched &S);
 hipError_t launch_whole(int vtype, bool adjoint, void *state, const FusedSched &S, const FGroup &g, const double *cs,
                         const WholeInit &in, double *gpart, int gstride, hipStream_t st);
-bool init_whole_kernels(int bytes);  // dynamic LDS the kernels may use
 void init_fused_kernels();
 size_t fused_lds_limit();
 // Forward (psi) or adjoint (psi, lam, gradient partials gpart[k * gstride + tile]).

@@ -1209,10 +1209,28 @@ int build_batch_packets(const std::vector<BatchPacketInst> &insts, const std::ve
     return FSV_OK;
 }
 
+namespace {
+
+// Dynamic LDS that k_whole may use, asked for once: a gfx950 CU's (a little
+// left for static LDS), or the 64 KiB of any kernel where that is refused.
+size_t whole_lds_limit() {
+    static const size_t lim = [] {
+        bool ok = true;
+        for (const void *f : {(const void *)k_whole<double, true>, (const void *)k_whole<double, false>,
+                              (const void *)k_whole<float, true>, (const void *)k_whole<float, false>})
+            ok = ok && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 163328) == hipSuccess;
+        (void)hipGetLastError();
+        return (size_t)(ok ? 163328 : 65536);
+    }();
+    return lim;
+}
+
+}  // namespace
+
 // 8192: FP64 at 7056 amplitudes takes 135 us instead of the packets' 150 us
 // (100 operators), FP32 at 15876 237 us instead of 172 us.
 int64_t whole_max_dim(int es) {
-    return std::min<int64_t>(8192, (int64_t)(fused_lds_limit() - 1024) / (2 * es));
+    return std::min<int64_t>(8192, (int64_t)(whole_lds_limit() - 1024) / (2 * es));
 }
 
 int build_whole(int64_t nsa, int64_t nsb, const std::vector<PairOp> &pops, const std::vector<uint32_t> &lists, int es,
@@ -1302,14 +1320,6 @@ hipError_t launch_whole(int vtype, bool adjoint, void *state, const FusedSched &
                        : whole_impl<double, false>(state, S, g, cs, in, gpart, gstride, st);
     return adjoint ? whole_impl<float, true>(state, S, g, cs, in, gpart, gstride, st)
                    : whole_impl<float, false>(state, S, g, cs, in, gpart, gstride, st);
-}
-
-bool init_whole_kernels(int bytes) {
-    bool ok = true;
-    for (const void *f : {(const void *)k_whole<double, true>, (const void *)k_whole<double, false>,
-                          (const void *)k_whole<float, true>, (const void *)k_whole<float, false>})
-        ok = ok && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, bytes) == hipSuccess;
-    return ok;
 }
 
 size_t batch_packet_lds(int wr, bool adjoint) {

@@ -434,8 +434,26 @@ def suite_pools_short_lds():
             exercise_pool(electrons(n, na, nb, 4, seed=n + nb), precision)
 
 
+def suite_whole_short_lds():
+    # 64 KiB of dynamic LDS for whole sweeps (FSV_STUB_LDS_REFUSE): states whose
+    # pairs fit it (400 and 3136 FP64, 7056 FP32 amplitudes) and one that does
+    # not (7056 FP64), which takes packet runs
+    for n, na, nb, precision, whole in ((12, 3, 3, 0, True), (16, 5, 5, 0, True), (18, 3, 3, 1, True),
+                                        (18, 3, 3, 0, False)):
+        p = electrons(n, na, nb, 20, seed=n)
+        print("whole sweeps", n, na, nb, precision, flush=True)
+        plan = make_plan(p, precision)
+        start = np.zeros(p.n_ops, np.int32)
+        runs = ok(lib.fsv_plan_runs(plan, 1, start.ctypes.data_as(I32), None), "runs")
+        if (runs == 1) != whole:
+            raise RuntimeError(f"{runs} runs")
+        ok(lib.fsv_plan_destroy(plan), "destroy")
+        exercise_plan(p, precision)
+
+
 SUITES = {"sigma": suite_sigma, "parity": suite_parity, "pools": suite_pools, "batch": suite_batch,
-          "c3": suite_c3, "placement": suite_placement, "pools_short_lds": suite_pools_short_lds}
+          "c3": suite_c3, "placement": suite_placement, "pools_short_lds": suite_pools_short_lds,
+          "whole_short_lds": suite_whole_short_lds}
 
 if __name__ == "__main__":
     for name in sys.argv[1:]:

@@ -87,6 +87,12 @@ def test_replay_pools_short_lds(hostcheck):
     _replay(hostcheck, "pools_short_lds", FSV_STUB_LDS_REFUSE="k_")
 
 
+def test_replay_whole_sweeps_short_lds(hostcheck):
+    # where the larger LDS limit is refused to whole sweeps alone, states that
+    # do not fit 64 KiB take packet runs
+    _replay(hostcheck, "whole_short_lds", FSV_STUB_LDS_REFUSE="k_whole")
+
+
 @pytest.fixture(scope="module")
 def kexec(hostcheck):
     import build as rt_build  # tests/cpu_runtime/build.py
