@@ -535,9 +535,6 @@ int fused_runs(const FusedSched &S, int *n_fused_ops) {
 }
 
 void init_fused_kernels() {
-    static bool done = false;
-    if (done) return;
-    done = true;
     const void *fns[] = {(const void *)k_fused<double, false>, (const void *)k_fused<double, true>,
                          (const void *)k_fused<float, false>, (const void *)k_fused<float, true>};
     for (const void *f : fns) {
@@ -552,7 +549,7 @@ void init_fused_kernels() {
 // Dynamic LDS every fused kernel accepts (their static LDS is the block_sum
 // scratch of the adjoint kernels).
 size_t fused_lds_limit() {
-    init_fused_kernels();
+    init_kernels();
     size_t lim = 163840;
     hipFuncAttributes fa;
     if (hipFuncGetAttributes(&fa, (const void *)k_fused<double, true>) == hipSuccess &&

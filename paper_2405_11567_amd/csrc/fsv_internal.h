@@ -274,7 +274,7 @@ hipError_t launch_plane_transpose(const double *in, double *out, int64_t rows, i
 // and its prefix parity).
 hipError_t launch_dense_image(int precision, int ordering, void *out, const double *S, const int32_t *ra,
                               const int2 *rb, int n, int na, int nb, int64_t nsb, hipStream_t st);
-void init_sigma_kernels();
+void init_sigma_kernels();  // by init_kernels only
 
 // ---- fused operator runs on the sector state (fsv_fused.hip, fsv_packet.hip) ----
 constexpr int kPacketAmps = 256;  // amplitudes (index slots) of one packet
@@ -411,7 +411,7 @@ int build_whole(int64_t nsa, int64_t nsb, const std::vector<PairOp> &pops, const
                 FusedSched &S);
 hipError_t launch_whole(int vtype, bool adjoint, void *state, const FusedSched &S, const FGroup &g, const double *cs,
                         const WholeInit &in, double *gpart, int gstride, hipStream_t st);
-void init_fused_kernels();
+void init_fused_kernels();  // by init_kernels only
 size_t fused_lds_limit();
 // Forward (psi) or adjoint (psi, lam, gradient partials gpart[k * gstride + tile]).
 // Packet groups are launched with launch_packets.

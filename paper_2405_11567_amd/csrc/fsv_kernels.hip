@@ -506,14 +506,20 @@ hipError_t adj_dispatch(void *psi, void *lam, const RotOp &op, const double *cs,
 int max_grid() { return kMaxGrid; }
 
 void init_kernels() {
-    init_sigma_kernels();
-    init_fused_kernels();
-    // the adjoint fused run stages psi and lam tiles: 128 KiB of dynamic LDS
-    (void)hipFuncSetAttribute((const void *)k_adj_fused<double, 12>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              2 * (1 << 12) * (int)sizeof(double2));
-    (void)hipFuncSetAttribute((const void *)k_adj_fused<float, 13>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                              2 * (1 << 13) * (int)sizeof(float2));
-    (void)hipGetLastError();
+    // a thread that builds a plan meanwhile waits until every limit is known:
+    // the plan's choice of kernels goes by them
+    static const bool once = [] {
+        init_sigma_kernels();
+        init_fused_kernels();
+        // the adjoint fused run stages psi and lam tiles: 128 KiB of dynamic LDS
+        (void)hipFuncSetAttribute((const void *)k_adj_fused<double, 12>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  2 * (1 << 12) * (int)sizeof(double2));
+        (void)hipFuncSetAttribute((const void *)k_adj_fused<float, 13>, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                  2 * (1 << 13) * (int)sizeof(float2));
+        (void)hipGetLastError();
+        return true;
+    }();
+    (void)once;
 }
 
 int max_fused_run() { return kMaxFusedRun; }

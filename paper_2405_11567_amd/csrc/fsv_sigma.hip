@@ -1615,8 +1615,6 @@ hipError_t convert_impl(const void *in, void *out, int64_t n, hipStream_t st) {
 }  // namespace
 
 void init_sigma_kernels() {
-    if (g_lds_max > 0) return;
-    g_lds_max = 65536;
     std::vector<const void *> fns = {(const void *)k_sigma_ab};
 #define FSV_ROW_FNS(BS, CP, LH, NC, NB, WV)                                \
     fns.push_back((const void *)k_row<BS, CP, LH, NC, NB, WV, ROW_ENERGY>); \
@@ -1637,7 +1635,7 @@ void init_sigma_kernels() {
     bool ok = true;
     for (const void *f : fns)
         ok = ok && hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, f == fns[0] ? 163840 : 163328) == hipSuccess;
-    if (ok) g_lds_max = 163840;  // a gfx950 CU's LDS
+    g_lds_max = ok ? 163840 : 65536;  // a gfx950 CU's LDS, or what any kernel may use
     (void)hipGetLastError();
 }
 

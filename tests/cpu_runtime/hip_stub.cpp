@@ -557,6 +557,9 @@ hipError_t hipExtLaunchKernel(const void *fn, dim3 g, dim3 b, void **, size_t sh
 }
 
 hipError_t hipFuncSetAttribute(const void *fn, hipFuncAttribute attr, int value) {
+    // FSV_STUB_SLOW_ATTRIBUTES: the time a real runtime takes to load the code
+    // object, so that threads meet in the library's first set-up
+    if (std::getenv("FSV_STUB_SLOW_ATTRIBUTES")) std::this_thread::sleep_for(std::chrono::milliseconds(20));
     std::lock_guard<std::mutex> lk(g_mu);
     auto it = find_kernel(fn, "hipFuncSetAttribute");
     if (attr == hipFuncAttributeMaxDynamicSharedMemorySize) {

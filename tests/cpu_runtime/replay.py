@@ -451,9 +451,34 @@ def suite_whole_short_lds():
         exercise_plan(p, precision)
 
 
+def suite_threads():
+    # the process's first plans made by several threads at once: the same tables
+    # as a plan made alone afterwards
+    import threading
+    p = electrons(24, 1, 5, 6, seed=77)  # rows of 792 columns
+    live0 = stub.hip_stub_live_device_bytes()
+    plans = [None] * 4
+
+    def make(i):
+        plans[i] = make_plan(p)
+
+    threads = [threading.Thread(target=make, args=(i,)) for i in range(len(plans))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    plans.append(make_plan(p))
+    sizes = [lib.fsv_plan_device_bytes(q) for q in plans]
+    print("threads", sizes, flush=True)
+    if len(set(sizes)) != 1 or stub.hip_stub_live_device_bytes() - live0 != sum(sizes):
+        raise RuntimeError("plans made at the same time differ")
+    for q in plans:
+        ok(lib.fsv_plan_destroy(q), "destroy")
+
+
 SUITES = {"sigma": suite_sigma, "parity": suite_parity, "pools": suite_pools, "batch": suite_batch,
           "c3": suite_c3, "placement": suite_placement, "pools_short_lds": suite_pools_short_lds,
-          "whole_short_lds": suite_whole_short_lds}
+          "whole_short_lds": suite_whole_short_lds, "threads": suite_threads}
 
 if __name__ == "__main__":
     for name in sys.argv[1:]:

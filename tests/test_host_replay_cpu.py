@@ -93,6 +93,11 @@ def test_replay_whole_sweeps_short_lds(hostcheck):
     _replay(hostcheck, "whole_short_lds", FSV_STUB_LDS_REFUSE="k_whole")
 
 
+def test_replay_first_plans_of_several_threads(hostcheck):
+    # no plan is built before the kernels' limits are known
+    _replay(hostcheck, "threads", FSV_STUB_SLOW_ATTRIBUTES="1")
+
+
 @pytest.fixture(scope="module")
 def kexec(hostcheck):
     import build as rt_build  # tests/cpu_runtime/build.py
