@@ -223,3 +223,30 @@ def test_whole_sweeps_without_pairs(fsv, before, empty, after, precision):
     e2, g2 = ref.energy_grad(p.theta[keep])
     assert abs(e - e2) < 1e-12 and np.abs(g[keep] - g2).max(initial=0.0) < 1e-11
     assert (g[before:before + empty] == 0.0).all()
+
+
+# rows of 5005 columns (30 qubits): the longest launch shape of general integrals,
+# and factorised ones
+@pytest.mark.parametrize("rank", [20, 0])
+def test_long_rows(fsv, rank):
+    p = _problem(15, 1, 6, rank, seed=931)
+    say("long rows", rank)
+    e, g = fsv.Plan(p).energy_grad(p.theta)
+    e_ref, g_ref = oracle_energy_grad(p)
+    assert abs(e - e_ref) < 1e-10 and np.abs(g - g_ref).max() < 1e-9
+
+
+# screening with three, two and one row pair per workgroup, in both precisions,
+# with a remainder of row pairs: FP64 rows of 792 and 1287 columns, FP32 rows of
+# 1287, 1716 and 3003
+@pytest.mark.parametrize("m,na,nb,precision", [(12, 2, 5, 0), (13, 2, 5, 0), (13, 2, 5, 1), (13, 2, 6, 1), (14, 1, 6, 1)])
+def test_pool_long_rows(fsv, m, na, nb, precision):
+    from workloads import uccsd_pool
+    p = _problem(m, na, nb, 0, seed=700 + 11 * m + nb)
+    full = np.asarray(uccsd_pool(m, na, nb), dtype=np.int32)
+    ops = np.ascontiguousarray(full[np.random.default_rng(m).permutation(len(full))[:40]])
+    say("pool long rows", m, na, nb, precision)
+    psi = sector.ansatz(m, na, nb, p.ops, p.theta, p.ordering, p.excitation)
+    want = sector.pool_gradients(psi, p.h, p.g, p.e_core, ops, na, nb, p.ordering, 0)
+    _, g = fsv.Plan(p, precision=precision).pool(ops).gradients(p.theta)
+    assert np.abs(g - want).max() < (1e-9 if precision == 0 else 1e-4)  # as test_pool_rows
