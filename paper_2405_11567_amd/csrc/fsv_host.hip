@@ -193,7 +193,7 @@ struct fsv_plan {
     // dense same-spin string Hamiltonians (FP64 GEMM on the matrix cores)
     rocblas_handle blas = nullptr;
     double *d_ha_dense = nullptr, *d_hb_dense = nullptr, *d_hb_dense_t = nullptr;
-    // row kernels: h' and the one-body tables made from it
+    // row kernels: h' (behind d_htilde) and the one-body tables made from it
     double *d_heff = nullptr, *d_hp = nullptr, *d_hda = nullptr, *d_hdb = nullptr;
     bool need_hb = true;  // whether a product uses the beta string Hamiltonian
     int32_t *d_im_flag = nullptr, im_epoch = 0;  // whether the last gathered state had imaginary parts
@@ -800,43 +800,50 @@ bool want_dense_same_spin(const fsv_plan &P) {
     return nnz_a * 16.0 > (double)P.nsa && (!P.need_hb || nnz_b * 16.0 > (double)P.nsb);
 }
 
-// The one-body tables of the row kernels from h + v: h'_pq = (h + v)_pq -
-// 1/2 sum_r (pr|rq).
-int upload_row_onebody(fsv_plan &P, const std::vector<double> &ht) {
-    if (!P.d_heff) return FSV_OK;
+// h + v (d_htilde) and, behind it, the one-body part of the row kernels (d_heff),
+// h'_pq = (h + v)_pq - 1/2 sum_r (pr|rq), in one copy.
+int upload_onebody(fsv_plan &P) {
     const int M = P.M, M2 = M * M, M3 = M2 * M;
-    std::vector<double> he(ht);
-    for (int p = 0; p < M; ++p)
-        for (int q = 0; q < M; ++q) {
-            double x = 0.0;
-            for (int r = 0; r < M; ++r) x += P.g[(size_t)p * M3 + r * M2 + r * M + q];
-            he[p * M + q] -= 0.5 * x;
-        }
-    const int rc = upload(P, P.d_heff, he.data(), he.size());
-    if (rc) return rc;
-    HIPCHECK(launch_row_onebody(P.d_heff, M, P.d_str_a, P.nsa, P.d_str_b, P.nsb, P.d_hp, P.d_hda, P.d_hdb, P.work));
+    std::vector<double> ht(P.h);
+    for (int i = 0; i < M2; ++i) ht[i] += P.v[i];
+    if (P.d_heff) {
+        ht.resize(2 * (size_t)M2);
+        for (int p = 0; p < M; ++p)
+            for (int q = 0; q < M; ++q) {
+                double x = 0.0;
+                for (int r = 0; r < M; ++r) x += P.g[(size_t)p * M3 + r * M2 + r * M + q];
+                ht[M2 + p * M + q] = ht[p * M + q] - 0.5 * x;
+            }
+    }
+    return upload(P, P.d_htilde, ht.data(), ht.size());
+}
+
+// The row kernels' one-body values from h'.
+int refresh_row_onebody(fsv_plan &P) {
+    if (P.d_heff)
+        HIPCHECK(launch_row_onebody(P.d_heff, P.M, P.d_str_a, P.nsa, P.d_str_b, P.nsb, P.d_hp, P.d_hda, P.d_hdb,
+                                    P.work));
     return FSV_OK;
 }
 
-// New one-body potential: h + v goes up (M^2 doubles) and the tables made
-// from it are rebuilt on the device: the string Hamiltonian values (and their
+// New one-body potential: h + v and h' go up (2 M^2 doubles) and the tables made
+// from them are rebuilt on the device: the string Hamiltonian values (and their
 // dense copies) from the fixed two-body parts and the one-body descriptors,
-// and the row kernels' one-body values.
+// and the row kernels' one-body values.  One copy: a second one, after the
+// first tables' launches, would wait for them (10 us of a call of 75 us).
 int upload_hamiltonian_values(fsv_plan &P) {
-    std::vector<double> ht(P.h);
-    for (size_t i = 0; i < ht.size(); ++i) ht[i] += P.v[i];
     // earlier work on the stream (a previous refresh reading h + v, or
     // products using the old values) completes before h + v is overwritten
     HIPCHECK(hipStreamSynchronize(P.work));
     int rc;
-    if ((rc = upload(P, P.d_htilde, ht.data(), ht.size()))) return rc;
+    if ((rc = upload_onebody(P))) return rc;
     HIPCHECK(launch_string_h_values(P.d_ha_val, P.d_ha_v2, P.d_ha_desc, P.d_str_a, P.d_htilde, P.M,
                                     (int64_t)P.ha_col.size(), P.work));
     if (P.need_hb)
         HIPCHECK(launch_string_h_values(P.d_hb_val, P.d_hb_v2, P.d_hb_desc, P.d_str_b, P.d_htilde, P.M,
                                         (int64_t)P.hb_col.size(), P.work));
     if ((rc = refresh_dense_same_spin(P))) return rc;
-    return upload_row_onebody(P, ht);
+    return refresh_row_onebody(P);
 }
 
 // Byte model of one pair kernel (read + write of the touched 128-byte lines).
@@ -1633,7 +1640,7 @@ int build_device(fsv_plan &P) {
         };
         if ((rc = part(P.sa, ra, P.ha_val.size(), &P.d_ha_v2, &P.d_ha_desc)) ||
             (P.need_hb && (rc = part(P.sb, rb, P.hb_val.size(), &P.d_hb_v2, &P.d_hb_desc))) ||
-            (rc = dalloc(P, &P.d_htilde, (size_t)M * M)))
+            (rc = dalloc(P, &P.d_htilde, 2 * M2)))
             return rc;
     }
     auto put = [&](const auto &v, auto **d) -> int {
@@ -1667,9 +1674,9 @@ int build_device(fsv_plan &P) {
         if ((rc = put(Lt, &d_Lt)) || (rc = put(Lp, &d_Lp)) || (rc = put(da, &d_lda)) ||
             (rc = put(by_factor(db, db.size() / rp), &d_ldb)))
             return rc;
-        if ((rc = dalloc(P, &P.d_heff, M2)) || (rc = dalloc(P, &P.d_hp, (size_t)npair)) ||
-            (rc = dalloc(P, &P.d_hda, P.nsa + 1)) || (rc = dalloc(P, &P.d_hdb, P.nsb + 1)) ||
-            (rc = upload_row_onebody(P, ht)))
+        P.d_heff = P.d_htilde + M2;
+        if ((rc = dalloc(P, &P.d_hp, (size_t)npair)) || (rc = dalloc(P, &P.d_hda, P.nsa + 1)) ||
+            (rc = dalloc(P, &P.d_hdb, P.nsb + 1)) || (rc = upload_onebody(P)) || (rc = refresh_row_onebody(P)))
             return rc;
     }
     if (direct_rows) {

@@ -102,7 +102,7 @@ std::map<hipGraph_t, std::vector<Node> *> &graphs() { static std::map<hipGraph_t
 std::map<hipGraphExec_t, std::vector<Node> *> &execs() { static std::map<hipGraphExec_t, std::vector<Node> *> m; return m; }
 std::set<void *> &blas_handles() { static std::set<void *> s; return s; }
 
-unsigned long g_launches = 0, g_replays = 0;
+unsigned long g_launches = 0, g_replays = 0, g_copies = 0;
 bool g_exec = false;  // kernel-executing build loaded
 
 std::string demangle(const char *s) {
@@ -165,6 +165,7 @@ void check_copy(void *dst, const void *src, size_t n, hipMemcpyKind k, const cha
 
 void do_copy(void *dst, const void *src, size_t n, hipMemcpyKind k, const char *what) {
     check_copy(dst, src, n, k, what);
+    ++g_copies;
     if (n) std::memmove(dst, src, n);
 }
 
@@ -816,6 +817,7 @@ hipError_t hipGraphLaunch(hipGraphExec_t ex, hipStream_t s) {
 // ---- test hooks ----
 unsigned long hip_stub_launches(void) { return g_launches; }
 unsigned long hip_stub_replays(void) { return g_replays; }
+unsigned long hip_stub_copies(void) { return g_copies; }
 size_t hip_stub_live_device_bytes(void) {
     std::lock_guard<std::mutex> lk(g_mu);
     size_t t = 0;

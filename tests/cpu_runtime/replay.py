@@ -37,6 +37,7 @@ stub.hipMalloc.argtypes = [ctypes.POINTER(vp), ctypes.c_size_t]
 stub.hipFree.argtypes = [vp]
 stub.hip_stub_launches.restype = ctypes.c_ulong
 stub.hip_stub_replays.restype = ctypes.c_ulong
+stub.hip_stub_copies.restype = ctypes.c_ulong
 stub.hip_stub_live_device_bytes.restype = ctypes.c_size_t
 stub.hip_stub_live_handles.restype = ctypes.c_size_t
 lib.fsv_last_error.restype = ctypes.c_char_p
@@ -476,9 +477,34 @@ def suite_threads():
         ok(lib.fsv_plan_destroy(q), "destroy")
 
 
+def suite_potential():
+    # a new one-body potential goes up in one copy (a second one would wait for
+    # the launches between them), for factorised and for general integrals
+    for general in (False, True):
+        p = random_problem(16, 8, 10, seed=88, theta_std=0.3, replace=True)
+        if general:
+            p.g = general_integrals(p.n_orb)
+        plan = make_plan(p)
+        for v in (np.ascontiguousarray(potential_v0(p.n_orb, seed=12)), None):
+            before = stub.hip_stub_copies()
+            ok(lib.set_onebody_potential(plan, dp(v) if v is not None else None), "potential")
+            n = stub.hip_stub_copies() - before
+            print("potential", general, n, flush=True)
+            if n != 1:
+                raise RuntimeError(f"{n} copies")
+        ok(lib.fsv_plan_destroy(plan), "destroy")
+
+
+def general_integrals(m):
+    f = np.random.default_rng(m).normal(0, 0.05, (m * m, m, m))
+    f = (f + f.transpose(0, 2, 1)).reshape(m * m, m * m)
+    return (f.T @ f).reshape(m, m, m, m)
+
+
 SUITES = {"sigma": suite_sigma, "parity": suite_parity, "pools": suite_pools, "batch": suite_batch,
           "c3": suite_c3, "placement": suite_placement, "pools_short_lds": suite_pools_short_lds,
-          "whole_short_lds": suite_whole_short_lds, "threads": suite_threads}
+          "whole_short_lds": suite_whole_short_lds, "threads": suite_threads,
+          "potential": suite_potential}
 
 if __name__ == "__main__":
     for name in sys.argv[1:]:

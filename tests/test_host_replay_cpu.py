@@ -98,6 +98,10 @@ def test_replay_first_plans_of_several_threads(hostcheck):
     _replay(hostcheck, "threads", FSV_STUB_SLOW_ATTRIBUTES="1")
 
 
+def test_replay_potential_copies(hostcheck):
+    _replay(hostcheck, "potential")
+
+
 @pytest.fixture(scope="module")
 def kexec(hostcheck):
     import build as rt_build  # tests/cpu_runtime/build.py
