@@ -375,7 +375,10 @@ __global__ void k_scatter(typename C2<R>::T *__restrict__ lam, const double *__r
 // sources at a time, which share the reads of row I.  Bound by the latency of
 // the row reads from L2: 2 x 29 us at 24 qubits for a real state, where one
 // wavefront per (I, e) reading both planes took 2 x 80 us (256 threads: 36 us,
-// two sources at a time: 35 us, the column loop unrolled by 8: 37 us).
+// two sources at a time: 35 us, the column loop unrolled by 8: 37 us).  Small
+// states are all latency, so the row's list is made by one wavefront's ballot
+// (a serial count per entry and a second barrier cost a call 2.5 us at 8 qubits,
+// 8 us at 24).
 constexpr int kRdmRows = 3;
 
 __global__ __launch_bounds__(512) void k_rdm_overlap(const double *__restrict__ A, int64_t ncols,
@@ -391,15 +394,17 @@ __global__ __launch_bounds__(512) void k_rdm_overlap(const double *__restrict__ 
         const uint32_t J = w & 0xFFFFu;
         return J != I && (I < J) == (((I ^ J) & 1u) == 0u);
     };
-    for (int e = tid; e < nexc; e += blockDim.x) words[e] = exc[(int64_t)I * nexc + e];
-    __syncthreads();
-    for (int e = tid; e < nexc; e += blockDim.x) {
+    if (wid == 0) {
         uint32_t at = 0;
-#pragma unroll 8
-        for (int k = 0; k < e; ++k) at += taken(words[k]) ? 1u : 0u;
-        const bool t = taken(words[e]);
-        if (t) mine[at] = (uint32_t)e;
-        if (e == nexc - 1) *count = at + (t ? 1u : 0u);
+        for (int e0 = 0; e0 < nexc; e0 += kWave) {
+            const int e = e0 + lane;
+            const uint32_t w = e < nexc ? exc[(int64_t)I * nexc + e] : I;
+            const uint64_t m = __ballot(taken(w));
+            if (e < nexc) words[e] = w;
+            if (taken(w)) mine[at + popc((uint64_t)(m & ((1ull << lane) - 1ull)))] = (uint32_t)e;
+            at += (uint32_t)popc(m);
+        }
+        if (lane == 0) *count = at;
     }
     __syncthreads();
     const double *a = A + 2 * (int64_t)I * ncols;
@@ -446,8 +451,16 @@ __global__ __launch_bounds__(512) void k_rdm_overlap(const double *__restrict__ 
             }
         }
 #pragma unroll
+        for (int off = kWave / 2; off > 0; off >>= 1) {  // wave_sum of all of them, their exchanges in flight together
+#pragma unroll
+            for (int u = 0; u < kRdmRows; ++u) re[u] += __shfl_xor(re[u], off, kWave);
+            if (cplx)
+#pragma unroll
+                for (int u = 0; u < kRdmRows; ++u) im[u] += __shfl_xor(im[u], off, kWave);
+        }
+#pragma unroll
         for (int u = 0; u < kRdmRows; ++u) {
-            const double x = wave_sum(re[u]), y = cplx ? wave_sum(im[u]) : 0.0;
+            const double x = re[u], y = im[u];
             if (g * kRdmRows + u >= n) continue;
             if (lane == 0) O[(int64_t)I * nexc + e[u]] = w[u] >> 31 ? make_double2(-x, -y) : make_double2(x, y);
             const int64_t J = w[u] & 0xFFFFu;

@@ -64,6 +64,12 @@ inline T __shfl_xor(T v, int mask, int width = 64) {
     return out;
 }
 
+inline unsigned long long __ballot(int p) {
+    unsigned long long v = p ? 1ull << fsv_cpu_lane() : 0ull;
+    for (int off = 1; off < 64; off <<= 1) v |= __shfl_xor(v, off);
+    return v;
+}
+
 // DPP lane move of a 32-bit value (quad permutations, row shifts, mirrors and
 // broadcasts); lanes whose source is invalid or whose row is masked off get old.
 inline int fsv_cpu_update_dpp(int old, int src, int ctrl, int row_mask, int bank_mask, bool bound_ctrl) {
