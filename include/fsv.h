@@ -293,7 +293,10 @@ int onebody_expectation(fsv_plan *plan, const void *psi_dev, const double *d, do
  * derivative is <psi| [H, T] |psi> = 2 Re <H psi| T |psi>, psi = psi(theta).
  * fsv_pool_create compiles a pool for a plan (which must use the sector
  * engine): ops is host, n_ops x 4 {a, b, j, i} in the plan's conventions,
- * excitation 0 fermionic / 1 qubit (as in fsv_problem).  Pools and plans may
+ * excitation 0 fermionic / 1 qubit (as in fsv_problem).  A pool is screened
+ * by staged rows shared between its operators or pair by pair, whichever a
+ * model of both expects to be faster (FSV_POOL=rows | pairs at creation asks
+ * for one of them).  Pools and plans may
  * be destroyed in either order: a pool whose plan is gone can still be
  * destroyed, and fsv_pool_gradients on it returns FSV_ESTATE.
  * Errors: FSV_EINVAL for an invalid operator, FSV_ESTATE for a dense-engine

@@ -2505,31 +2505,35 @@ int fsv_pool_create(fsv_pool **out, fsv_plan *P, const int32_t *ops, int32_t n_o
         }
         return FSV_OK;
     };
-    Q->U = pool_rows_u(P->svt, P->nsb);
-    if (Q->U > 0) {
-        // groups of the operators that move the same alpha electrons
-        std::map<uint64_t, int> of;
-        std::vector<std::vector<int32_t>> gen, plain;
-        std::vector<PoolGroup> groups;
-        for (int t = 0; t < n_ops; ++t) {
-            uint64_t ann = 0, cre = 0;
-            bool beta = false;
-            for (int x = 0; x < 4; ++x) {
-                const int so = ops[4 * t + x];
-                if (so >= 0 && so % 2 == 0) (x < 2 ? cre : ann) |= 1ull << (so / 2);
-                beta = beta || (so >= 0 && so % 2 == 1);
-            }
-            const auto in = of.emplace(ann << 32 | cre, (int)groups.size());
-            if (in.second) {
-                PoolGroup g{};
-                g.offA = (ann | cre) ? pops[t].offA : -1;
-                g.nA = (ann | cre) ? pops[t].nA : (int32_t)P->nsa;
-                groups.push_back(g);
-                gen.emplace_back();
-                plain.emplace_back();
-            }
-            (beta ? gen : plain)[in.first->second].push_back(t);
+    // groups of the operators that move the same alpha electrons
+    std::map<uint64_t, int> of;
+    std::vector<std::vector<int32_t>> gen, plain;
+    std::vector<PoolGroup> groups;
+    for (int t = 0; t < n_ops; ++t) {
+        uint64_t ann = 0, cre = 0;
+        bool beta = false;
+        for (int x = 0; x < 4; ++x) {
+            const int so = ops[4 * t + x];
+            if (so >= 0 && so % 2 == 0) (x < 2 ? cre : ann) |= 1ull << (so / 2);
+            beta = beta || (so >= 0 && so % 2 == 1);
         }
+        const auto in = of.emplace(ann << 32 | cre, (int)groups.size());
+        if (in.second) {
+            PoolGroup g{};
+            g.offA = (ann | cre) ? pops[t].offA : -1;
+            g.nA = (ann | cre) ? pops[t].nA : (int32_t)P->nsa;
+            groups.push_back(g);
+            gen.emplace_back();
+            plain.emplace_back();
+        }
+        (beta ? gen : plain)[in.first->second].push_back(t);
+    }
+    double pairs = 0.0, rows = 0.0;
+    for (const PairOp &o : pops)
+        pairs += (double)(o.nA >= 0 ? o.nA : P->nsa) * (double)(o.nB >= 0 ? o.nB : P->nsb);
+    for (const PoolGroup &g : groups) rows += (double)g.nA;
+    Q->U = pool_rows_u(P->svt, P->nsa, P->nsb, pairs, rows);
+    if (Q->U > 0) {
         std::vector<int32_t> gops;
         std::vector<int2> tasks;
         std::vector<int64_t> off(n_ops + 1, 0);
@@ -2616,11 +2620,9 @@ int fsv_pool_gradients(fsv_pool *Q, const double *theta, void *psi, void *lam, d
         int r;
         if ((r = enq_forward(P, psi))) return r;
         if ((r = enq_sigma(P, psi, lam))) return r;
-        if (Q->U > 0 && Q->n_gen + Q->n_plain > 0) {
+        if (Q->U > 0) {
             HIPCHECK(launch_pool_rows(P.svt, psi, lam, Q->d_ops, Q->d_lists, Q->d_groups, Q->d_gops, Q->d_tasks,
                                       Q->n_gen, Q->n_plain, Q->U, P.nsb, Q->d_off, Q->d_part, Q->n, Q->d_out, P.work));
-        } else if (Q->U > 0) {  // no operator moves any pair of this sector
-            HIPCHECK(launch_fill_zero(Q->d_out, sizeof(double) * (size_t)Q->n, P.work));
         } else {
             HIPCHECK(launch_pool(P.svt, psi, lam, Q->d_ops, Q->d_lists, Q->n, Q->gx, P.nsa, P.nsb, Q->d_part, P.work));
             HIPCHECK(launch_reduce_rows(Q->d_part, Q->d_counts, Q->gx, Q->n, 2.0, Q->d_out, P.work));

@@ -251,7 +251,9 @@ struct PoolGroup {
     int32_t op0, ngen, nplain, nA, parts, pad;
     int64_t offA;
 };
-int pool_rows_u(int vtype, int64_t nsb);  // 0: rows too long
+// U for a pool of so many amplitude pairs in all its operators and row pairs in all
+// its groups; 0: the pool is screened operator by operator (launch_pool).
+int pool_rows_u(int vtype, int64_t nsa, int64_t nsb, double pairs, double rows);
 hipError_t launch_pool_rows(int vtype, const void *psi, const void *lam, const PairOp *ops, const uint32_t *lists,
                             const PoolGroup *groups, const int32_t *gops, const int2 *tasks, int n_gen, int n_plain,
                             int U, int64_t nsb, const int64_t *off, double *partial, int n_ops, double *out,

@@ -11,6 +11,7 @@
 
 #include <algorithm>
 #include <cstdlib>
+#include <cstring>
 #include <vector>
 
 #include "fsv_device.h"
@@ -1730,12 +1731,29 @@ hipError_t launch_pool(int vtype, const void *psi, const void *lam, const PairOp
     return hipGetLastError();
 }
 
-int pool_rows_u(int vtype, int64_t nsb) {
+int pool_rows_u(int vtype, int64_t nsa, int64_t nsb, double pairs, double rows) {
     // row pairs per workgroup: two workgroups of 512 threads per CU while the
     // rows allow it, at least one row pair in a CU's LDS (or in the 64 KiB that
     // are left where a larger block is refused)
     const int64_t per = 4 * nsb * vtype_bytes(vtype), lim = g_lds_max >= 163840 ? 163328 : 65024;
     if ((vtype != V_F64 && vtype != V_F32) || per > lim) return 0;
+    // k_pool_rows reads whole rows once per group, k_pool the pairs of every
+    // operator.  Times in us, bytes / 1e6 per us = TB/s, fitted to pools of 5 to
+    // 1818 operators at 16 to 30 qubits.  k_pool: 10 TB/s while psi and lam fit
+    // one XCD's L2 (4 MB; 22 qubits, 400 operators: 20 us, rows 28), 4.9 while
+    // they fit all eight (24 qubits, 50 / 200 / 400 / 1818 operators: 13 / 85 /
+    // 176 / 860, rows 49 / 87 / 104 / 233), 3.2 beyond (28 qubits with 5 + 5
+    // electrons, 50 / 200 / 800 operators: 130 / 590 / 2290, rows 230 / 460 /
+    // 720).  Rows: 4.5 TB/s with two workgroups per CU, 2.6 with one (28
+    // qubits with 6 + 6 electrons, 200 / 800 operators: 1670 / 2780, k_pool
+    // 1160 / 5230), the launches and the operators' LDS reads besides.
+    const double amp = vtype_bytes(vtype), state = 2.0 * amp * (double)nsa * (double)nsb;
+    const double by_op = 4.0 * amp * pairs, by_row = 4.0 * amp * rows * (double)nsb;
+    const double t_op = by_op / (state <= 4e6 ? 10e6 : state <= 32e6 ? 4.9e6 : 3.2e6);
+    const double t_row = 12.0 + by_row / (per <= 81664 ? 4.5e6 : 2.6e6) + by_op / 60e6;
+    const char *mode = std::getenv("FSV_POOL");  // rows | pairs: whichever the sizes say
+    const bool forced = mode && std::strcmp(mode, "rows") == 0;
+    if ((mode && std::strcmp(mode, "pairs") == 0) || (!forced && t_op <= t_row)) return 0;
     int64_t u = std::min<int64_t>(81664, lim) / per;
     return (int)(u < 1 ? 1 : (u > kPoolU ? kPoolU : u));
 }

@@ -240,7 +240,8 @@ def test_long_rows(fsv, rank):
 # with a remainder of row pairs: FP64 rows of 792 and 1287 columns, FP32 rows of
 # 1287, 1716 and 3003
 @pytest.mark.parametrize("m,na,nb,precision", [(12, 2, 5, 0), (13, 2, 5, 0), (13, 2, 5, 1), (13, 2, 6, 1), (14, 1, 6, 1)])
-def test_pool_long_rows(fsv, m, na, nb, precision):
+def test_pool_long_rows(fsv, m, na, nb, precision, monkeypatch):
+    monkeypatch.setenv("FSV_POOL", "rows")
     from workloads import uccsd_pool
     p = _problem(m, na, nb, 0, seed=700 + 11 * m + nb)
     full = np.asarray(uccsd_pool(m, na, nb), dtype=np.int32)
@@ -250,3 +251,44 @@ def test_pool_long_rows(fsv, m, na, nb, precision):
     want = sector.pool_gradients(psi, p.h, p.g, p.e_core, ops, na, nb, p.ordering, 0)
     _, g = fsv.Plan(p, precision=precision).pool(ops).gradients(p.theta)
     assert np.abs(g - want).max() < (1e-9 if precision == 0 else 1e-4)  # as test_pool_rows
+
+
+# the cases of test_pool_rows through each of the two screening kernels (pools
+# of these sizes take pairs by themselves), and nothing to screen: operators
+# without a pair in the sector
+@pytest.mark.parametrize("mode", ["rows", "pairs"])
+@pytest.mark.parametrize("m,na,nb,excitation,ordering,precision", [
+    (2, 1, 1, 0, 0, 0), (7, 2, 2, 1, 0, 0), (9, 4, 4, 0, 1, 0), (9, 3, 4, 1, 1, 0), (11, 3, 5, 1, 0, 0),
+    (12, 2, 6, 0, 0, 0), (12, 6, 2, 1, 0, 0), (9, 4, 4, 1, 0, 1)])
+def test_pool_both_ways(fsv, mode, m, na, nb, excitation, ordering, precision, monkeypatch):
+    monkeypatch.setenv("FSV_POOL", mode)
+    test_pool_rows(fsv, m, na, nb, excitation, ordering, precision)
+
+
+@pytest.mark.parametrize("mode", ["rows", "pairs", ""])
+def test_pool_without_pairs(fsv, mode, monkeypatch):
+    monkeypatch.setenv("FSV_POOL", mode)
+    p = _problem(4, 1, 1, 0, seed=551)
+    say("pool without pairs", mode)
+    ops = np.array([[4, 6, 2, 0], [5, 7, 3, 1]], dtype=np.int32)
+    _, g = fsv.Plan(p).pool(ops).gradients(p.theta)
+    assert (g == 0.0).all()
+
+
+# the choice between the two, by sizes: the whole pool at 24 qubits is screened
+# by rows, 50 of its operators and a 22-qubit pool pair by pair; both agree
+# (sums of the same products in another order)
+@pytest.mark.parametrize("m,na,nb,k", [(12, 6, 6, 0), (12, 6, 6, 50), (11, 5, 5, 400)])
+def test_pool_choice(fsv, m, na, nb, k, monkeypatch):
+    from workloads import uccsd_pool
+    p = _problem(m, na, nb, 0, seed=560 + m)
+    full = np.asarray(uccsd_pool(m, na, nb), dtype=np.int32)
+    ops = np.ascontiguousarray(full[np.random.default_rng(k).permutation(len(full))[:k or len(full)]])
+    say("pool choice", m, na, nb, k)
+    plan = fsv.Plan(p)
+    got = []
+    for mode in ("", "rows", "pairs"):
+        monkeypatch.setenv("FSV_POOL", mode)
+        got.append(plan.pool(ops).gradients(p.theta)[1])
+    assert np.array_equal(got[0], got[1 if k == 0 else 2])
+    assert np.abs(got[1] - got[2]).max() < 1e-12

@@ -84,7 +84,7 @@ def test_replay_with_busy_streams(hostcheck):
 
 def test_replay_pools_short_lds(hostcheck):
     # where the larger LDS limit is refused, a pool's workgroups fit 64 KiB
-    _replay(hostcheck, "pools_short_lds", FSV_STUB_LDS_REFUSE="k_")
+    _replay(hostcheck, "pools_short_lds", FSV_STUB_LDS_REFUSE="k_", FSV_POOL="rows")
 
 
 def test_replay_whole_sweeps_short_lds(hostcheck):
