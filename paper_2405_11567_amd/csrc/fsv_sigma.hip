@@ -1437,6 +1437,8 @@ hipError_t row_launch(int planes, const SectorTabs &T, const double *C, double *
         FSV_ROW(64, 1, 8, 1, 2, 4);
     else if (n <= 128)
         FSV_ROW(128, 1, 8, 1, 2, 4);
+    else if (n <= 192)
+        FSV_ROW(192, 1, 8, 1, 2, 4);
     else if (n <= 256)
         FSV_ROW(256, 1, 8, 1, 2, 4);
     else if (n <= 512)
