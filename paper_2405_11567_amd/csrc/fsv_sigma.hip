@@ -481,7 +481,9 @@ __device__ __forceinline__ double flip_sign(double v, uint32_t sign_bit) {  // s
 
 // NB buffers of NC pairs (1: long rows, a second barrier per buffer); WV: waves
 // per SIMD the registers must allow.
-template <int BS, int CP, int LH, int NC, int NB, int WV, int OUT>
+// PS groups of wavefronts share the orbital pairs and source rows of a row: each
+// has all of its columns, and their sums meet in LDS.
+template <int BS, int CP, int LH, int NC, int NB, int WV, int PS, int OUT>
 __global__ __launch_bounds__(BS, WV) void k_row(const double *__restrict__ C, double *__restrict__ S,
                                             void *__restrict__ z, double *__restrict__ epart,
                                             const uint32_t *__restrict__ tp, const double *__restrict__ Lp,
@@ -490,8 +492,12 @@ __global__ __launch_bounds__(BS, WV) void k_row(const double *__restrict__ C, do
                                             const double *__restrict__ Lt, const double *__restrict__ da,
                                             const double *__restrict__ heff, const double *__restrict__ hda,
                                             RowArgs a) {
+    static_assert(PS == 1 || (LH == kRowR && NB == 2 && BS / PS % kWave == 0), "whole wavefronts, one pass");
     extern __shared__ double buf[];
-    const int n = a.ncols, ncp = (n + 1) >> 1, zero = 2 * ncp, Wp = zero + 2, tid = threadIdx.x;
+    constexpr int CB = BS / PS;  // threads of a group
+    const int n = a.ncols, ncp = (n + 1) >> 1, zero = 2 * ncp, Wp = zero + 2;
+    const int tid = PS == 1 ? threadIdx.x : threadIdx.x % CB;  // the thread's place in its group
+    const int part = PS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / CB);
     // XCD x takes a contiguous range of rows: neighbouring strings share most
     // of their source rows, which then share that XCD's L2
     int row;
@@ -500,7 +506,7 @@ __global__ __launch_bounds__(BS, WV) void k_row(const double *__restrict__ C, do
         row = x * per + min(x, rem) + (v >> 3);
     }
     if (OUT == ROW_ENERGY && blockIdx.y && *a.im_flag != a.im_epoch) {  // a zero imaginary plane
-        if (tid == 0) epart[a.nrows + row] = 0.0;
+        if (threadIdx.x == 0) epart[a.nrows + row] = 0.0;
         return;
     }
     const double *Cp = C + (int64_t)blockIdx.y * a.plane;
@@ -511,9 +517,9 @@ __global__ __launch_bounds__(BS, WV) void k_row(const double *__restrict__ C, do
     // take a uniform base and a 32-bit byte offset per lane.
     uint32_t off[CP];
 #pragma unroll
-    for (int q = 0; q < CP; ++q) off[q] = 16u * (uint32_t)min(tid + q * BS, ncp - 1);
+    for (int q = 0; q < CP; ++q) off[q] = 16u * (uint32_t)min(tid + q * CB, ncp - 1);
     auto pair = [&](int q) { return (int)(off[q] >> 4); };
-    auto on = [&](int q) { return tid + q * BS < ncp; };
+    auto on = [&](int q) { return tid + q * CB < ncp; };
     auto load2 = [&](const double *p, int q) { return *(const dbl2u *)((const char *)p + off[q]); };
     // a value and, Wp further on, its negative: partner words index either
     auto put2 = [&](double *b, int q, double x, double y) {
@@ -533,7 +539,7 @@ __global__ __launch_bounds__(BS, WV) void k_row(const double *__restrict__ C, do
     };
     constexpr double f = OUT == ROW_ENERGY ? 1.0 : 0.5;  // Y takes half of B_l C (exact scaling)
     double s[CP][2];
-    for (int t = tid; t < (OUT == ROW_ENERGY ? 2 : 2 * NB * NC); t += BS) buf[t * Wp + zero] = 0.0;
+    for (int t = tid; t < (OUT == ROW_ENERGY || PS > 1 ? 2 : 2 * NB * NC); t += CB) buf[t * Wp + zero] = 0.0;
     double en = 0.0;
     const uint32_t *ex = exc + (int64_t)row * a.nexc;
     for (int l0 = 0; l0 < kRowR; l0 += LH) {
@@ -545,7 +551,7 @@ __global__ __launch_bounds__(BS, WV) void k_row(const double *__restrict__ C, do
         for (int q = 0; q < CP; ++q) {
             const dbl2u c = load2(crow, q);
             const double c0 = f * c.x, c1 = f * c.y;
-            if (on(q)) put2(buf, q, c0, c1);
+            if (part == 0 && on(q)) put2(buf, q, c0, c1);
 #pragma unroll
             for (int l = 0; l < LH; ++l) {
                 const dbl2u w = load2(db + (l0 + l) * zero, q);
@@ -561,6 +567,11 @@ __global__ __launch_bounds__(BS, WV) void k_row(const double *__restrict__ C, do
                 const double e = OUT == ROW_ENERGY ? hda[row] + a.ecore : a.ecore;
                 s[q][0] += e * c.x;
                 s[q][1] += e * c.y;
+            }
+            if (PS > 1 && part) {  // the diagonal terms once
+                s[q][0] = s[q][1] = 0.0;
+#pragma unroll
+                for (int l = 0; l < LH; ++l) v[q][0][l] = v[q][1][l] = 0.0;
             }
             fence();
         }
@@ -592,14 +603,15 @@ __global__ __launch_bounds__(BS, WV) void k_row(const double *__restrict__ C, do
             }
         };
         {
-            int k = 0;
+            int k = part * KB;  // whole blocks by turns, the rest of the pairs to the last group
             uint32_t t[KB][CP];
-            for (; k + KB <= a.npair; k += KB) {
+            for (; k + KB <= a.npair; k += PS * KB) {
 #pragma unroll
                 for (int u = 0; u < KB; ++u) words(k + u, t[u]);
 #pragma unroll
                 for (int u = 0; u < KB; ++u) gather(k + u, t[u]);
             }
+            if (PS > 1) k = part == PS - 1 ? a.npair / KB * KB : a.npair;
             for (; k < a.npair; ++k) {
                 words(k, t[0]);
                 gather(k, t[0]);
@@ -639,23 +651,52 @@ __global__ __launch_bounds__(BS, WV) void k_row(const double *__restrict__ C, do
 #pragma unroll
                 for (int q = 0; q < CP; ++q) x[q] = load2(p, q);
             };
-            int e = 0;
+            int e = part * EB;
             dbl2u x[EB][CP];
-            for (; e + EB <= a.noff; e += EB) {
+            for (; e + EB <= a.noff; e += PS * EB) {
 #pragma unroll
                 for (int u = 0; u < EB; ++u) source(e + u, x[u]);
 #pragma unroll
                 for (int u = 0; u < EB; ++u) arow(ex[e + u], x[u]);
             }
+            if (PS > 1) e = part == PS - 1 ? a.noff / EB * EB : a.noff;
             for (; e < a.noff; ++e) {
                 source(e, x[0]);
                 arow(ex[e], x[0]);
             }
         }
+        if (PS > 1) {  // every group gets the sums over all of them
+            __syncthreads();
+            double *red = buf + tid;
+#pragma unroll
+            for (int q = 0; q < CP; ++q)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                    for (int l = 0; l < LH; ++l) red[(((q * 2 + h) * (LH + 1) + l) * PS + part) * CB] = v[q][h][l];
+                    red[(((q * 2 + h) * (LH + 1) + LH) * PS + part) * CB] = s[q][h];
+                }
+            __syncthreads();
+#pragma unroll
+            for (int q = 0; q < CP; ++q)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+#pragma unroll
+                    for (int l = 0; l <= LH; ++l) {
+                        double x = red[((q * 2 + h) * (LH + 1) + l) * PS * CB];
+#pragma unroll
+                        for (int p = 1; p < PS; ++p) x += red[(((q * 2 + h) * (LH + 1) + l) * PS + p) * CB];
+                        if (l < LH)
+                            v[q][h][l] = x;
+                        else
+                            s[q][h] = part ? 0.0 : x;
+                    }
+                }
+        }
         if (OUT == ROW_ENERGY) {
 #pragma unroll
             for (int q = 0; q < CP; ++q)
-                if (on(q)) {
+                if (part == 0 && on(q)) {
                     double t0 = 0.0, t1 = 0.0;
 #pragma unroll
                     for (int l = 0; l < LH; ++l) {
@@ -673,15 +714,20 @@ __global__ __launch_bounds__(BS, WV) void k_row(const double *__restrict__ C, do
 #pragma unroll
                 for (int l = 0; l < LH; ++l) {
                     const dbl2u w = load2(db + (l0 + l) * zero, q);
-                    s[q][0] += w.x * v[q][0][l];
-                    s[q][1] += w.y * v[q][1][l];
+                    s[q][0] += part ? 0.0 : w.x * v[q][0][l];
+                    s[q][1] += part ? 0.0 : w.y * v[q][1][l];
                 }
                 fence();
             }
-            __syncthreads();  // readers of the row in buf are done
+            __syncthreads();  // readers of the row (or of the sums) in buf are done
+            double *mine = buf + part * 2 * NB * NC * Wp;  // the group's buffers
+            if (PS > 1) {
+                for (int t = tid; t < 2 * NB * NC; t += CB) mine[t * Wp + zero] = 0.0;
+            }
             int par = 0;
-            for (int k0 = 0; k0 < a.npair; k0 += NC, par ^= 1) {
-                double *b = buf + (NB == 2 ? par * 2 * NC * Wp : 0);
+            for (int kb = 0; kb < a.npair; kb += PS * NC, par ^= 1) {
+                const int k0 = kb + part * NC;
+                double *b = mine + (NB == 2 ? par * 2 * NC * Wp : 0);
                 uint32_t t[NC][CP];
 #pragma unroll
                 for (int u = 0; u < NC; ++u) words(min(k0 + u, a.npair - 1), t[u]);
@@ -721,11 +767,26 @@ __global__ __launch_bounds__(BS, WV) void k_row(const double *__restrict__ C, do
             }
         }
     }
+    if (PS > 1 && OUT != ROW_ENERGY) {
+        __syncthreads();
+        double *red = buf + tid;
+#pragma unroll
+        for (int q = 0; q < CP; ++q)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) red[((q * 2 + h) * PS + part) * CB] = s[q][h];
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < CP; ++q)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int p = 1; p < PS; ++p) s[q][h] += part ? 0.0 : red[((q * 2 + h) * PS + p) * CB];
+    }
     // results
     double *srow = OUT == ROW_ENERGY ? nullptr : S + (int64_t)blockIdx.y * a.plane + (int64_t)row * a.ld;
 #pragma unroll
     for (int q = 0; q < CP; ++q)
-        if (on(q)) {
+        if (part == 0 && on(q)) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) {
                 const int col = 2 * pair(q) + h;
@@ -743,7 +804,7 @@ __global__ __launch_bounds__(BS, WV) void k_row(const double *__restrict__ C, do
             }
         }
     en = block_sum(en);
-    if (tid == 0) epart[(int64_t)blockIdx.y * a.nrows + row] = en;
+    if (threadIdx.x == 0) epart[(int64_t)blockIdx.y * a.nrows + row] = en;
 }
 
 // One-body tables of k_row from h' (M x M): the off-diagonal values per
@@ -1406,12 +1467,27 @@ int g_lds_max = -1;
 
 // Launch shapes of the row kernels: threads, column pairs per thread, factor
 // columns per pass (k_row) or orbital pairs per chunk (k_ab), pairs per LDS
-// buffer, buffers, and waves per SIMD, by the row's column pairs (n =
-// ceil(columns / 2)).  At 924 columns 256 threads x 2 pairs (four rows
-// resident per CU) took 102 us, 512 x 1 101-112 us, 128 x 4 116 us, two pairs
-// per buffer 139 us.  At 6435 columns 1024 threads x 4 pairs and half of the
+// buffer, buffers, waves per SIMD, and groups per row (k_row), by the row's
+// column pairs (n = ceil(columns / 2)).  At 924 columns 256 threads x 2 pairs
+// (four rows resident per CU) took 102 us, 512 x 1 101-112 us, 128 x 4 116 us,
+// two pairs per buffer 139 us.  At 6435 columns 1024 threads x 4 pairs and half of the
 // factors per pass took 13.5 ms, 512 x 7 14.2 ms, a quarter of the factors per
 // pass 21 ms.
+// Few short rows leave most of the chip idle, and a row takes as long as its chain
+// of M (M - 1) / 2 orbital pairs, however few of them reach a column: 2 of 12 to
+// 15 beta electrons took longer than the former kernel, whose threads followed
+// their columns' excitations (28 qubits with 3 + 2 electrons 86 us a call against
+// 77, 24 qubits with 2 + 2 74 against 68).  With the pairs shared by four groups
+// (two at 257 to 384 columns) these take 73 and 65 us.  The line lies at two
+// workgroups per CU: 495 rows of 66 columns 80 -> 73 us, 792 rows 88 -> 91, 715
+// rows of 286 110 -> 117; and at 28 pairs: 12 qubits (15 pairs) 52 -> 53 us, 16
+// qubits 60 -> 59.
+template <int BS, int CP, int NC, int NB, int PS, int OUT>
+size_t row_lds(int Wp) {
+    const size_t bufs = sizeof(double) * (OUT == ROW_ENERGY ? 2 : 2 * NB * NC * PS) * (size_t)Wp;
+    return PS == 1 ? bufs : std::max(bufs, sizeof(double) * BS * CP * 2 * (kRowR + 1));  // the groups' sums take their place
+}
+
 template <int OUT>
 hipError_t row_launch(int planes, const SectorTabs &T, const double *C, double *S, void *z, double *epart,
                       const int32_t *im_flag, int32_t im_epoch, hipStream_t st) {
@@ -1429,28 +1505,32 @@ hipError_t row_launch(int planes, const SectorTabs &T, const double *C, double *
     a.im_flag = im_flag;
     const int n = (a.ncols + 1) / 2, Wp = 2 * n + 2;
     const dim3 grid((unsigned)a.nrows, (unsigned)planes);
-#define FSV_ROW(BS, CP, LH, NC, NB, WV)                                                                        \
-    hipLaunchKernelGGL((k_row<BS, CP, LH, NC, NB, WV, OUT>), grid, dim3(BS),                                   \
-                       sizeof(double) * (OUT == ROW_ENERGY ? 2 : 2 * NB * NC) * (size_t)Wp, st, C, S, z, epart, \
-                       T.tp, T.Lp, T.hp, T.db, T.hdb, T.excA, T.Lt, T.da, T.heff, T.hda, a)
-    if (n <= 64)
-        FSV_ROW(64, 1, 8, 1, 2, 4);
+    const bool few = (int64_t)planes * a.nrows <= 512 && a.npair >= 28;
+#define FSV_ROW(BS, CP, LH, NC, NB, WV, PS)                                                                     \
+    hipLaunchKernelGGL((k_row<BS, CP, LH, NC, NB, WV, PS, OUT>), grid, dim3(BS), (row_lds<BS, CP, NC, NB, PS, OUT>(Wp)), \
+                       st, C, S, z, epart, T.tp, T.Lp, T.hp, T.db, T.hdb, T.excA, T.Lt, T.da, T.heff, T.hda, a)
+    if (n <= 64 && few)
+        FSV_ROW(256, 1, 8, 1, 2, 4, 4);
+    else if (n <= 64)
+        FSV_ROW(64, 1, 8, 1, 2, 4, 1);
     else if (n <= 128)
-        FSV_ROW(128, 1, 8, 1, 2, 4);
+        FSV_ROW(128, 1, 8, 1, 2, 4, 1);
+    else if (n <= 192 && few)
+        FSV_ROW(384, 1, 8, 1, 2, 4, 2);
     else if (n <= 192)
-        FSV_ROW(192, 1, 8, 1, 2, 4);
+        FSV_ROW(192, 1, 8, 1, 2, 4, 1);
     else if (n <= 256)
-        FSV_ROW(256, 1, 8, 1, 2, 4);
+        FSV_ROW(256, 1, 8, 1, 2, 4, 1);
     else if (n <= 512)
-        FSV_ROW(256, 2, 8, 1, 2, 4);
+        FSV_ROW(256, 2, 8, 1, 2, 4, 1);
     else if (n <= 1024)
-        FSV_ROW(512, 2, 8, 1, 2, 4);
+        FSV_ROW(512, 2, 8, 1, 2, 4, 1);
     else if (n <= 2048)
-        FSV_ROW(512, 4, 8, 1, 2, 2);
+        FSV_ROW(512, 4, 8, 1, 2, 2, 1);
     else if (n <= 4096)
-        FSV_ROW(1024, 4, 4, 1, 1, 4);
+        FSV_ROW(1024, 4, 4, 1, 1, 4, 1);
     else
-        FSV_ROW(1024, 5, 2, 1, 1, 4);
+        FSV_ROW(1024, 5, 2, 1, 1, 4, 1);
 #undef FSV_ROW
     return hipGetLastError();
 }
@@ -1619,11 +1699,11 @@ hipError_t convert_impl(const void *in, void *out, int64_t n, hipStream_t st) {
 
 void init_sigma_kernels() {
     std::vector<const void *> fns = {(const void *)k_sigma_ab};
-#define FSV_ROW_FNS(BS, CP, LH, NC, NB, WV)                                \
-    fns.push_back((const void *)k_row<BS, CP, LH, NC, NB, WV, ROW_ENERGY>); \
-    fns.push_back((const void *)k_row<BS, CP, LH, NC, NB, WV, ROW_S>);      \
-    fns.push_back((const void *)k_row<BS, CP, LH, NC, NB, WV, ROW_ZIP>);    \
-    fns.push_back((const void *)k_row<BS, CP, LH, NC, NB, WV, ROW_ZIP32>)
+#define FSV_ROW_FNS(BS, CP, LH, NC, NB, WV)                                   \
+    fns.push_back((const void *)k_row<BS, CP, LH, NC, NB, WV, 1, ROW_ENERGY>); \
+    fns.push_back((const void *)k_row<BS, CP, LH, NC, NB, WV, 1, ROW_S>);      \
+    fns.push_back((const void *)k_row<BS, CP, LH, NC, NB, WV, 1, ROW_ZIP>);    \
+    fns.push_back((const void *)k_row<BS, CP, LH, NC, NB, WV, 1, ROW_ZIP32>)
     FSV_ROW_FNS(512, 2, 8, 1, 2, 4);
     FSV_ROW_FNS(512, 4, 8, 1, 2, 2);
     FSV_ROW_FNS(1024, 4, 4, 1, 1, 4);
