@@ -1527,10 +1527,8 @@ hipError_t row_launch(int planes, const SectorTabs &T, const double *C, double *
         FSV_ROW(512, 2, 8, 1, 2, 4, 1);
     else if (n <= 2048)
         FSV_ROW(512, 4, 8, 1, 2, 2, 1);
-    else if (n <= 4096)
-        FSV_ROW(1024, 4, 4, 1, 1, 4, 1);
     else
-        FSV_ROW(1024, 5, 2, 1, 1, 4, 1);
+        FSV_ROW(1024, 4, 4, 1, 1, 4, 1);
 #undef FSV_ROW
     return hipGetLastError();
 }
@@ -1555,17 +1553,17 @@ hipError_t ab_launch(const double *C, double *S, const SectorTabs &T, int planes
     hipLaunchKernelGGL((k_abm<W, NT>), grid, dim3(W * kWave),                                                     \
                        sizeof(double) * 8 * (size_t)Wp + sizeof(AbSource) * 4 * (size_t)((a.noff + 4) / 4), st, C, \
                        S, T.tp, T.gp, T.dg, T.excA, a)
-    // k_abm holds a row's offset in 32 bits
-    const bool wide = a.nrows * a.ld >= (int64_t)1 << 29;
-    if (!wide && n <= 64)
+    // k_abm holds a row's offset in 32 bits: at most 32768 rows (15-bit ranks) of two
+    // planes of 2048 columns are 1 GiB
+    if (n <= 64)
         FSV_ABM(4, 2);
-    else if (!wide && n <= 128)
+    else if (n <= 128)
         FSV_ABM(4, 4);
-    else if (!wide && n <= 256)
+    else if (n <= 256)
         FSV_ABM(8, 4);
-    else if (!wide && n <= 512)
+    else if (n <= 512)
         FSV_ABM(8, 8);
-    else if (!wide && n <= 1024)
+    else if (n <= 1024)
         FSV_ABM(16, 8);
     else if (n <= 2048)
         FSV_AB(512, 4, 8, 1);
@@ -1589,9 +1587,11 @@ hipError_t alpha_same_spin(int planes, const SectorTabs &T, const double *C, dou
 }  // namespace
 
 bool row_kernel_fits(int64_t ncols) {
-    // two LDS rows of 8 bytes a column (a row and its negative); with a smaller
-    // limit only the short rows' buffers
-    return ncols >= 2 && ncols <= (g_lds_max >= 163840 ? 10200 : 480);
+    // two LDS rows of 8 bytes a column (a row and its negative), on 1024 threads
+    // of four column pairs; of the sectors of up to 17 orbitals only those with
+    // rows of 11440 and more columns are left out.  With a smaller LDS limit only
+    // the short rows' buffers fit.
+    return ncols >= 2 && ncols <= (g_lds_max >= 163840 ? 8192 : 480);
 }
 
 bool ab_kernel_fits(int64_t ncols) {  // four rows: two buffers and their negatives
@@ -1707,7 +1707,6 @@ void init_sigma_kernels() {
     FSV_ROW_FNS(512, 2, 8, 1, 2, 4);
     FSV_ROW_FNS(512, 4, 8, 1, 2, 2);
     FSV_ROW_FNS(1024, 4, 4, 1, 1, 4);
-    FSV_ROW_FNS(1024, 5, 2, 1, 1, 4);
 #undef FSV_ROW_FNS
     fns.push_back((const void *)k_abm<8, 8>);
     fns.push_back((const void *)k_abm<16, 8>);
