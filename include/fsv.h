@@ -203,14 +203,16 @@ int energy_grad(fsv_plan *plan, const double *theta, void *psi_dev, void *lam_de
  * capture, tight serving loops, harnesses that forbid allocation): the same
  * energy and adjoint gradient as energy_grad (same kernels, same results to
  * rounding), with no allocation in the call.  Its per-call scratch (the
- * interleaved (psi, lam) pairs of the adjoint sweep, the transposes and the
- * factorised intermediate of H psi, the energy and gradient partials) lives in
- * one static device block of 64 MiB per GPU that the library holds until the
- * process ends, not in the plan's workspace.  A plan whose scratch exceeds the
- * block (sector states above roughly 1.3 M amplitudes at K = 200) gets
- * FSV_EINVAL, the needed size in the message; the dense engine gets
- * FSV_ESTATE.  Kernels are launched one by one (no graph is captured or
- * instantiated).  Every call on one GPU shares its block: calls that overlap
+ * interleaved (psi, lam) pairs of the adjoint sweep, the transposes of H psi, the
+ * energy and gradient partials) lives in one static device block of 64 MiB per
+ * GPU that the library holds until the process ends, not in the plan's workspace.  Plans are accepted by a size:
+ * 32 bytes per sector amplitude (40 for FP32 states), 64 KiB per operator, and
+ * 64 bytes more per amplitude where (pq|rs) factorises and rows are longer than
+ * 1137 - n_orb^2 beta strings (a limit of the entry point: the call itself no
+ * longer uses those).  A plan above 64 MiB (about 1.7 M amplitudes at K = 200,
+ * 0.56 M with the longer rows) gets FSV_EINVAL, its size in the message; the
+ * dense engine gets FSV_ESTATE.  Kernels are launched one by one (no graph is
+ * captured or instantiated).  Every call on one GPU shares its block: calls that overlap
  * on one GPU (plans on different streams, or threads) race and must be
  * serialised by the caller.  Nothing in the block needs to start at zero; its
  * contents between calls are unspecified.  Arguments as for energy_grad. */

@@ -747,7 +747,7 @@ int lr_pad(int) { return 8; }  // factor columns of the factorised kernels (rank
 
 void choose_sigma(fsv_plan &P, int &R_out, std::vector<double> &Lt_out) {
     R_out = 0;
-    const char *mode = std::getenv("FSV_SIGMA");  // direct: never factorised
+    const char *mode = std::getenv("FSV_SIGMA");  // direct: never factorised (lowrank: the rule as it is)
     if (mode && std::strcmp(mode, "direct") == 0) return;
     const int M2 = P.M * P.M;
     if (P.nexcA <= 0 || P.nexcB <= 0 || M2 > 511) return;
@@ -1773,10 +1773,11 @@ int build_device(fsv_plan &P) {
             P.na_off[i] = at;
             at += (parts[i] + 255) & ~(size_t)255;
         }
-        // the limit by which plans are accepted is part of the entry point: it
-        // counts 1024 energy partials (the block itself holds more beyond it)
-        // and, for factorised products on rows of more than 1137 - M^2 columns,
-        // eight further sector vectors
+        // the limit by which plans are accepted is part of the entry point and
+        // stays as it was, above what the parts come to: it counts 1024 energy
+        // partials (the block itself holds more beyond it) and, for factorised
+        // products on rows of more than 1137 - M^2 columns, eight further sector
+        // vectors, which a former product took
         P.na_need = at - ((parts[5] + 255) & ~(size_t)255) + 8 * 1024;
         if (R > 0 && (int64_t)R * (P.nexcA + P.nexcB) < (int64_t)P.nexcA * P.nexcB &&
             ((int64_t)M2 + P.nsb) * 9 * 8 * 2 > 163840)
@@ -2161,7 +2162,7 @@ int energy_grad_noalloc(fsv_plan *P, const double *theta, void *psi, void *lam, 
     if (P->K > 0 && !grad_out) return fail(FSV_EINVAL, "grad_out is NULL");
     if (P->engine != 0) return fail(FSV_ESTATE, "energy_grad_noalloc runs on the sector engine");
     if (P->na_need > kScratchBytes)
-        return fail(FSV_EINVAL, "this plan needs %zu bytes of scratch; energy_grad_noalloc has %zu", P->na_need,
+        return fail(FSV_EINVAL, "this plan counts as %zu bytes of scratch; energy_grad_noalloc takes %zu", P->na_need,
                     kScratchBytes);
     void *base = nullptr;
     int rc;
