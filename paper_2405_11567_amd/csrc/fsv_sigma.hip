@@ -1476,12 +1476,13 @@ int g_lds_max = -1;
 // Few short rows leave most of the chip idle, and a row takes as long as its chain
 // of M (M - 1) / 2 orbital pairs, however few of them reach a column: 2 of 12 to
 // 15 beta electrons took longer than the former kernel, whose threads followed
-// their columns' excitations (28 qubits with 3 + 2 electrons 86 us a call against
-// 77, 24 qubits with 2 + 2 74 against 68).  With the pairs shared by four groups
-// (two at 257 to 384 columns) these take 73 and 65 us.  The line lies at two
-// workgroups per CU: 495 rows of 66 columns 80 -> 73 us, 792 rows 88 -> 91, 715
-// rows of 286 110 -> 117; and at 28 pairs: 12 qubits (15 pairs) 52 -> 53 us, 16
-// qubits 60 -> 59.
+// their columns' excitations (us a call: 28 qubits with 3 + 2 electrons 83
+// against 77, 24 qubits with 2 + 2 72 against 67).  With the pairs shared by four
+// groups (two at 257 to 384 columns) these take 68 and 61 us.  The groups run
+// on two and three waves per SIMD, the registers that their sums need (with four
+// they spilled).  The lines lie where the chip is full anyway: 495 rows of 66
+// columns 79 -> 68 us, 1365 rows of 105 130 -> 120, 1716 rows of 78 123 -> 128;
+// 364 rows of 364 columns 94 -> 89, 715 rows of 286 109 -> 113.
 template <int BS, int CP, int NC, int NB, int PS, int OUT>
 size_t row_lds(int Wp) {
     const size_t bufs = sizeof(double) * (OUT == ROW_ENERGY ? 2 : 2 * NB * NC * PS) * (size_t)Wp;
@@ -1505,18 +1506,18 @@ hipError_t row_launch(int planes, const SectorTabs &T, const double *C, double *
     a.im_flag = im_flag;
     const int n = (a.ncols + 1) / 2, Wp = 2 * n + 2;
     const dim3 grid((unsigned)a.nrows, (unsigned)planes);
-    const bool few = (int64_t)planes * a.nrows <= 512 && a.npair >= 28;
+    const int64_t rows = (int64_t)planes * a.nrows;
 #define FSV_ROW(BS, CP, LH, NC, NB, WV, PS)                                                                     \
     hipLaunchKernelGGL((k_row<BS, CP, LH, NC, NB, WV, PS, OUT>), grid, dim3(BS), (row_lds<BS, CP, NC, NB, PS, OUT>(Wp)), \
                        st, C, S, z, epart, T.tp, T.Lp, T.hp, T.db, T.hdb, T.excA, T.Lt, T.da, T.heff, T.hda, a)
-    if (n <= 64 && few)
-        FSV_ROW(256, 1, 8, 1, 2, 4, 4);
+    if (n <= 64 && rows <= 1536)
+        FSV_ROW(256, 1, 8, 1, 2, 2, 4);
     else if (n <= 64)
         FSV_ROW(64, 1, 8, 1, 2, 4, 1);
     else if (n <= 128)
         FSV_ROW(128, 1, 8, 1, 2, 4, 1);
-    else if (n <= 192 && few)
-        FSV_ROW(384, 1, 8, 1, 2, 4, 2);
+    else if (n <= 192 && rows <= 512)
+        FSV_ROW(384, 1, 8, 1, 2, 3, 2);
     else if (n <= 192)
         FSV_ROW(192, 1, 8, 1, 2, 4, 1);
     else if (n <= 256)

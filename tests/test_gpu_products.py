@@ -295,8 +295,8 @@ def test_pool_choice(fsv, m, na, nb, k, monkeypatch):
 
 
 # rows whose orbital pairs are shared by groups of wavefronts (few rows of at most
-# 128 or of 257 to 384 columns) and the next ones that are not: 28 and 21 pairs,
-# 495 and 792 rows, 13 and 715 rows; pairs and source rows that leave a rest
+# 128 or of 257 to 384 columns) and rows that are not (792 rows, two planes; 715
+# rows); pairs and source rows that leave a rest
 @pytest.mark.parametrize("m,na,nb", [
     (8, 1, 2), (8, 7, 2), (8, 3, 4), (9, 4, 2), (11, 1, 2), (12, 4, 2), (12, 5, 2), (13, 1, 3), (13, 4, 3), (14, 2, 3)])
 def test_row_groups(fsv, m, na, nb):
