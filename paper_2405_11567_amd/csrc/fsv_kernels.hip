@@ -373,12 +373,12 @@ __global__ void k_scatter(typename C2<R>::T *__restrict__ lam, const double *__r
 // odd ones by the higher, which spreads them evenly) and written to both;
 // a row's diagonal excitations share its norm.  A wavefront takes kRdmRows
 // sources at a time, which share the reads of row I.  Bound by the latency of
-// the row reads from L2: 2 x 29 us at 24 qubits for a real state, where one
-// wavefront per (I, e) reading both planes took 2 x 80 us (256 threads: 36 us,
-// two sources at a time: 35 us, the column loop unrolled by 8: 37 us).  Small
-// states are all latency, so the row's list is made by one wavefront's ballot
-// (a serial count per entry and a second barrier cost a call 2.5 us at 8 qubits,
-// 8 us at 24).
+// the row reads from L2: 2 x 25 us at 24 qubits for a real state, where one
+// wavefront per (I, e) reading both planes took 2 x 80 us.  Small states are all
+// latency, so the row's list is made by one wavefront's ballot (a serial count
+// per entry and a second barrier took 29 us at 24 qubits and cost a call 2.5 us
+// at 8; with them 256 threads took 36 us, two sources at a time 35 us, the column
+// loop unrolled by 8 37 us).
 constexpr int kRdmRows = 3;
 
 __global__ __launch_bounds__(512) void k_rdm_overlap(const double *__restrict__ A, int64_t ncols,

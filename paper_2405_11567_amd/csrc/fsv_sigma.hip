@@ -965,12 +965,12 @@ __global__ __launch_bounds__(BS) void k_ab(const double *__restrict__ C, double 
 // r of a lane is pair 4 r + lane / 16, so G goes through LDS four pairs at a
 // time, and two workgroups share a CU at 924 columns (59 KB of LDS, 113
 // registers), one exchanging while the other multiplies.  Bound by the matrix
-// cores: 150 us at 24 qubits (924 rows and columns, 37 terms, 78 pairs), of
+// cores: 160 us at 24 qubits (924 rows and columns, 37 terms, 78 pairs), of
 // which the products take 120 us at the 45 TFLOP/s that back-to-back FP64 MFMA
 // reach on this card.  With vector arithmetic (k_ab, whose factors are scalar
-// loads that it waits for) the rows of 70 / 126 / 252 / 462 / 924 / 1716 columns
-// took 24 / 29 / 46 / 88 / 203 / 267 us, here 10.6 / 12 / 17 / 45 / 150 / 146;
-// products of tiles without columns skipped: 163 -> 150.
+// loads that it waits for) the rows of 70 / 126 / 252 / 462 / 924 columns took
+// 24 / 29 / 46 / 88 / 203 us, here 9.6 / 11 / 16 / 41 / 160.  Tiles without columns
+// are skipped.
 struct AbSource {
     const double *a;      // factors
     uint32_t off, sign;  // its row, in bytes; sign bit
@@ -1482,7 +1482,8 @@ int g_lds_max = -1;
 // on two and three waves per SIMD, the registers that their sums need (with four
 // they spilled).  The lines lie where the chip is full anyway: 495 rows of 66
 // columns 79 -> 68 us, 1365 rows of 105 130 -> 120, 1716 rows of 78 123 -> 128;
-// 364 rows of 364 columns 94 -> 89, 715 rows of 286 109 -> 113.
+// 364 rows of 364 columns 94 -> 89, 715 rows of 286 109 -> 113; at 15 pairs (12
+// qubits) 51 -> 48, at 6 (8 qubits) the kernel alone 5.9 -> 7.8.
 template <int BS, int CP, int NC, int NB, int PS, int OUT>
 size_t row_lds(int Wp) {
     const size_t bufs = sizeof(double) * (OUT == ROW_ENERGY ? 2 : 2 * NB * NC * PS) * (size_t)Wp;
@@ -1510,7 +1511,7 @@ hipError_t row_launch(int planes, const SectorTabs &T, const double *C, double *
 #define FSV_ROW(BS, CP, LH, NC, NB, WV, PS)                                                                     \
     hipLaunchKernelGGL((k_row<BS, CP, LH, NC, NB, WV, PS, OUT>), grid, dim3(BS), (row_lds<BS, CP, NC, NB, PS, OUT>(Wp)), \
                        st, C, S, z, epart, T.tp, T.Lp, T.hp, T.db, T.hdb, T.excA, T.Lt, T.da, T.heff, T.hda, a)
-    if (n <= 64 && rows <= 1536)
+    if (n <= 64 && rows <= 1536 && a.npair >= 15)
         FSV_ROW(256, 1, 8, 1, 2, 2, 4);
     else if (n <= 64)
         FSV_ROW(64, 1, 8, 1, 2, 4, 1);
